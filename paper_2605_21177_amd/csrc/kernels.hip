@@ -4,8 +4,8 @@
 //                       token slabs, LDS transpose reads, 32x32x16 bf16 MFMA, fp32
 //                       accumulators; epilogue stores g, a slab partial, or applies
 //                       AdamW straight from the accumulators.
-//   wgrad_simt_kernel   the same contraction with fp32 FMAs for the fp32 configuration
-//                       and for shapes the MFMA kernel's 16-byte loads cannot take.
+//   wgrad_simt_kernel   the same contraction with fp32 FMAs for shapes the MFMA kernel's 16-byte
+//                       loads cannot take (the fp32 configuration: wgrad_f32.hip).
 //   wgrad_edge_kernel   the up-to-9 partial / unaligned rows of a chunk that has too few
 //                       rows for the MFMA kernel to carry them (plain FMA).
 //   colsum_kernel       1-D scale-vector gradient sum_t dY[t,j] * X[t,j], X normalised by the
@@ -24,152 +24,11 @@
 #include <cstdint>
 #include <cstdlib>
 
+#include "device.h"
 #include "internal.h"
+#include "launch.h"
 
 namespace chunkft {
-
-// ---------------------------------------------------------------------------
-// small device helpers
-// ---------------------------------------------------------------------------
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((ext_vector_type(4))) unsigned int u32x4_t;
-typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));   // 16 bytes at any dword
-typedef unsigned int u32x2_a2 __attribute__((ext_vector_type(2), aligned(2)));   // 8 bytes at any bf16
-#define LDS_PTR(T) __attribute__((address_space(3))) T*
-
-// Compile-time loop: the body sees its index as a constant, so register arrays
-// indexed by it never fall back to scratch memory.
-template <int I> struct IntC { static constexpr int value = I; };
-template <int N, int I = 0, class F>
-__device__ __forceinline__ void static_for(F&& f) {
-  if constexpr (I < N) {
-    f(IntC<I>{});
-    static_for<N, I + 1>(f);
-  }
-}
-
-__device__ __forceinline__ unsigned short f32_to_bf16_rne(float f) {
-  unsigned int u = __float_as_uint(f);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return (unsigned short)((u >> 16) | 0x40u);  // quiet NaN
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (unsigned short)(u >> 16);
-}
-
-__device__ __forceinline__ float bf16_bits_to_f32(unsigned short b) {
-  return __uint_as_float(((unsigned int)b) << 16);
-}
-
-template <typename T> __device__ __forceinline__ float load_as_f32(const T* p);
-template <> __device__ __forceinline__ float load_as_f32<float>(const float* p) { return *p; }
-template <> __device__ __forceinline__ float load_as_f32<unsigned short>(const unsigned short* p) {
-  return bf16_bits_to_f32(*p);
-}
-
-// One AdamW update in fp32 (Algorithm 1 lines 19-21).  Every path that updates
-// state goes through this function so that fused and un-fused calls agree bit
-// for bit; contraction is written out (the file is built with -ffp-contract=off).
-// The last line is theta - lr * (m_hat / (sqrt(v_hat) + eps) + wd * theta).
-__device__ __forceinline__ void adamw_update(float g, float& theta, float& m, float& v,
-                                             const AdamWConsts& c) {
-  const float m_new = fmaf(c.beta1, m, c.one_minus_beta1 * g);
-  const float v_new = fmaf(c.beta2, v, c.one_minus_beta2 * (g * g));
-  const float m_hat = m_new * c.inv_bias1;
-  const float v_hat = v_new * c.inv_bias2;
-  // v_sqrt_f32 and v_rcp_f32 are accurate to 1 ulp: far inside the 1e-5 the update is held to,
-  // and an order of magnitude fewer instructions than the correctly rounded sequences
-  const float step = fmaf(m_hat, __builtin_amdgcn_rcpf(__builtin_amdgcn_sqrtf(v_hat) + c.eps), c.weight_decay * theta);
-  theta = fmaf(-c.lr, step, theta);
-  m = m_new;
-  v = v_new;
-}
-
-// Turn one gradient value into its destination.  i = chunk-local index,
-// flat = element index in the tensor, slab = token slab of a split call.
-template <int MODE>
-__device__ __forceinline__ void emit(const Sinks& s, int64_t E, int32_t slab, int64_t i,
-                                     int64_t flat, float val) {
-  if constexpr (MODE == EMIT_STORE) {
-    s.g[i] = val;
-  } else if constexpr (MODE == EMIT_ACCUM) {
-    s.g[i] += val;
-  } else if constexpr (MODE == EMIT_PARTIAL) {
-    s.ws[(int64_t)slab * s.ws_pitch + i] = val;
-  } else {
-    float th = s.master[i], mm = s.m[i], vv = s.v[i];
-    adamw_update(val, th, mm, vv, s.c);
-    s.master[i] = th;
-    s.m[i] = mm;
-    s.v[i] = vv;
-    if (s.w_kind == W_BF16) ((unsigned short*)s.W)[flat] = f32_to_bf16_rne(th);
-    else if (s.w_kind == W_F32) ((float*)s.W)[flat] = th;
-  }
-}
-
-// Four consecutive gradient values at once.  The 16-byte fp32 accesses work at
-// any 4-byte alignment but stream about 15% faster when 16-byte aligned, whereas
-// the 8-byte bf16 store costs next to nothing at 2-byte alignment: callers align
-// their groups of four to the fp32 arrays.  Pointers are already offset to the
-// first of the four elements.
-struct Vec4Sink {
-  float* g;        // EMIT_STORE / EMIT_ACCUM / EMIT_PARTIAL destination
-  float* master;
-  float* m;
-  float* v;
-  void* W;         // low-precision copy (bf16 or fp32) or nullptr
-};
-
-// Chunk state and gradients are streamed: read once, written once, never reused
-// by the same kernel, and far larger than the caches.  All these accesses carry
-// the non-temporal hint.
-struct State4 {
-  f32x4_u th, mm, vv;
-};
-
-template <int MODE>
-__device__ __forceinline__ State4 load_state4(const Vec4Sink& d) {
-  State4 st;
-  if constexpr (MODE == EMIT_ACCUM) {
-    st.th = __builtin_nontemporal_load((const f32x4_u*)d.g);
-  } else if constexpr (MODE == EMIT_ADAMW) {
-    st.th = __builtin_nontemporal_load((const f32x4_u*)d.master);
-    st.mm = __builtin_nontemporal_load((const f32x4_u*)d.m);
-    st.vv = __builtin_nontemporal_load((const f32x4_u*)d.v);
-  }
-  return st;
-}
-
-template <int MODE>
-__device__ __forceinline__ void finish4(const Vec4Sink& d, int w_kind, const AdamWConsts& c, f32x4_u val,
-                                        State4 st) {
-  if constexpr (MODE == EMIT_STORE || MODE == EMIT_PARTIAL) {
-    // the gradient is read again by the next kernel (AdamW or the slab reduction):
-    // a plain store lets the 256 MB memory-side cache keep it
-    *(f32x4_u*)d.g = val;
-  } else if constexpr (MODE == EMIT_ACCUM) {
-    st.th += val;
-    *(f32x4_u*)d.g = st.th;
-  } else {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      float t = st.th[e], a = st.mm[e], b = st.vv[e];
-      adamw_update(val[e], t, a, b, c);
-      st.th[e] = t; st.mm[e] = a; st.vv[e] = b;
-    }
-    __builtin_nontemporal_store(st.th, (f32x4_u*)d.master);
-    __builtin_nontemporal_store(st.mm, (f32x4_u*)d.m);
-    __builtin_nontemporal_store(st.vv, (f32x4_u*)d.v);
-    if (w_kind == W_BF16) {
-      u32x2_a2 pk;
-      pk[0] = (unsigned int)f32_to_bf16_rne(st.th[0]) | ((unsigned int)f32_to_bf16_rne(st.th[1]) << 16);
-      pk[1] = (unsigned int)f32_to_bf16_rne(st.th[2]) | ((unsigned int)f32_to_bf16_rne(st.th[3]) << 16);
-      __builtin_nontemporal_store(pk, (u32x2_a2*)d.W);
-    } else if (w_kind == W_F32) {
-      __builtin_nontemporal_store(st.th, (f32x4_u*)d.W);
-    }
-  }
-}
 
 // ---------------------------------------------------------------------------
 // bf16 MFMA weight-gradient kernel
@@ -373,10 +232,6 @@ __device__ __forceinline__ bf16x4 lds_tr_read(unsigned addr) {
   bf16x4 r;
   asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(r) : "v"(addr), "n"(OFF) : "memory");
   return r;
-}
-// s_waitcnt vmcnt(N) alone (gfx9 encoding: vmcnt in bits 3:0 and 15:14, others "no wait")
-template <int N> __device__ __forceinline__ void wait_vmcnt() {
-  __builtin_amdgcn_s_waitcnt((N & 0xF) | (7 << 4) | (0xF << 8) | ((N >> 4) << 14));
 }
 #define WAIT_HALVES(h)                                                                                   \
   asm volatile("s_waitcnt lgkmcnt(0)"                                                                    \
@@ -1327,15 +1182,6 @@ __device__ __forceinline__ void mfma_tile16(const MfmaParams& q, const int item,
   TIMELINE_STAMP(q, item, 3);
 }
 
-// Workgroup ids are dealt round-robin to the 8 XCDs; each XCD gets one contiguous run of work
-// items so that tiles sharing dY rows / X columns meet in the same L2.  Returns -1 for the
-// padding workgroups at the end of the grid.
-__device__ __forceinline__ int xcd_work_item(int n_items) {
-  const int per_xcd = (n_items + 7) >> 3;
-  const int item = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
-  return item < n_items ? item : -1;
-}
-
 // Two workgroups share a compute unit.  Started together they run their MFMA loops
 // together and then their HBM-bound epilogues together; with stagger > 0 the second
 // one of each pair (workgroups are dealt to the 32 compute units of an XCD in order:
@@ -1443,7 +1289,7 @@ __global__ __launch_bounds__(C::NT, 2) void wgrad_group_kernel(const GroupParams
 }
 
 // ---------------------------------------------------------------------------
-// FMA weight-gradient kernel (fp32 configuration and unaligned bf16 shapes)
+// FMA weight-gradient kernel (bf16 shapes the MFMA kernel's 16-byte loads cannot take)
 // ---------------------------------------------------------------------------
 struct SimtParams {
   WgradProblem p;
@@ -1884,8 +1730,6 @@ __global__ __launch_bounds__(256) void elementwise_kernel(const ElemParams q) {
 // ---------------------------------------------------------------------------
 namespace {
 
-inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
-
 // Start delay (units of 8128 cycles) of the second workgroup of each compute unit in the fused
 // call, whose epilogue is long and HBM-bound: measured best at 6 for 1024 tokens (196 us against
 // 200 us at 8, 208 us at 0), flat between 6 and 10 for 4096 and 8192; the plain gradient gains
@@ -1908,24 +1752,14 @@ using FusedCfg = RingCfg<1, 3, 32>;
 
 template <class C, int MODE>
 int launch_mfma_mode(const MfmaParams& q, int grid, hipStream_t st) {
-  // The dynamic LDS limit is a per-device attribute of the kernel; raising it is idempotent, so
-  // a race between threads only repeats the call.
-  static std::atomic<bool> attr_set[kMaxDevices] = {};
-  const auto kern = &wgrad_mfma_kernel<C, MODE>;
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return (int)hipErrorInvalidDevice;
-  if (dev < 0 || dev >= kMaxDevices || !attr_set[dev].load(std::memory_order_acquire)) {
-    hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)C::LDS_BYTES);
-    if (e != hipSuccess) return (int)e;
-    if (dev >= 0 && dev < kMaxDevices) attr_set[dev].store(true, std::memory_order_release);
-  }
+  const int err = raise_lds_limit<&wgrad_mfma_kernel<C, MODE>>(C::LDS_BYTES);
+  if (err != 0) return err;
   MfmaArgs args;
   args.q[0] = q;
 #ifdef CHUNKFT_TIMELINE
   args.q[0].timeline = g_timeline_words >= (size_t)q.n_tile_items * 8 ? g_timeline : nullptr;
 #endif
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(C::NT), C::LDS_BYTES, st, args);
+  hipLaunchKernelGGL((wgrad_mfma_kernel<C, MODE>), dim3(grid), dim3(C::NT), C::LDS_BYTES, st, args);
   return (int)hipGetLastError();
 }
 
@@ -2035,16 +1869,8 @@ int launch_wgrad_bf16_mfma(const WgradProblem& p, int mode, const Sinks& s, void
 // ---- grouped fused call
 template <class C>
 static int launch_group_cfg(const GroupSegment* segs, int n, hipStream_t st) {
-  static std::atomic<bool> attr_set[kMaxDevices] = {};
-  const auto kern = &wgrad_group_kernel<C>;
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return (int)hipErrorInvalidDevice;
-  if (dev < 0 || dev >= kMaxDevices || !attr_set[dev].load(std::memory_order_acquire)) {
-    hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)C::LDS_BYTES);
-    if (e != hipSuccess) return (int)e;
-    if (dev >= 0 && dev < kMaxDevices) attr_set[dev].store(true, std::memory_order_release);
-  }
+  const int lds_err = raise_lds_limit<&wgrad_group_kernel<C>>(C::LDS_BYTES);
+  if (lds_err != 0) return lds_err;
   for (int first = 0; first < n; first += kGroupMax) {
     const int count = n - first < kGroupMax ? n - first : kGroupMax;
     GroupParams gp{};
@@ -2071,7 +1897,7 @@ static int launch_group_cfg(const GroupSegment* segs, int n, hipStream_t st) {
     gp.n_segs = count;
     gp.n_items = (int32_t)items;
     const int grid = (gp.n_items + 7) / 8 * 8;
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(C::NT), C::LDS_BYTES, st, gp);
+    hipLaunchKernelGGL((wgrad_group_kernel<C>), dim3(grid), dim3(C::NT), C::LDS_BYTES, st, gp);
     const int err = (int)hipGetLastError();
     if (err != 0) return err;
   }
@@ -2096,6 +1922,7 @@ static int launch_simt_t(const SimtParams& q, int grid, int mode, hipStream_t st
 }
 
 int launch_wgrad_simt(const WgradProblem& p, int dtype, int mode, const Sinks& s, void* stream) {
+  if (dtype == 0) return launch_wgrad_f32(p, mode, s, stream);
   SimtParams q{};
   q.p = p;
   q.s = s;
@@ -2107,9 +1934,7 @@ int launch_wgrad_simt(const WgradProblem& p, int dtype, int mode, const Sinks& s
   q.tiles_m = (int32_t)tiles_m;
   q.tiles_n = (int32_t)tiles_n;
   const int64_t grid = tiles_m * tiles_n * p.S;
-  hipStream_t st = (hipStream_t)stream;
-  return dtype == 0 ? launch_simt_t<float>(q, (int)grid, mode, st)
-                    : launch_simt_t<unsigned short>(q, (int)grid, mode, st);
+  return launch_simt_t<unsigned short>(q, (int)grid, mode, (hipStream_t)stream);
 }
 
 template <typename T, int NORM>

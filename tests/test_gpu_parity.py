@@ -96,6 +96,22 @@ def test_config1_fp32_layer():
     _full_check(case, begin, end)
 
 
+# The fp32 gradient: rows that are whole 16-byte pieces go through the LDS ring (slabs of 8 tokens, tiles of
+# 32 x 32 by 8 waves, of 32 x 64 by 4 from 257 tiles on), others straight to registers (32 x 32 by 16 waves, 32 x
+# 128 by 4).  Sizes at the edges: tensors smaller than a tile, one row or column more or less than a tile, token
+# counts around a slab, a step of two tokens and a wave's share.  The tolerance is _full_check's 1e-5; the
+# error of an fp32 sum of T products is about sqrt(T) 2^-24, 2e-6 at the longest here.
+@pytest.mark.parametrize("out,n_in,T,split_k", [
+    (1, 1, 1, None), (3, 40, 5, None), (32, 64, 8, None), (36, 68, 9, None), (28, 132, 64, None), (132, 60, 31, None),
+    (100, 128, 257, 3), (548, 1028, 70, None), (544, 1088, 8, 1),           # ring: few tiles, more than 256
+    (31, 33, 17, None), (33, 31, 16, 2), (33, 129, 130, None), (547, 1027, 33, None), (545, 1024, 2, None)])
+def test_fp32_tiles_and_token_remainders(out, n_in, T, split_k):
+    case = WL.linear_case(np.random.default_rng(31 * out + n_in), "f", out, n_in, T, WL.F32, 1e-3)
+    n = out * n_in
+    for begin, end in {(0, n), (n // 3, n - n // 5), (n // 2, n // 2 + 1)}:
+        _full_check(case, begin, end, split_k=split_k if split_k and T >= 2 * split_k else None, warm=True, step=2)
+
+
 def test_config1_standalone_adamw_elementwise():
     """The AdamW entry point alone, both sides fed the same fp32 gradient."""
     case, begin, end = WL.config1()
