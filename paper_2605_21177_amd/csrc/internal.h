@@ -98,9 +98,10 @@ int launch_fused_group(const GroupSegment* segs, int n, bool large_tile, void* s
 
 // All launchers return a hipError_t as int (0 = success).
 int launch_wgrad_bf16_mfma(const WgradProblem& p, int mode, const Sinks& s, void* stream);
-// Matrices off the bf16 MFMA path: fp32 (the fp32 matrix kernel) and bf16 shapes without 16-byte rows.
+// Matrices without 16-byte bf16 rows: fp32 ones go to launch_wgrad_f32, bf16 ones to launch_wgrad_ragged.
 int launch_wgrad_simt(const WgradProblem& p, int dtype, int mode, const Sinks& s, void* stream);
 int launch_wgrad_f32(const WgradProblem& p, int mode, const Sinks& s, void* stream);
+int launch_wgrad_ragged(const WgradProblem& p, int mode, const Sinks& s, void* stream);
 int launch_colsum(const WgradProblem& p, int dtype, int mode, const Sinks& s, void* stream);
 // Scale vector of RMSNorm / LayerNorm with the normalisation done here: p.X is the raw input,
 // stats is a device scratch of 2 * T floats.

@@ -4,8 +4,6 @@
 //                       token slabs, LDS transpose reads, 32x32x16 bf16 MFMA, fp32
 //                       accumulators; epilogue stores g, a slab partial, or applies
 //                       AdamW straight from the accumulators.
-//   wgrad_simt_kernel   the same contraction with fp32 FMAs for shapes the MFMA kernel's 16-byte
-//                       loads cannot take (the fp32 configuration: wgrad_f32.hip).
 //   wgrad_edge_kernel   the up-to-9 partial / unaligned rows of a chunk that has too few
 //                       rows for the MFMA kernel to carry them (plain FMA).
 //   colsum_kernel       1-D scale-vector gradient sum_t dY[t,j] * X[t,j], X normalised by the
@@ -13,6 +11,7 @@
 //   embed_wgrad_kernel  embedding table gradient: per table row the sum of the dY rows of
 //                       the tokens that name it, in token order.
 //   elementwise_kernel  AdamW over a chunk and/or the fixed-order sum of slab partials.
+// fp32 layers are in wgrad_f32.hip, bf16 layers without 16-byte rows in wgrad_ragged.hip.
 //
 // The operations are those of the paper's Section 3.1 (gradient of the active
 // slices only, through the chunk-aware operators of Algorithm 1 line 8) and
@@ -1289,79 +1288,6 @@ __global__ __launch_bounds__(C::NT, 2) void wgrad_group_kernel(const GroupParams
 }
 
 // ---------------------------------------------------------------------------
-// FMA weight-gradient kernel (bf16 shapes the MFMA kernel's 16-byte loads cannot take)
-// ---------------------------------------------------------------------------
-struct SimtParams {
-  WgradProblem p;
-  int64_t r0;
-  int32_t tiles_m, tiles_n;
-  Sinks s;
-};
-
-template <typename T, int MODE>
-__global__ __launch_bounds__(256) void wgrad_simt_kernel(const SimtParams q) {
-  constexpr int BM = 64, BN = 64, BK = 16;
-  __shared__ float As[BK][BM + 4];
-  __shared__ float Bs[BK][BN + 4];
-  const WgradProblem& p = q.p;
-  const int n_tiles = q.tiles_m * q.tiles_n;
-  const int slab = blockIdx.x / n_tiles;
-  const int tile = blockIdx.x - slab * n_tiles;
-  const int tile_m = tile / q.tiles_n, tile_n = tile % q.tiles_n;
-  const int64_t row0 = q.r0 + (int64_t)tile_m * BM;
-  const int64_t col0 = (int64_t)tile_n * BN;
-  const int64_t k_begin = (int64_t)slab * p.kslab;
-  const int64_t k_end = (k_begin + p.kslab < p.T) ? k_begin + p.kslab : p.T;
-  const T* dY = (const T*)p.dY;
-  const T* X = (const T*)p.X;
-  const int tid = threadIdx.x;
-  const int tx = tid & 15, ty = tid >> 4;
-  float acc[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
-
-  for (int64_t k0 = k_begin; k0 < k_end; k0 += BK) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int id = tid + i * 256;
-      const int kr = id >> 6, mm = id & 63;
-      const int64_t t = k0 + kr;
-      const int64_t r = row0 + mm, c = col0 + mm;
-      As[kr][mm] = (t < k_end && r < p.out) ? load_as_f32<T>(dY + t * p.lddy + r) : 0.f;
-      Bs[kr][mm] = (t < k_end && c < p.in) ? load_as_f32<T>(X + t * p.ldx + c) : 0.f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < BK; ++k) {
-      float a[4], b[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = As[k][ty * 4 + i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = Bs[k][tx * 4 + j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-    }
-    __syncthreads();
-  }
-  const int64_t E = p.end - p.begin;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int64_t row = row0 + ty * 4 + i;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int64_t col = col0 + tx * 4 + j;
-      const int64_t flat = row * p.in + col;
-      if (col < p.in && flat >= p.begin && flat < p.end)
-        emit<MODE>(q.s, E, slab, flat - p.begin, flat, acc[i][j]);
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
 // scale-vector gradient: g[j] = sum_t dY[t, j] * X[t, j]
 // ---------------------------------------------------------------------------
 // With NORM the operator normalises its input itself: X is the raw input and stats[2t],
@@ -1910,31 +1836,8 @@ int launch_fused_group(const GroupSegment* segs, int n, bool large_tile, void* s
                     : launch_group_cfg<FusedCfg>(segs, n, (hipStream_t)stream);
 }
 
-template <typename T>
-static int launch_simt_t(const SimtParams& q, int grid, int mode, hipStream_t st) {
-  switch (mode) {
-    case EMIT_STORE: hipLaunchKernelGGL((wgrad_simt_kernel<T, EMIT_STORE>), dim3(grid), dim3(256), 0, st, q); break;
-    case EMIT_ACCUM: hipLaunchKernelGGL((wgrad_simt_kernel<T, EMIT_ACCUM>), dim3(grid), dim3(256), 0, st, q); break;
-    case EMIT_PARTIAL: hipLaunchKernelGGL((wgrad_simt_kernel<T, EMIT_PARTIAL>), dim3(grid), dim3(256), 0, st, q); break;
-    default: hipLaunchKernelGGL((wgrad_simt_kernel<T, EMIT_ADAMW>), dim3(grid), dim3(256), 0, st, q); break;
-  }
-  return (int)hipGetLastError();
-}
-
 int launch_wgrad_simt(const WgradProblem& p, int dtype, int mode, const Sinks& s, void* stream) {
-  if (dtype == 0) return launch_wgrad_f32(p, mode, s, stream);
-  SimtParams q{};
-  q.p = p;
-  q.s = s;
-  q.r0 = p.begin / p.in;
-  const int64_t rows = (p.end - 1) / p.in - q.r0 + 1;
-  const int64_t tiles_m = ceil_div(rows, 64), tiles_n = ceil_div(p.in, 64);
-  if (tiles_m > 0x7fffffff || tiles_n > 0x7fffffff || tiles_m * tiles_n > 0x7fffffff / p.S)
-    return (int)hipErrorInvalidValue;                  // the grid is counted in 32 bits
-  q.tiles_m = (int32_t)tiles_m;
-  q.tiles_n = (int32_t)tiles_n;
-  const int64_t grid = tiles_m * tiles_n * p.S;
-  return launch_simt_t<unsigned short>(q, (int)grid, mode, (hipStream_t)stream);
+  return dtype == 0 ? launch_wgrad_f32(p, mode, s, stream) : launch_wgrad_ragged(p, mode, s, stream);
 }
 
 template <typename T, int NORM>

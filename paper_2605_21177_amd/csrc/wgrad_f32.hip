@@ -15,20 +15,11 @@
 
 #include <cstdint>
 
-#include "device.h"
-#include "internal.h"
-#include "launch.h"
+#include "tiles.h"
 
 namespace chunkft {
 
 namespace {
-
-struct F32Params {
-  WgradProblem p;
-  int64_t r0;                  // first row of the chunk
-  int32_t tiles_m, tiles_n, n_items, group_m;
-  Sinks s;
-};
 
 template <int TM_, int TN_, int WK_>
 struct F32Cfg {
@@ -60,38 +51,6 @@ template <> struct FloatN<1> { typedef float reg, mem; };
 __device__ __forceinline__ float element(float v, int) { return v; }
 template <class V> __device__ __forceinline__ float element(V v, int i) { return v[i]; }
 
-// Which tile and which tokens a workgroup takes.
-struct Place {
-  int64_t row0, col0;          // first row and column that this tile emits
-  int64_t row_b, col_b;        // first row and column that it loads
-  int64_t k_begin, k_end;      // tokens of its slab
-  int slab;
-};
-
-template <class C>
-__device__ __forceinline__ Place place_of(const F32Params& q, int item) {
-  const WgradProblem& p = q.p;
-  Place w;
-  const int n_tiles = q.tiles_m * q.tiles_n;
-  w.slab = item / n_tiles;
-  const int tile = item - w.slab * n_tiles;
-  // tile order inside an XCD's run of items as in the bf16 kernel: groups of tile rows
-  const int per_group = q.group_m * q.tiles_n;
-  const int first_m = tile / per_group * q.group_m;
-  const int gsz = (q.tiles_m - first_m < q.group_m) ? q.tiles_m - first_m : q.group_m;
-  const int in_grp = tile % per_group;
-  w.row0 = q.r0 + (int64_t)(first_m + in_grp % gsz) * C::BM;
-  w.col0 = (int64_t)(in_grp / gsz) * C::BN;
-  // A tile that would reach past the tensor is moved back inside it (the rows and columns it then shares
-  // with its neighbour are not emitted); a tensor smaller than a tile only meets the 32 x 32
-  // configuration, whose lanes past the end re-read the last row or column.
-  w.row_b = (w.row0 + C::BM > p.out && p.out >= C::BM) ? p.out - C::BM : w.row0;
-  w.col_b = (w.col0 + C::BN > p.in && p.in >= C::BN) ? p.in - C::BN : w.col0;
-  w.k_begin = (int64_t)w.slab * p.kslab;
-  w.k_end = (w.k_begin + p.kslab < p.T) ? w.k_begin + p.kslab : p.T;
-  return w;
-}
-
 template <class C>
 __device__ __forceinline__ void clear(f32x16 (&acc)[C::TM][C::TN]) {
 #pragma unroll
@@ -111,12 +70,10 @@ __device__ __forceinline__ void mma(f32x16 (&acc)[C::TM][C::TN], typename FloatN
     for (int j = 0; j < C::TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(element(a, i), element(b, j), acc[i][j], 0, 0, 0);
 }
 
-// The waves' partial tiles meet in LDS and leave row by row, four columns per lane, up to four groups of
-// them per trip so that their state loads travel together.
+// The waves' partial tiles meet in LDS and leave row by row.
 template <class C, int MODE>
-__device__ __forceinline__ void finish_tile(const F32Params& q, const Place& w, const f32x16 (&acc)[C::TM][C::TN],
+__device__ __forceinline__ void finish_tile(const TileGrid& q, const Place& w, const f32x16 (&acc)[C::TM][C::TN],
                                             float* staged, int wave, int lane) {
-  const WgradProblem& p = q.p;
   // register v of block (i, j) is row TM * ((v / 4) * 8 + (lane / 32) * 4 + v % 4) + i, column TN * (lane % 32) + j
   float* const mine = staged + wave * (C::BM * C::PITCH) + C::TN * (lane & 31);
 #pragma unroll
@@ -128,67 +85,19 @@ __device__ __forceinline__ void finish_tile(const F32Params& q, const Place& w, 
       for (int j = 0; j < C::TN; ++j) dst[j] = acc[i][j][v];
     }
   __syncthreads();
-  const int64_t E = p.end - p.begin;
-  float* const g_dst = MODE == EMIT_PARTIAL ? q.s.ws + (int64_t)w.slab * q.s.ws_pitch : q.s.g;
-  constexpr int LPR = C::BN / 4, GROUPS = C::BM * LPR;
-  constexpr int STEP = GROUPS < C::NT ? 1 : (GROUPS / C::NT < 4 ? GROUPS / C::NT : 4);
-  static_assert(GROUPS < C::NT || GROUPS % (C::NT * STEP) == 0, "whole trips");
-  for (int o = threadIdx.x; o < GROUPS; o += C::NT * STEP) {
-    Vec4Sink d[STEP];
-    State4 st[STEP];
-    bool whole[STEP], some[STEP];
-    int64_t flat[STEP];
-#pragma unroll
-    for (int u = 0; u < STEP; ++u) {
-      const int rr = (o + u * C::NT) / LPR, cc = (o + u * C::NT) % LPR * 4;
-      const int64_t row = w.row_b + rr, col = w.col_b + cc;
-      flat[u] = row * p.in + col;
-      some[u] = row >= w.row0 && row < p.out && flat[u] < p.end && flat[u] + 4 > p.begin && col < p.in && col + 4 > w.col0;
-      whole[u] = some[u] && flat[u] >= p.begin && flat[u] + 4 <= p.end && col >= w.col0 && col + 4 <= p.in;
-      const int64_t i = flat[u] - p.begin;
-      d[u].g = g_dst + i;
-      d[u].master = q.s.master + i;
-      d[u].m = q.s.m + i;
-      d[u].v = q.s.v + i;
-      d[u].W = q.s.w_kind == W_BF16 ? (void*)((unsigned short*)q.s.W + flat[u]) : (void*)((float*)q.s.W + flat[u]);
-      if (whole[u]) st[u] = load_state4<MODE>(d[u]);
-    }
-#pragma unroll
-    for (int u = 0; u < STEP; ++u) {
-      if (!some[u]) continue;
-      const int rr = (o + u * C::NT) / LPR, cc = (o + u * C::NT) % LPR * 4;
-      const float* src = staged + rr * C::PITCH + cc;
-      float4 val = *(const float4*)src;
-#pragma unroll
-      for (int k = 1; k < C::WK; ++k) {
-        const float4 x = *(const float4*)(src + k * (C::BM * C::PITCH));
-        val.x += x.x; val.y += x.y; val.z += x.z; val.w += x.w;
-      }
-      if (whole[u]) {
-        finish4<MODE>(d[u], q.s.w_kind, q.s.c, f32x4_u{val.x, val.y, val.z, val.w}, st[u]);
-      } else {
-        const float e4[4] = {val.x, val.y, val.z, val.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int64_t col = w.col_b + cc + e, f = flat[u] + e;
-          if (col >= w.col0 && col < p.in && f >= p.begin && f < p.end)
-            emit<MODE>(q.s, E, w.slab, f - p.begin, f, e4[e]);
-        }
-      }
-    }
-  }
+  emit_rows<MODE, C::BM, C::BN, C::PITCH, C::NT, C::WK>(q, w, staged, [](int rr) { return rr; });
 }
 
 // Operands straight from memory: any alignment, any size.
 template <class C, int MODE>
-__global__ __launch_bounds__(C::NT) void wgrad_f32_kernel(const F32Params q) {
+__global__ __launch_bounds__(C::NT) void wgrad_f32_kernel(const TileGrid q) {
   extern __shared__ __attribute__((aligned(16))) float staged[];        // [WK][BM][PITCH]
   typedef typename FloatN<C::TM>::reg VA;
   typedef typename FloatN<C::TN>::reg VB;
   const int item = xcd_work_item(q.n_items);
   if (item < 0) return;
   const WgradProblem& p = q.p;
-  const Place w = place_of<C>(q, item);
+  const Place w = place_of<C::BM, C::BN>(q, item);
   const int lane = threadIdx.x & 63, half = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int steps = (int)((w.k_end - w.k_begin + 1) >> 1);
@@ -289,14 +198,14 @@ __device__ __forceinline__ typename FloatN<N>::reg lds_read(unsigned addr) {
 }
 
 template <class C, int MODE>
-__global__ __launch_bounds__(C::NT, 2) void wgrad_f32_ring_kernel(const F32Params q) {
+__global__ __launch_bounds__(C::NT, 2) void wgrad_f32_ring_kernel(const TileGrid q) {
   extern __shared__ __attribute__((aligned(1024))) float staged[];
   typedef typename FloatN<C::TM>::reg VA;
   typedef typename FloatN<C::TN>::reg VB;
   const int item = xcd_work_item(q.n_items);
   if (item < 0) return;
   const WgradProblem& p = q.p;
-  const Place w = place_of<C>(q, item);
+  const Place w = place_of<C::BM, C::BN>(q, item);
   const int lane = threadIdx.x & 63, half = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int slabs = (int)((w.k_end - w.k_begin + C::KS - 1) / C::KS);
@@ -411,7 +320,7 @@ template <class C> constexpr bool is_ring = false;
 template <int TM, int TN, int WK, int NS> constexpr bool is_ring<F32RingCfg<TM, TN, WK, NS>> = true;
 
 template <auto Kern, class C>
-int launch_kernel(const F32Params& q, hipStream_t st) {
+int launch_kernel(const TileGrid& q, hipStream_t st) {
   const int err = raise_lds_limit<Kern>(C::LDS_BYTES);
   if (err != 0) return err;
   hipLaunchKernelGGL(Kern, dim3((q.n_items + 7) / 8 * 8), dim3(C::NT), C::LDS_BYTES, st, q);
@@ -419,25 +328,15 @@ int launch_kernel(const F32Params& q, hipStream_t st) {
 }
 
 template <class C, int MODE>
-int launch_mode(const F32Params& q, hipStream_t st) {
+int launch_mode(const TileGrid& q, hipStream_t st) {
   if constexpr (is_ring<C>) return launch_kernel<&wgrad_f32_ring_kernel<C, MODE>, C>(q, st);
   else return launch_kernel<&wgrad_f32_kernel<C, MODE>, C>(q, st);
 }
 
 template <class C>
 int launch_cfg(const WgradProblem& p, int mode, const Sinks& s, hipStream_t st) {
-  F32Params q{};
-  q.p = p;
-  q.s = s;
-  q.r0 = p.begin / p.in / C::ROW_STEP * C::ROW_STEP;
-  const int64_t rows = (p.end - 1) / p.in - q.r0 + 1;
-  const int64_t tiles_m = ceil_div(rows, C::BM), tiles_n = ceil_div(p.in, C::BN);
-  if (tiles_m > 0x3fffffff || tiles_n > 0x3fffffff || tiles_m * tiles_n > 0x3fffffff / p.S)
-    return (int)hipErrorInvalidValue;                  // work items are counted in 32 bits
-  q.tiles_m = (int32_t)tiles_m;
-  q.tiles_n = (int32_t)tiles_n;
-  q.n_items = (int32_t)(tiles_m * tiles_n * p.S);
-  q.group_m = 8;
+  TileGrid q;
+  if (!fill_grid<C::BM, C::BN>(q, p, s, C::ROW_STEP)) return (int)hipErrorInvalidValue;
   switch (mode) {
     case EMIT_STORE: return launch_mode<C, EMIT_STORE>(q, st);
     case EMIT_ACCUM: return launch_mode<C, EMIT_ACCUM>(q, st);

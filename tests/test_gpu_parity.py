@@ -292,6 +292,19 @@ def test_bf16_unaligned_shape_takes_fma_path():
     _full_check(case, 101, 9999, split_k=2)
 
 
+# Layers without 16-byte rows: 64 x 64 tiles in four token groups (few tiles), 64 x 128 in two (more than 256
+# tiles of 128 x 128), 128 x 128 (the same with more than 1024 tokens), element by element below 64 rows or
+# columns.  Sizes at the edges of tiles, token counts around a slab of 32 and a group's share of slabs.
+@pytest.mark.parametrize("out,n_in,T,split_k", [
+    (1, 3, 5, None), (63, 200, 40, None), (200, 63, 33, 2), (64, 65, 1, None), (65, 64, 31, None), (129, 127, 32, None),
+    (130, 131, 129, 3), (127, 1001, 257, None), (2051, 2053, 45, None), (2049, 2178, 161, 1), (2047, 2050, 1600, 1)])
+def test_bf16_rows_without_alignment(out, n_in, T, split_k):
+    case = WL.linear_case(np.random.default_rng(17 * out + n_in), "r", out, n_in, T, WL.BF16, 1e-3)
+    n = out * n_in
+    for begin, end in ({(0, n), (n // 3, n - n // 5)} if n < 1 << 20 else {(1, n - 1)}):
+        _full_check(case, begin, end, split_k=split_k if split_k and T >= 2 * split_k else None, warm=True, step=2)
+
+
 def test_bf16_strided_operands():
     """Row strides larger than the row length (views into wider buffers)."""
     rng = np.random.default_rng(79)
