@@ -1227,6 +1227,127 @@ __global__ __launch_bounds__(C::NT, 2) void wgrad_mfma_kernel(const MfmaArgs arg
 }
 
 // ---------------------------------------------------------------------------
+// scale-vector gradient: g[j] = sum_t dY[t, j] * X[t, j]
+// ---------------------------------------------------------------------------
+// A block is CB columns over all tokens.  The tokens are dealt to 128 groups, group g = tokens g, g + 128, ...;
+// a lane takes VE = 16 bytes / element size columns of a group, so that a wave's load is 1 KB of whole
+// pieces (with one 2-byte column per lane, as this kernel had it, the loads were 128 bytes and a compute
+// unit took in 3 bytes per clock).  The group sums meet in LDS, eight at a time and then the sixteen sums of
+// eight, in group order: the result depends neither on CB nor on the number of threads.
+// With NORM the operator normalises its input itself: X is the raw input and stats[2t],
+// stats[2t+1] are the token's mean (0 for RMSNorm) and reciprocal standard deviation.
+constexpr int kColsumGroups = 128;
+constexpr int kColsumCols = 64;                // columns of a block in the grouped call
+constexpr int kColsumUnroll = 4;               // tokens in flight per lane
+
+template <typename T> struct Piece;            // 16 bytes of consecutive elements at any element
+template <> struct Piece<float> {
+  static constexpr int N = 4;
+  f32x4_u v;
+  __device__ __forceinline__ void load(const float* p) { v = *(const f32x4_u*)p; }
+  __device__ __forceinline__ float at(int i) const { return v[i]; }
+};
+template <> struct Piece<unsigned short> {
+  static constexpr int N = 8;
+  typedef unsigned int raw_t __attribute__((ext_vector_type(4), aligned(2)));
+  u32x4_t v;
+  __device__ __forceinline__ void load(const unsigned short* p) { v = *(const raw_t*)p; }
+  __device__ __forceinline__ float at(int i) const {
+    return __uint_as_float(i & 1 ? v[i / 2] & 0xffff0000u : v[i / 2] << 16);
+  }
+};
+
+template <int CB> constexpr size_t colsum_lds_floats = (size_t)(kColsumGroups + 16) * CB;
+
+template <typename T, int MODE, int NORM, int NT, int CB>
+__device__ __forceinline__ void colsum_block(const WgradProblem& p, const Sinks& s, const float* stats, int64_t block,
+                                             float* red) {
+  constexpr int VE = Piece<T>::N, LPG = CB / VE, NG = NT / LPG, U = kColsumUnroll;
+  static_assert(CB % VE == 0 && kColsumGroups % NG == 0, "whole passes over the groups");
+  const T* const dY = (const T*)p.dY;
+  const T* const X = (const T*)p.X;
+  const int l = threadIdx.x % LPG;
+  const int64_t first = p.begin + block * CB + l * VE;        // the lane's columns, nominally
+  // a piece that would reach past the row is moved back; a vector shorter than a piece goes by elements
+  const bool pieces = p.in >= VE;
+  const int64_t col = pieces ? (first + VE <= p.in ? first : p.in - VE) : first;
+  for (int g = threadIdx.x / LPG; g < kColsumGroups; g += NG) {
+    float acc[VE];
+#pragma unroll
+    for (int e = 0; e < VE; ++e) acc[e] = 0.f;
+    if (first < p.end) {
+      auto add = [&](int64_t t, const Piece<T>& x, const Piece<T>& d) {
+        float mean = 0.f, rstd = 1.f;
+        if constexpr (NORM) { mean = stats[2 * t]; rstd = stats[2 * t + 1]; }
+#pragma unroll
+        for (int e = 0; e < VE; ++e) {
+          float v = x.at(e);
+          if constexpr (NORM) v = (v - mean) * rstd;
+          acc[e] = fmaf(d.at(e), v, acc[e]);
+        }
+      };
+      if (pieces) {
+        int64_t t = g;
+        for (; t + (U - 1) * kColsumGroups < p.T; t += U * kColsumGroups) {
+          Piece<T> x[U], d[U];
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            x[u].load(X + (t + u * kColsumGroups) * p.ldx + col);
+            d[u].load(dY + (t + u * kColsumGroups) * p.lddy + col);
+          }
+#pragma unroll
+          for (int u = 0; u < U; ++u) add(t + u * kColsumGroups, x[u], d[u]);
+        }
+        for (; t < p.T; t += kColsumGroups) {
+          Piece<T> x, d;
+          x.load(X + t * p.ldx + col);
+          d.load(dY + t * p.lddy + col);
+          add(t, x, d);
+        }
+      } else {
+        for (int64_t t = g; t < p.T; t += kColsumGroups)
+          for (int e = 0; e < VE; ++e) {
+            if (col + e >= p.in) break;
+            float v = load_as_f32<T>(X + t * p.ldx + col + e);
+            if constexpr (NORM) v = (v - stats[2 * t]) * stats[2 * t + 1];
+            acc[e] = fmaf(load_as_f32<T>(dY + t * p.lddy + col + e), v, acc[e]);
+          }
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < VE; ++e) red[g * CB + l * VE + e] = acc[e];
+  }
+  __syncthreads();
+  float* const red2 = red + kColsumGroups * CB;
+  for (int o = threadIdx.x; o < 16 * CB; o += NT) {
+    const int part = o / CB, c = o % CB;
+    float sum = red[part * 8 * CB + c];
+#pragma unroll
+    for (int k = 1; k < 8; ++k) sum += red[(part * 8 + k) * CB + c];
+    red2[o] = sum;
+  }
+  __syncthreads();
+  if (threadIdx.x < CB) {
+    const int lane = threadIdx.x / VE, e = threadIdx.x % VE;
+    const int64_t nominal = p.begin + block * CB + lane * VE, j = nominal + e;
+    if (j < p.end) {
+      // in a piece that was moved back, column j sits that much further on
+      const int64_t moved = pieces && nominal + VE > p.in ? nominal - (p.in - VE) : 0;
+      const int c = (int)(lane * VE + e + moved);
+      float sum = red2[c];
+      for (int k = 1; k < 16; ++k) sum += red2[k * CB + c];
+      emit<MODE>(s, p.end - p.begin, 0, j - p.begin, j, sum);
+    }
+  }
+}
+
+template <typename T, int MODE, int NORM, int NT, int CB>
+__global__ __launch_bounds__(NT) void colsum_kernel(const WgradProblem p, const Sinks s, const float* stats) {
+  __shared__ float red[colsum_lds_floats<CB>];
+  colsum_block<T, MODE, NORM, NT, CB>(p, s, stats, blockIdx.x, red);
+}
+
+// ---------------------------------------------------------------------------
 // one launch for all segments of a chunk (fused call only)
 // ---------------------------------------------------------------------------
 // The work items of up to kGroupMax segments are laid end to end: the tiles of each bf16 matrix
@@ -1242,36 +1363,6 @@ struct GroupParams {
 };
 static_assert(sizeof(GroupParams) <= 4096, "the table travels as a kernel argument");
 
-// 64 elements of a scale-vector segment: the arithmetic of colsum_kernel (16 token groups, each summed
-// in ascending token order, then added in group order), with the workgroup's waves taking the token
-// groups in turn.
-template <class C, int MODE>
-__device__ __forceinline__ void colsum_item(const MfmaParams& q, const int block, unsigned char* ldsb) {
-  constexpr int TG = 16;
-  float (*red)[64] = reinterpret_cast<float (*)[64]>(ldsb);
-  const WgradProblem& p = q.p;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t j = p.begin + (int64_t)block * 64 + lane;
-  const unsigned short* dY = (const unsigned short*)p.dY;
-  const unsigned short* X = (const unsigned short*)p.X;
-  for (int tg = wave; tg < TG; tg += C::NW) {
-    float acc = 0.f;
-    if (j < p.end)
-#pragma unroll 8
-      for (int64_t t = tg; t < p.T; t += TG) {
-        const float x = bf16_bits_to_f32(X[t * p.ldx + j]);
-        acc = fmaf(bf16_bits_to_f32(dY[t * p.lddy + j]), x, acc);
-      }
-    red[tg][lane] = acc;
-  }
-  __syncthreads();
-  if (wave == 0 && j < p.end) {
-    float sum = red[0][lane];
-    for (int g = 1; g < TG; ++g) sum += red[g][lane];
-    emit<MODE>(q.s, p.end - p.begin, 0, j - p.begin, j, sum);
-  }
-}
-
 template <class C>
 __global__ __launch_bounds__(C::NT, 2) void wgrad_group_kernel(const GroupParams gp) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char ldsb[];
@@ -1282,67 +1373,52 @@ __global__ __launch_bounds__(C::NT, 2) void wgrad_group_kernel(const GroupParams
   while (si + 1 < gp.n_segs && item >= gp.item_start[si + 1]) ++si;
   const MfmaParams& q = gp.seg[si];
   const int local = item - gp.item_start[si];
-  if (q.tiles_m == 0) colsum_item<C, EMIT_ADAMW>(q, local, ldsb);
+  if (q.tiles_m == 0)
+    colsum_block<unsigned short, EMIT_ADAMW, 0, C::NT, kColsumCols>(q.p, q.s, nullptr, local, reinterpret_cast<float*>(ldsb));
   else if constexpr (C::MI == 16) mfma_tile16<C, EMIT_ADAMW>(q, local, ldsb);
   else mfma_tile<C, EMIT_ADAMW>(q, local, ldsb);
 }
 
-// ---------------------------------------------------------------------------
-// scale-vector gradient: g[j] = sum_t dY[t, j] * X[t, j]
-// ---------------------------------------------------------------------------
-// With NORM the operator normalises its input itself: X is the raw input and stats[2t],
-// stats[2t+1] are the token's mean (0 for RMSNorm) and reciprocal standard deviation.
-template <typename T, int MODE, int NORM>
-__global__ __launch_bounds__(1024) void colsum_kernel(const WgradProblem p, const Sinks s, const float* stats) {
-  constexpr int TG = 16;
-  __shared__ float red[TG][64];
-  const int lane = threadIdx.x & 63, tg = threadIdx.x >> 6;
-  const int64_t j = p.begin + (int64_t)blockIdx.x * 64 + lane;
-  const T* dY = (const T*)p.dY;
-  const T* X = (const T*)p.X;
-  float acc = 0.f;
-  if (j < p.end)
-#pragma unroll 8                                   // eight tokens' loads in flight; the sum keeps its order
-    for (int64_t t = tg; t < p.T; t += TG) {
-      float x = load_as_f32<T>(X + t * p.ldx + j);
-      if constexpr (NORM) x = (x - stats[2 * t]) * stats[2 * t + 1];
-      acc = fmaf(load_as_f32<T>(dY + t * p.lddy + j), x, acc);
-    }
-  red[tg][lane] = acc;
-  __syncthreads();
-  if (tg == 0 && j < p.end) {
-    float sum = red[0][lane];
-    for (int g = 1; g < TG; ++g) sum += red[g][lane];
-    emit<MODE>(s, p.end - p.begin, 0, j - p.begin, j, sum);
-  }
-}
-
 // Per-token statistics of RMSNorm (SUB = 0) or LayerNorm (SUB = 1): one wave per token, two
-// passes over the row (mean first, then the centred sum of squares), fp32.
+// passes over the row (mean first, then the centred sum of squares), fp32, 16 bytes per lane.
 template <typename T, int SUB>
 __global__ __launch_bounds__(256) void norm_stats_kernel(const T* X, int64_t ldx, int64_t n, int64_t tokens,
                                                          float eps, float* stats) {
+  constexpr int VE = Piece<T>::N, U = 4;
   const int lane = threadIdx.x & 63;
   const int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (t >= tokens) return;
   const T* row = X + t * ldx;
-  auto wave_sum = [](float v) {
+  auto row_sum = [&](auto term) {                             // sum of term(x) over the row
+    float s[2] = {0.f, 0.f};
+    int64_t j = lane * VE;
+    for (; j + (U - 1) * 64 * VE + VE <= n; j += U * 64 * VE) {
+      Piece<T> x[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) x[u].load(row + j + u * 64 * VE);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int e = 0; e < VE; ++e) s[e & 1] = term(x[u].at(e), s[e & 1]);
+    }
+    for (; j + VE <= n; j += 64 * VE) {
+      Piece<T> x;
+      x.load(row + j);
+#pragma unroll
+      for (int e = 0; e < VE; ++e) s[e & 1] = term(x.at(e), s[e & 1]);
+    }
+    for (; j < n; ++j) {                                      // the one lane whose piece the row's end cuts
+      s[0] = term(load_as_f32<T>(row + j), s[0]);
+      if ((j + 1) % VE == 0) break;
+    }
+    float v = s[0] + s[1];
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
     return v;
   };
   float mean = 0.f;
-  if constexpr (SUB) {
-    float s1 = 0.f;
-    for (int64_t j = lane; j < n; j += 64) s1 += load_as_f32<T>(row + j);
-    mean = wave_sum(s1) / (float)n;
-  }
-  float s2 = 0.f;
-  for (int64_t j = lane; j < n; j += 64) {
-    const float d = load_as_f32<T>(row + j) - mean;
-    s2 = fmaf(d, d, s2);
-  }
-  const float var = wave_sum(s2) / (float)n;
+  if constexpr (SUB) mean = row_sum([](float x, float s) { return s + x; }) / (float)n;
+  const float var = row_sum([&](float x, float s) { return fmaf(x - mean, x - mean, s); }) / (float)n;
   if (lane == 0) {
     stats[2 * t] = mean;
     stats[2 * t + 1] = 1.0f / sqrtf(var + eps);
@@ -1840,29 +1916,32 @@ int launch_wgrad_simt(const WgradProblem& p, int dtype, int mode, const Sinks& s
   return dtype == 0 ? launch_wgrad_f32(p, mode, s, stream) : launch_wgrad_ragged(p, mode, s, stream);
 }
 
+// A block is one 128-byte line of every token: with half a line the two blocks of a line each fetch all of it
+// (bf16, 4096 x 4096: 25 against 18 us), with two lines an fp32 vector fills too few compute units (49 against 35 us).
 template <typename T, int NORM>
-static int launch_colsum_t(const WgradProblem& p, int grid, int mode, const Sinks& s, const float* stats,
-                           hipStream_t st) {
+static int launch_colsum_t(const WgradProblem& p, int mode, const Sinks& s, const float* stats, hipStream_t st) {
+  constexpr int CB = 128 / sizeof(T), NT = 1024;
+  const int64_t blocks = ceil_div(p.end - p.begin, CB);
+  if (blocks > 0x7fffffff) return (int)hipErrorInvalidValue;
+  const dim3 grid((unsigned)blocks), threads(NT);
   switch (mode) {
-    case EMIT_STORE: hipLaunchKernelGGL((colsum_kernel<T, EMIT_STORE, NORM>), dim3(grid), dim3(1024), 0, st, p, s, stats); break;
-    case EMIT_ACCUM: hipLaunchKernelGGL((colsum_kernel<T, EMIT_ACCUM, NORM>), dim3(grid), dim3(1024), 0, st, p, s, stats); break;
-    default: hipLaunchKernelGGL((colsum_kernel<T, EMIT_ADAMW, NORM>), dim3(grid), dim3(1024), 0, st, p, s, stats); break;
+    case EMIT_STORE: hipLaunchKernelGGL((colsum_kernel<T, EMIT_STORE, NORM, NT, CB>), grid, threads, 0, st, p, s, stats); break;
+    case EMIT_ACCUM: hipLaunchKernelGGL((colsum_kernel<T, EMIT_ACCUM, NORM, NT, CB>), grid, threads, 0, st, p, s, stats); break;
+    default: hipLaunchKernelGGL((colsum_kernel<T, EMIT_ADAMW, NORM, NT, CB>), grid, threads, 0, st, p, s, stats); break;
   }
   return (int)hipGetLastError();
 }
 
 int launch_colsum(const WgradProblem& p, int dtype, int mode, const Sinks& s, void* stream) {
-  const int64_t grid = ceil_div(p.end - p.begin, 64);
-  if (grid > 0x7fffffff) return (int)hipErrorInvalidValue;
   hipStream_t st = (hipStream_t)stream;
-  return dtype == 0 ? launch_colsum_t<float, 0>(p, (int)grid, mode, s, nullptr, st)
-                    : launch_colsum_t<unsigned short, 0>(p, (int)grid, mode, s, nullptr, st);
+  return dtype == 0 ? launch_colsum_t<float, 0>(p, mode, s, nullptr, st)
+                    : launch_colsum_t<unsigned short, 0>(p, mode, s, nullptr, st);
 }
 
 int launch_norm_wgrad(const WgradProblem& p, int dtype, bool subtract_mean, float eps, float* stats, int mode,
                       const Sinks& s, void* stream) {
-  const int64_t grid = ceil_div(p.end - p.begin, 64), sgrid = ceil_div(p.T, 4);
-  if (grid > 0x7fffffff || sgrid > 0x7fffffff) return (int)hipErrorInvalidValue;
+  const int64_t sgrid = ceil_div(p.T, 4);
+  if (sgrid > 0x7fffffff) return (int)hipErrorInvalidValue;
   hipStream_t st = (hipStream_t)stream;
   if (dtype == 0) {
     if (subtract_mean) hipLaunchKernelGGL((norm_stats_kernel<float, 1>), dim3((int)sgrid), dim3(256), 0, st, (const float*)p.X, p.ldx, p.in, p.T, eps, stats);
@@ -1873,8 +1952,8 @@ int launch_norm_wgrad(const WgradProblem& p, int dtype, bool subtract_mean, floa
   }
   const int err = (int)hipGetLastError();
   if (err != 0) return err;
-  return dtype == 0 ? launch_colsum_t<float, 1>(p, (int)grid, mode, s, stats, st)
-                    : launch_colsum_t<unsigned short, 1>(p, (int)grid, mode, s, stats, st);
+  return dtype == 0 ? launch_colsum_t<float, 1>(p, mode, s, stats, st)
+                    : launch_colsum_t<unsigned short, 1>(p, mode, s, stats, st);
 }
 
 template <typename T>

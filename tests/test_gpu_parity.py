@@ -472,6 +472,19 @@ def test_self_normalising_scale_vectors(kind):
     _full_check(wide, 0, 4096)
 
 
+# Lanes take 16-byte pieces of a scale vector (8 bf16 or 4 fp32 columns): vectors shorter than a piece, with a
+# cut last piece, ranges that start inside one; token counts around the 128 groups and the four tokens in flight.
+@pytest.mark.parametrize("n,T", [(1, 1), (3, 130), (7, 127), (9, 128), (63, 129), (65, 511), (130, 513), (1029, 640)])
+@pytest.mark.parametrize("kind", [WL.VECTOR, WL.RMSNORM, WL.LAYERNORM])
+def test_scale_vector_pieces_and_token_groups(n, T, kind):
+    for dtype in (WL.BF16, WL.F32):
+        rng = np.random.default_rng(1000 * n + T)
+        case = WL.vector_case(rng, "v", n, T, dtype, 1e-3) if kind == WL.VECTOR else \
+            WL.norm_case(rng, "n", n, T, dtype, 1e-3, kind)
+        for begin, end in {(0, n), (n // 3, n - n // 5), (n - 1, n)}:
+            _full_check(case, begin, end, warm=True, step=2)
+
+
 def test_warm_state_second_step():
     _full_check(_small_bf16(seed=81), 264 * 2 + 33, 264 * 519 + 1, warm=True, step=2)
 
