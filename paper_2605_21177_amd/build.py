@@ -20,7 +20,7 @@ OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libchunkft.so")
 LIB_TIMELINE = os.path.join(PKG, "libchunkft_timeline.so")   # diagnostic twin: workgroups note their phase times
 
-SOURCES = ["kernels.hip", "wgrad_f32.hip", "wgrad_ragged.hip", "static_ws.hip", "calib.hip", "api.cpp", "shape.cpp", "plan.cpp", "mover.cpp"]
+SOURCES = ["kernels.hip", "wgrad_f32.hip", "wgrad_ragged.hip", "wgrad_small.hip", "static_ws.hip", "calib.hip", "api.cpp", "shape.cpp", "plan.cpp", "mover.cpp"]
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

@@ -30,6 +30,16 @@ __device__ __forceinline__ void static_for(F&& f) {
   }
 }
 
+// LDS transpose read issued as opaque assembly: the compiler must not know that
+// it reads LDS, or it would wait for every outstanding global->LDS load before
+// it.  The counterpart is that waiting for its result is also done by hand,
+// and that no branch may lie between a read and its wait.
+template <int OFF>
+__device__ __forceinline__ bf16x4 lds_tr_read(unsigned addr) {
+  bf16x4 r;
+  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(r) : "v"(addr), "n"(OFF) : "memory");
+  return r;
+}
 // s_waitcnt vmcnt(N) alone (gfx9 encoding: vmcnt in bits 3:0 and 15:14, others "no wait")
 template <int N> __device__ __forceinline__ void wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt((N & 0xF) | (7 << 4) | (0xF << 8) | ((N >> 4) << 14));

@@ -38,8 +38,6 @@ struct Sinks {
   AdamWConsts c;
 };
 
-constexpr int kMaxEdgeRows = 9;
-
 struct WgradProblem {
   const void* X;
   const void* dY;
@@ -64,7 +62,8 @@ struct RowSplit {
 };
 RowSplit split_rows(const WgradProblem& p);               // needs p.begin, p.end, p.in only
 bool plain_takes_large_tile(int64_t large_tiles, int64_t slab_tokens, int compute_units);   // tile of the plain gradient
-bool edge_rows_folded(const RowSplit& rs);                // the MFMA kernel carries the edge rows itself
+bool edge_rows_folded(const RowSplit& rs);                // the large-tile kernel carries the edge rows itself
+bool takes_small_tiles(int64_t in, int64_t T, int64_t begin, int64_t end, int compute_units);   // 64 x 64 tiles
 
 // Tile of the plain MFMA gradient and of the FMA kernel: what the token split is chosen from.
 constexpr int64_t kMainTileM = 256, kMainTileN = 256, kMainTileK = 32;
@@ -100,6 +99,8 @@ int launch_fused_group(const GroupSegment* segs, int n, bool large_tile, void* s
 int launch_wgrad_bf16_mfma(const WgradProblem& p, int mode, const Sinks& s, void* stream);
 // Matrices without 16-byte bf16 rows: fp32 ones go to launch_wgrad_f32, bf16 ones to launch_wgrad_ragged.
 int launch_wgrad_simt(const WgradProblem& p, int dtype, int mode, const Sinks& s, void* stream);
+// A bf16 matrix in 64 x 64 tiles.
+int launch_wgrad_small(const WgradProblem& p, int mode, const Sinks& s, void* stream);
 int launch_wgrad_f32(const WgradProblem& p, int mode, const Sinks& s, void* stream);
 int launch_wgrad_ragged(const WgradProblem& p, int mode, const Sinks& s, void* stream);
 int launch_colsum(const WgradProblem& p, int dtype, int mode, const Sinks& s, void* stream);

@@ -4,14 +4,13 @@
 //                       token slabs, LDS transpose reads, 32x32x16 bf16 MFMA, fp32
 //                       accumulators; epilogue stores g, a slab partial, or applies
 //                       AdamW straight from the accumulators.
-//   wgrad_edge_kernel   the up-to-9 partial / unaligned rows of a chunk that has too few
-//                       rows for the MFMA kernel to carry them (plain FMA).
 //   colsum_kernel       1-D scale-vector gradient sum_t dY[t,j] * X[t,j], X normalised by the
 //                       caller or here (norm_stats_kernel: per-token mean and 1/std).
 //   embed_wgrad_kernel  embedding table gradient: per table row the sum of the dY rows of
 //                       the tokens that name it, in token order.
 //   elementwise_kernel  AdamW over a chunk and/or the fixed-order sum of slab partials.
-// fp32 layers are in wgrad_f32.hip, bf16 layers without 16-byte rows in wgrad_ragged.hip.
+// fp32 layers are in wgrad_f32.hip, bf16 layers without 16-byte rows in wgrad_ragged.hip, chunks of few tiles in
+// wgrad_small.hip.
 //
 // The operations are those of the paper's Section 3.1 (gradient of the active
 // slices only, through the chunk-aware operators of Algorithm 1 line 8) and
@@ -36,10 +35,9 @@ namespace chunkft {
 //   body rows [rb0, rb1): complete rows, rb0 a multiple of 8 (16-byte dY loads),
 //   computed by the MFMA kernel with no range mask beyond the row bound;
 //   edge rows: the partial first row, the up-to-7 complete rows before rb0, and
-//   the partial last row -- at most kMaxEdgeRows of them.  The workgroups of the
+//   the partial last row -- at most 9 of them.  The workgroups of the
 //   first tile row, which stream every X column tile anyway, carry them as one
-//   extra 32-row MFMA block; only when the body has at most 128 rows (a chunk of a
-//   few rows) does the small FMA edge kernel compute them.
+//   extra 32-row MFMA block.  (A chunk whose body has at most 128 rows does not come here.)
 // Diagnostic build only (-DCHUNKFT_TIMELINE, a library of its own: libchunkft_timeline.so): every
 // workgroup of the MFMA kernel notes when it starts, when the first fragments of its tile are in
 // registers, when its loop ends and when its epilogue ends (the 100 MHz constant counter), and where
@@ -68,19 +66,12 @@ struct MfmaParams {
   int32_t n_tile_items;        // tiles_m * tiles_n * S
   int32_t group_m;
   int32_t stagger;             // start delay of every second resident workgroup, in units of 8128 cycles
-  int64_t lead_base;           // edge rows folded into the first tile row (-1: none), as in EdgeParams
+  int64_t lead_base;           // edge rows folded into the first tile row (the 8-row group before rb0; -1: none)
   int64_t trail_row;
   Sinks s;
 #ifdef CHUNKFT_TIMELINE
   unsigned long long* timeline;
 #endif
-};
-
-struct EdgeParams {
-  WgradProblem p;
-  int64_t lead_base;   // first row of the 8-row group that holds the leading edge rows, or -1
-  int64_t trail_row;   // the partial last row, or -1
-  Sinks s;
 };
 
 // Tile configuration of the MFMA kernel: a (128 WM) x 256 output tile per workgroup
@@ -117,121 +108,6 @@ struct RingCfg {
                 "the main loops are written out for this shape");
 };
 
-// Edge rows of a chunk whose body is too short to carry them in the MFMA kernel: the leading ones all
-// lie in one 8-aligned group of rows (one 16-byte piece of dY per token), the trailing one is a single
-// row.  A block is 32 columns over all tokens, done by 512 (token group, 8-column group) pairs -- 8
-// "virtual waves" of 64 lanes, lane l = 8-column group l % 4 of token group 16 vw + l / 4, tokens
-// t = token group (mod 128) in ascending order: per token one 16-byte piece of X, one of dY and the
-// trailing row's value feed 72 FMAs (with one column and 2-byte loads per lane the kernel was bound by
-// its load instructions: 300 us at 4096 tokens, eight times what it takes now).  The 16 token groups
-// of a virtual wave are added by a butterfly over the lanes, the 8 virtual waves meet in LDS and are
-// added in order.  A workgroup of NT threads takes the virtual waves NT / 64 at a time; the sums do not
-// depend on NT.
-constexpr int kEdgeCols = 32;
-constexpr int kEdgeVW = 8;                        // virtual waves per block
-constexpr int kEdgeTG = 16 * kEdgeVW;             // token groups
-constexpr int kEdgeThreads = 64 * kEdgeVW;
-constexpr int kEdgeUnroll = 4;
-
-template <int NT, int MODE>
-__device__ __forceinline__ void edge_rows_block(const WgradProblem& p, const Sinks& s, const int64_t lead_base,
-                                                const int64_t trail_row, const int64_t block,
-                                                float (*red)[kMaxEdgeRows][kEdgeCols]) {
-  static_assert(NT % 64 == 0 && kEdgeThreads % NT == 0, "whole virtual waves per pass");
-  const unsigned short* X = (const unsigned short*)p.X;
-  const unsigned short* dY = (const unsigned short*)p.dY;
-  const bool has_lead = lead_base >= 0, has_trail = trail_row >= 0;
-  const int lane = threadIdx.x & 63;
-  const int cg = lane & 3, tgl = lane >> 2;
-  const int64_t col8 = block * kEdgeCols + cg * 8;               // in % 8 == 0: a group of 8 columns is whole or absent
-  const bool col_ok = col8 < p.in;
-  for (int vw = threadIdx.x >> 6; vw < kEdgeVW; vw += NT / 64) {
-    float acc[kMaxEdgeRows][8];
-#pragma unroll
-    for (int e = 0; e < kMaxEdgeRows; ++e)
-#pragma unroll
-      for (int c = 0; c < 8; ++c) acc[e][c] = 0.f;
-    for (int64_t t0 = vw * 16 + tgl; t0 < p.T; t0 += (int64_t)kEdgeTG * kEdgeUnroll) {
-      uint4 xs[kEdgeUnroll], ld[kEdgeUnroll];
-      unsigned short tr[kEdgeUnroll];
-#pragma unroll
-      for (int u = 0; u < kEdgeUnroll; ++u) {
-        const int64_t t = t0 + (int64_t)u * kEdgeTG;
-        const bool ok = t < p.T && col_ok;
-        xs[u] = ok ? *(const uint4*)(X + t * p.ldx + col8) : make_uint4(0, 0, 0, 0);
-        ld[u] = (ok && has_lead) ? *(const uint4*)(dY + t * p.lddy + lead_base) : make_uint4(0, 0, 0, 0);
-        tr[u] = (ok && has_trail) ? dY[t * p.lddy + trail_row] : (unsigned short)0;
-      }
-#pragma unroll
-      for (int u = 0; u < kEdgeUnroll; ++u) {
-        const unsigned int xw[4] = {xs[u].x, xs[u].y, xs[u].z, xs[u].w};
-        const unsigned int dw[4] = {ld[u].x, ld[u].y, ld[u].z, ld[u].w};
-        float x[8], d[kMaxEdgeRows];
-#pragma unroll
-        for (int h = 0; h < 4; ++h) {
-          x[2 * h] = __uint_as_float(xw[h] << 16);
-          x[2 * h + 1] = __uint_as_float(xw[h] & 0xffff0000u);
-          d[2 * h] = __uint_as_float(dw[h] << 16);
-          d[2 * h + 1] = __uint_as_float(dw[h] & 0xffff0000u);
-        }
-        d[8] = bf16_bits_to_f32(tr[u]);
-#pragma unroll
-        for (int e = 0; e < kMaxEdgeRows; ++e)
-#pragma unroll
-          for (int c = 0; c < 8; ++c) acc[e][c] = fmaf(d[e], x[c], acc[e][c]);
-      }
-    }
-    // the 16 token groups of this virtual wave: lanes that differ in bits 2-5
-#pragma unroll
-    for (int e = 0; e < kMaxEdgeRows; ++e)
-#pragma unroll
-      for (int c = 0; c < 8; ++c) {
-        float v = acc[e][c];
-        v += __shfl_xor(v, 4);
-        v += __shfl_xor(v, 8);
-        v += __shfl_xor(v, 16);
-        v += __shfl_xor(v, 32);
-        if (tgl == 0) red[vw][e][cg * 8 + c] = v;
-      }
-  }
-  __syncthreads();
-  for (int o = threadIdx.x; o < kMaxEdgeRows * kEdgeCols; o += NT) {
-    const int e = o / kEdgeCols, c = o & (kEdgeCols - 1);
-    const int64_t col = block * kEdgeCols + c;
-    const int64_t row = e < 8 ? (has_lead ? lead_base + e : -1) : trail_row;   // -1: nothing to emit
-    const int64_t flat = row * p.in + col;
-    if (col < p.in && row >= 0 && flat >= p.begin && flat < p.end) {
-      float sum = red[0][e][c];
-      for (int g = 1; g < kEdgeVW; ++g) sum += red[g][e][c];
-      const int64_t E = p.end - p.begin, i = flat - p.begin;
-      if constexpr (MODE == EMIT_PARTIAL) {
-        // the edge rows take all tokens at once: slab 0 carries the sum, the rest zero
-        s.ws[i] = sum;
-        for (int32_t sl = 1; sl < p.S; ++sl) s.ws[(int64_t)sl * s.ws_pitch + i] = 0.f;
-      } else {
-        emit<MODE>(s, E, 0, i, flat, sum);
-      }
-    }
-  }
-}
-
-template <int MODE>
-__global__ __launch_bounds__(kEdgeThreads) void wgrad_edge_kernel(const EdgeParams q) {
-  __shared__ float red[kEdgeVW][kMaxEdgeRows][kEdgeCols];
-  edge_rows_block<kEdgeThreads, MODE>(q.p, q.s, q.lead_base, q.trail_row, blockIdx.x, red);
-}
-
-
-// LDS transpose read issued as opaque assembly: the compiler must not know that
-// it reads LDS, or it would wait for every outstanding global->LDS load before
-// it.  The counterpart is that waiting for its result is also done by hand
-// (WAIT_HALVES below).
-template <int OFF>
-__device__ __forceinline__ bf16x4 lds_tr_read(unsigned addr) {
-  bf16x4 r;
-  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(r) : "v"(addr), "n"(OFF) : "memory");
-  return r;
-}
 #define WAIT_HALVES(h)                                                                                   \
   asm volatile("s_waitcnt lgkmcnt(0)"                                                                    \
                : "+v"(h[0]), "+v"(h[1]), "+v"(h[2]), "+v"(h[3]), "+v"(h[4]), "+v"(h[5]), "+v"(h[6]),     \
@@ -1815,30 +1691,9 @@ bool fill_mfma_params(const WgradProblem& p, int mode, const Sinks& s, const Row
   return true;
 }
 
-int launch_edge_rows(const WgradProblem& p, int mode, const Sinks& s, const RowSplit& rs, hipStream_t st) {
-  EdgeParams e{};
-  e.p = p;
-  e.s = s;
-  e.lead_base = rs.lead_base;
-  e.trail_row = rs.trail_row;
-  const dim3 grid((unsigned)ceil_div(p.in, kEdgeCols)), block(kEdgeThreads);
-  switch (mode) {
-    case EMIT_STORE: hipLaunchKernelGGL((wgrad_edge_kernel<EMIT_STORE>), grid, block, 0, st, e); break;
-    case EMIT_ACCUM: hipLaunchKernelGGL((wgrad_edge_kernel<EMIT_ACCUM>), grid, block, 0, st, e); break;
-    case EMIT_PARTIAL: hipLaunchKernelGGL((wgrad_edge_kernel<EMIT_PARTIAL>), grid, block, 0, st, e); break;
-    default: hipLaunchKernelGGL((wgrad_edge_kernel<EMIT_ADAMW>), grid, block, 0, st, e); break;
-  }
-  return (int)hipGetLastError();
-}
-
 template <class C>
 int launch_mfma_cfg(const WgradProblem& p, int mode, const Sinks& s, hipStream_t st) {
   const RowSplit rs = split_rows(p);
-  if (!edge_rows_folded(rs) && (rs.lead_base >= 0 || rs.trail_row >= 0)) {
-    const int err = launch_edge_rows(p, mode, s, rs, st);
-    if (err != 0) return err;
-  }
-  if (rs.rb1 <= rs.rb0) return 0;
   MfmaParams q;
   if (!fill_mfma_params<C>(p, mode, s, rs, q)) return (int)hipErrorInvalidValue;   // work items are counted in 32 bits
   const int grid = (q.n_tile_items + 7) / 8 * 8;
@@ -1851,6 +1706,7 @@ int launch_mfma_cfg(const WgradProblem& p, int mode, const Sinks& s, hipStream_t
 }
 
 int launch_wgrad_bf16_mfma(const WgradProblem& p, int mode, const Sinks& s, void* stream) {
+  if (takes_small_tiles(p.in, p.T, p.begin, p.end, device_compute_units())) return launch_wgrad_small(p, mode, s, stream);
   // The plain gradient (short epilogue) is a little faster on the large tile; the fused call,
   // whose epilogue moves 26 bytes per element, gains from two workgroups per compute unit.
   if (mode == EMIT_ADAMW) {

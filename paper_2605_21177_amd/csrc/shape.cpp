@@ -36,10 +36,38 @@ RowSplit split_rows(const WgradProblem& p) {
   return rs;
 }
 
-// The edge rows ride in the MFMA kernel if it has the tile rows that carry them (more than 128 body
-// rows = two tile rows of the small tile; the same rule for both tile sizes, so that every call sums
-// every element in the same order).
+// The edge rows ride in the large-tile kernel if it has the tile rows that carry them (more than 128 body
+// rows = two tile rows of the 128 x 256 tile); a chunk with a shorter body goes to the small tiles, which
+// have no edge rows.
 bool edge_rows_folded(const RowSplit& rs) { return rs.rb1 - rs.rb0 > 128; }
+
+namespace {
+// 64 x 64 tiles over the rows of [begin, end), the first one rounded down to a multiple of 8
+int64_t small_tiles(int64_t in, int64_t begin, int64_t end) {
+  const int64_t rows = (end - 1) / in - begin / in / 8 * 8 + 1;
+  return ceil_div(rows, 64) * ceil_div(in, 64);
+}
+}  // namespace
+
+// Which chunks go to the 64 x 64 tiles.  A 256 x 256 or 128 x 256 tile per compute unit needs millions of
+// elements; below that most of the device has no work (1 Mi elements of 1024 x 1024 at 256 tokens are 32
+// tiles: the fused call needed 30 us, 9 us of it latency in small tiles).  Small tiles read their operands
+// 1.5 - 4 times as often and a compute unit takes in 27 bytes per clock, so they lose where the token loop
+// decides.  Gradient / fused call in us, small tiles against the better of the large ones:
+//   1024 tokens: 0.5 Mi elements 9.9 / 12.2 against 18.8 / 19.6, 2 Mi 15 / 23 - 21 / 42, 4 Mi 20 / 37 - 20 / 43, 8 Mi
+//   (2112 tiles) 35 / 63 - 25 / 62;   2048 tokens: 2 Mi (528 tiles) 24 / 33 - 29 / 40, 4 Mi 32 / 46 - 29 / 52;
+//   4096 tokens: 1 Mi (272 tiles) 28 / 33 - 30 / 35, 2 Mi 41 / 49 - 37 / 48;   8192 tokens: 0.5 Mi (144 tiles) 28 / 31 -
+//   31 / 33, 1 Mi 43 / 48 - 37 / 43;   256 tokens: 4 Mi 11 / 26 - 14 / 38, 8 Mi 16 / 49 - 15 / 51.
+bool takes_small_tiles(int64_t in, int64_t T, int64_t begin, int64_t end, int compute_units) {
+  const int64_t cus = compute_units > 0 ? compute_units : kDefaultComputeUnits;
+  WgradProblem p{};
+  p.begin = begin;
+  p.end = end;
+  p.in = in;
+  if (!edge_rows_folded(split_rows(p))) return true;
+  const int64_t tiles = small_tiles(in, begin, end);
+  return tiles <= cus * 43 / 10 && tiles * T <= cus * 6600;
+}
 
 bool group_takes_segment(const WgradProblem& p, bool vector) {
   if (vector) return true;
@@ -101,6 +129,25 @@ Split pick_split(int32_t kind, int32_t dtype, int64_t out, int64_t in, int64_t T
   const int64_t bm = mfma ? kMainTileM : kSimtTileM, bn = mfma ? kMainTileN : kSimtTileN;
   const int64_t bk = mfma ? kMainTileK : kSimtTileK;
   int64_t S = forced;
+  if (S <= 0 && mfma && takes_small_tiles(in, T, begin, end, compute_units)) {
+    // Small tiles: a workgroup needs about 0.2 us per 32 tokens while no more than 1.6 of them share a
+    // compute unit, in proportion longer beyond; a split costs 4 us for the reduction's launch and 8
+    // bytes per element and slab at 5 TB/s.  The cheapest S up to 8 with at least 512 tokens per slab is within
+    // 15 % of the best of 1 - 32 slabs in 30 measured cases (16 - 576 tiles, 1024 - 8192 tokens), e.g. 80 tiles,
+    // 4096 tokens: 16 us with 5 or 6 slabs against 27 with one; 272 tiles, 2048 tokens: 19 with one, 21 with two.
+    const double tiles = (double)small_tiles(in, begin, end), elems = (double)(end - begin);
+    const double room = 1.6 * (compute_units > 0 ? compute_units : kDefaultComputeUnits);
+    double best = 0.0;
+    for (int64_t k = 1; k <= 8 && (k == 1 || T / k >= 512); ++k) {
+      const double crowd = tiles * (double)k / room;
+      const double cost = 0.2 * (double)T / 32.0 / (double)k * (crowd > 1.0 ? crowd : 1.0) +
+                          (k > 1 ? 4.0 + (double)k * elems * 8.0 / 5e6 : 0.0);
+      if (k == 1 || cost < best) {
+        best = cost;
+        S = k;
+      }
+    }
+  }
   if (S <= 0) {
     int64_t rows = (end - 1) / in - begin / in + 1;
     if (mfma) {                                       // the MFMA kernel tiles the body rows only

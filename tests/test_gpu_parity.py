@@ -284,6 +284,19 @@ def test_bf16_random_shapes_and_ranges():
                     step=1 + case_no % 3)
 
 
+# Chunks of few tiles go to 64 x 64 tiles with a ring of four 32-token slabs: tensors smaller than a tile, a row
+# group or a column group more or less than one, ranges inside one row, token counts below, at and above a slab and the
+# ring, forced slabs and the ones the library picks (T = 2048 and 4160: several).
+@pytest.mark.parametrize("out,n_in,T,split_k", [
+    (8, 8, 1, None), (64, 64, 32, None), (72, 56, 31, None), (56, 72, 33, 2), (136, 264, 127, None), (128, 128, 129, 3),
+    (1000, 72, 160, None), (200, 4104, 97, None), (264, 520, 2048, None), (64, 192, 4160, None), (1032, 1040, 65, None)])
+def test_bf16_small_tiles(out, n_in, T, split_k):
+    case = WL.linear_case(np.random.default_rng(13 * out + n_in), "s", out, n_in, T, WL.BF16, 1e-3)
+    n = out * n_in
+    for begin, end in {(0, n), (n // 3, n - n // 5), (n // 2, n // 2 + 1)} if n < 1 << 20 else {(1, n - 1)}:
+        _full_check(case, begin, end, split_k=split_k if split_k and T >= 2 * split_k else None, warm=True, step=2)
+
+
 def test_bf16_unaligned_shape_takes_fma_path():
     rng = np.random.default_rng(78)
     case = WL.linear_case(rng, "odd", 137, 100, 53, WL.BF16, 1e-3)   # in, out not multiples of 8
