@@ -80,8 +80,8 @@ class _ChunkLinear(torch.autograd.Function):
         dx = dy.matmul(W) if ctx.needs_input_grad[0] else None
         if seg is not None and seg.end > seg.begin:
             out, n_in = W.shape
-            x2 = x.reshape(-1, n_in)
-            dy2 = dy.reshape(-1, out)
+            x2 = x if x.dim() == 2 else x.reshape(-1, n_in)
+            dy2 = dy if dy.dim() == 2 else dy.reshape(-1, out)
             if x2.stride(1) != 1:
                 x2 = x2.contiguous()
             if dy2.stride(1) != 1:
@@ -109,6 +109,8 @@ def chunk_linear(x: torch.Tensor, W: torch.Tensor, seg: Optional[ChunkSegment]) 
         raise ValueError("W must not require grad: the dense weight gradient is never formed")
     if not W.is_contiguous():
         raise ValueError("W must be contiguous (the chunk is a range of its flattened elements)")
+    if x.requires_grad:
+        return _ChunkLinear.apply(x, W, None, seg)
     global _anchor
     if _anchor is None or _anchor.device != x.device:
         # makes autograd run backward also for a first layer whose input needs no gradient

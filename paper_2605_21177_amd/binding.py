@@ -251,34 +251,47 @@ def chunkft_plan_stats(chunks: Sequence[Tuple[int, int, int, int]], resident_byt
 
 
 # ---------------------------------------------------------- device calls
+_torch = None         # torch, imported by the first device call (the planner works without it)
+
+
+def _torch_module():
+    global _torch
+    if _torch is None:
+        import torch
+        _torch = torch
+    return _torch
+
+
 def _torch_dtype_code(t) -> int:
-    import torch
-    if t.dtype == torch.float32:
-        return F32
-    if t.dtype == torch.bfloat16:
+    torch = _torch or _torch_module()
+    d = t.dtype
+    if d is torch.bfloat16:
         return BF16
-    raise TypeError(f"unsupported tensor dtype {t.dtype}")
+    if d is torch.float32:
+        return F32
+    raise TypeError(f"unsupported tensor dtype {d}")
 
 
 def make_layer(kind: int, X, dY, out: int, n_in: int, split_k: int = 0, norm_eps: float = 0.0) -> Layer:
     """Describe a backward step from two row-major device tensors: X [T, in] and dY
     (for EMBEDDING X is the 1-D int64 tensor of token ids)."""
-    if dY.dim() != 2 or dY.stride(1) != 1:
+    dy_strides = dY.stride()
+    if len(dy_strides) != 2 or dy_strides[1] != 1:
         raise ValueError("dY must be 2-D with unit inner stride")
     if not (X.is_cuda and dY.is_cuda):
         raise ValueError("X and dY must live on the GPU")
     d = _torch_dtype_code(dY)
+    x_strides, tokens = X.stride(), X.shape[0]
     if kind == EMBEDDING:
-        import torch
-        if X.dim() != 1 or X.dtype != torch.int64 or X.stride(0) != 1 or X.shape[0] != dY.shape[0]:
+        if len(x_strides) != 1 or X.dtype is not _torch.int64 or x_strides[0] != 1 or tokens != dY.shape[0]:
             raise ValueError("token ids must be a contiguous 1-D int64 tensor with one id per row of dY")
-        return Layer(kind, d, out, n_in, X.shape[0], X.data_ptr(), 1, dY.data_ptr(), dY.stride(0), split_k, 0, 0.0)
-    if X.dim() != 2 or X.stride(1) != 1:
+        return Layer(kind, d, out, n_in, tokens, X.data_ptr(), 1, dY.data_ptr(), dy_strides[0], split_k, 0, 0.0)
+    if len(x_strides) != 2 or x_strides[1] != 1:
         raise ValueError("X must be 2-D with unit inner stride")
-    if _torch_dtype_code(X) != d:
+    if X.dtype is not dY.dtype:
         raise TypeError("X and dY must share a dtype")
-    return Layer(kind, d, out, n_in, X.shape[0], X.data_ptr(), X.stride(0), dY.data_ptr(), dY.stride(0),
-                 split_k, 0, float(norm_eps))
+    return Layer(kind, d, out, n_in, tokens, X.data_ptr(), x_strides[0], dY.data_ptr(), dy_strides[0],
+                 split_k, 0, norm_eps)
 
 
 def chunk_array(n: int, begin: int, device="cuda", fill=None):
@@ -312,9 +325,12 @@ def chunk_state(n: int, begin: int, device="cuda", count: int = 3):
 
 
 def _stream_ptr(stream) -> int:
-    import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return s.cuda_stream
+    """The hipStream_t of `stream`, or of the current device's current stream.  The raw handle is asked for: a
+    Stream object built for it costs 3 us, as much as the launch itself."""
+    if stream is not None:
+        return stream.cuda_stream
+    torch = _torch or _torch_module()
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _ptr(t) -> Optional[int]:
