@@ -1217,10 +1217,16 @@ __device__ __forceinline__ void colsum_block(const WgradProblem& p, const Sinks&
   }
 }
 
-template <typename T, int MODE, int NORM, int NT, int CB>
-__global__ __launch_bounds__(NT) void colsum_kernel(const WgradProblem p, const Sinks s, const float* stats) {
+// one group per LPG lanes
+template <typename T, int CB> constexpr int kColsumThreads = kColsumGroups * CB / Piece<T>::N;
+
+template <typename T, int MODE, int NORM, int CB>
+__global__ __launch_bounds__((kColsumThreads<T, CB>)) void colsum_kernel(const WgradProblem p, const Sinks s, const float* stats,
+                                                                         int blocks) {
   __shared__ float red[colsum_lds_floats<CB>];
-  colsum_block<T, MODE, NORM, NT, CB>(p, s, stats, blockIdx.x, red);
+  const int block = xcd_work_item(blocks);
+  if (block < 0) return;
+  colsum_block<T, MODE, NORM, kColsumThreads<T, CB>, CB>(p, s, stats, block, red);
 }
 
 // ---------------------------------------------------------------------------
@@ -1772,20 +1778,33 @@ int launch_wgrad_simt(const WgradProblem& p, int dtype, int mode, const Sinks& s
   return dtype == 0 ? launch_wgrad_f32(p, mode, s, stream) : launch_wgrad_ragged(p, mode, s, stream);
 }
 
-// A block is one 128-byte line of every token: with half a line the two blocks of a line each fetch all of it
-// (bf16, 4096 x 4096: 25 against 18 us), with two lines an fp32 vector fills too few compute units (49 against 35 us).
-template <typename T, int NORM>
-static int launch_colsum_t(const WgradProblem& p, int mode, const Sinks& s, const float* stats, hipStream_t st) {
-  constexpr int CB = 128 / sizeof(T), NT = 1024;
+template <typename T, int NORM, int CB>
+static int launch_colsum_cb(const WgradProblem& p, int mode, const Sinks& s, const float* stats, hipStream_t st) {
   const int64_t blocks = ceil_div(p.end - p.begin, CB);
-  if (blocks > 0x7fffffff) return (int)hipErrorInvalidValue;
-  const dim3 grid((unsigned)blocks), threads(NT);
+  if (blocks > 0x7ffffff0) return (int)hipErrorInvalidValue;
+  const dim3 grid((unsigned)((blocks + 7) / 8 * 8)), threads((kColsumThreads<T, CB>));
+  const int n = (int)blocks;
   switch (mode) {
-    case EMIT_STORE: hipLaunchKernelGGL((colsum_kernel<T, EMIT_STORE, NORM, NT, CB>), grid, threads, 0, st, p, s, stats); break;
-    case EMIT_ACCUM: hipLaunchKernelGGL((colsum_kernel<T, EMIT_ACCUM, NORM, NT, CB>), grid, threads, 0, st, p, s, stats); break;
-    default: hipLaunchKernelGGL((colsum_kernel<T, EMIT_ADAMW, NORM, NT, CB>), grid, threads, 0, st, p, s, stats); break;
+    case EMIT_STORE: hipLaunchKernelGGL((colsum_kernel<T, EMIT_STORE, NORM, CB>), grid, threads, 0, st, p, s, stats, n); break;
+    case EMIT_ACCUM: hipLaunchKernelGGL((colsum_kernel<T, EMIT_ACCUM, NORM, CB>), grid, threads, 0, st, p, s, stats, n); break;
+    default: hipLaunchKernelGGL((colsum_kernel<T, EMIT_ADAMW, NORM, CB>), grid, threads, 0, st, p, s, stats, n); break;
   }
   return (int)hipGetLastError();
+}
+
+// What a block takes of every token: a whole 128-byte line, half of one or a quarter, the widest that still leaves no
+// compute unit with a second block.  A compute unit takes in about 27 bytes per clock in whole lines, so narrow vectors
+// want more units (the parts of a line meet in one XCD's L2: its blocks are neighbours there) and wide ones whole
+// lines.  Line / half / quarter, fused RMSNorm and LayerNorm calls in us: bf16 1024 wide, 16384 tokens 78 / 69 / 52;
+// 4096 wide, 4096 tokens 28.8 / 26.4 / 24.1; 8192 wide, 16384 tokens 183 / 174 / 255; 16384 wide, 4096 tokens
+// 67 / 73 / 87;  fp32 2048 wide, 4096 tokens 29.4 / 26.5 / 24.4; 4096 wide 48.4 / 45.5 / 50.2; 8192 wide 83 / 87 / 100.
+template <typename T, int NORM>
+static int launch_colsum_t(const WgradProblem& p, int mode, const Sinks& s, const float* stats, hipStream_t st) {
+  constexpr int LINE = 128 / sizeof(T);
+  const int64_t n = p.end - p.begin, cus = device_compute_units();
+  if (ceil_div(n, LINE / 4) <= cus) return launch_colsum_cb<T, NORM, LINE / 4>(p, mode, s, stats, st);
+  if (ceil_div(n, LINE / 2) <= cus) return launch_colsum_cb<T, NORM, LINE / 2>(p, mode, s, stats, st);
+  return launch_colsum_cb<T, NORM, LINE>(p, mode, s, stats, st);
 }
 
 int launch_colsum(const WgradProblem& p, int dtype, int mode, const Sinks& s, void* stream) {

@@ -512,6 +512,17 @@ def test_warm_state_on_ranges_with_separate_edge_rows(begin, end, split_k):
     _full_check(_small_bf16(seed=83), begin, end, split_k=split_k, warm=True, step=3)
 
 
+# A block takes a quarter, a half or the whole of a 128-byte line of a scale vector: on either side of 256 blocks of
+# each (bf16: 16, 32 and 64 columns a block, fp32: 8, 16 and 32).
+@pytest.mark.parametrize("dtype,n", [(WL.F32, 2048), (WL.F32, 2049), (WL.F32, 4097), (WL.BF16, 4096), (WL.BF16, 4099),
+                                     (WL.BF16, 8193)])
+def test_scale_vector_line_parts(dtype, n):
+    rng = np.random.default_rng(n)
+    for case in (WL.norm_case(rng, "n", n, 161, dtype, 1e-3, WL.LAYERNORM), WL.vector_case(rng, "v", n, 97, dtype, 1e-3)):
+        for begin, end in {(0, n), (1, n - 2)}:
+            _full_check(case, begin, end, warm=True, step=2)
+
+
 # ------------------------------------------- scaled-down configurations 2-5
 def test_config2_scaled():
     case, begin, end = WL.config2(scale=4)          # 3584 x 1024, 2 Mi-element chunk
