@@ -1867,8 +1867,12 @@ static int launch_elem(ElemParams& q, int mode, hipStream_t st) {
   int64_t blocks = ceil_div(nvec, 256);
   // One block of 256 threads per CU, one group of four elements per thread in flight: the
   // seven streams of the update then reach 5.9 - 6.0 TB/s; with twice the blocks, or twice the
-  // groups per trip, HBM efficiency drops to 5.3 - 5.4 TB/s (measured sweep).
-  const int64_t cap = (int64_t)device_compute_units();
+  // groups per trip, HBM efficiency drops to 5.3 - 5.4 TB/s (measured sweep: 16 Mi elements 87 us against 92).
+  // Short passes wait for latency instead: AdamW on 1 / 2 / 4 Mi elements 7.2 / 12.1 / 23.7 us with one block per CU,
+  // 6.4 / 10.8 / 22.8 with two, and the sum of slabs, whose slab loads add to the chain, takes four (fused call
+  // with 3 slabs, 2 / 4 Mi elements at 4096 tokens: 47.4 / 79.3 us with one, 43.6 / 70.7 with two, 42.7 / 68.2 with four).
+  const int64_t short_pass = int64_t(4) << 20;
+  const int64_t cap = (int64_t)device_compute_units() * (q.n > short_pass ? 1 : q.S > 1 ? 4 : 2);
   if (blocks > cap) blocks = cap;
   if (blocks < 1) blocks = 1;
   switch (mode) {

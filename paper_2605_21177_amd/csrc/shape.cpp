@@ -52,12 +52,13 @@ int64_t small_tiles(int64_t in, int64_t begin, int64_t end) {
 // Which chunks go to the 64 x 64 tiles.  A 256 x 256 or 128 x 256 tile per compute unit needs millions of
 // elements; below that most of the device has no work (1 Mi elements of 1024 x 1024 at 256 tokens are 32
 // tiles: the fused call needed 30 us, 9 us of it latency in small tiles).  Small tiles read their operands
-// 1.5 - 4 times as often and a compute unit takes in 27 bytes per clock, so they lose where the token loop
-// decides.  Gradient / fused call in us, small tiles against the better of the large ones:
-//   1024 tokens: 0.5 Mi elements 9.9 / 12.2 against 18.8 / 19.6, 2 Mi 15 / 23 - 21 / 42, 4 Mi 20 / 37 - 20 / 43, 8 Mi
-//   (2112 tiles) 35 / 63 - 25 / 62;   2048 tokens: 2 Mi (528 tiles) 24 / 33 - 29 / 40, 4 Mi 32 / 46 - 29 / 52;
-//   4096 tokens: 1 Mi (272 tiles) 28 / 33 - 30 / 35, 2 Mi 41 / 49 - 37 / 48;   8192 tokens: 0.5 Mi (144 tiles) 28 / 31 -
-//   31 / 33, 1 Mi 43 / 48 - 37 / 43;   256 tokens: 4 Mi 11 / 26 - 14 / 38, 8 Mi 16 / 49 - 15 / 51.
+// 1.5 - 4 times as often, so they lose where the token loop decides.  Fused call in us, small tiles against the
+// better of the large ones, each at its best split (chunks of 4096-wide rows):
+//   256 tokens: 1 Mi elements 9 against 27, 4 Mi 27 - 37, 8 Mi (2112 tiles) 46 - 49;  1024 tokens: 1 Mi 15 - 25, 2 Mi 23 - 32,
+//   4 Mi 41 - 47, 8 Mi 67 - 63;   2048 tokens: 1 Mi 22 - 28, 2 Mi (528 tiles) 33 - 35, 4 Mi 59 - 51;   4096 tokens: 0.5 Mi (144
+//   tiles) 22 - 24, 1 Mi (272) 34 - 31, 2 Mi 51 - 42;   8192 tokens: 0.25 Mi 27 - 28, 0.5 Mi 36 - 36, 1 Mi 55 - 41;
+//   184-wide rows, 3620 tokens, 1.2 Mi (324 tiles) 44 - 38.  The gradient by itself crosses at the same products of tiles
+//   and tokens.
 bool takes_small_tiles(int64_t in, int64_t T, int64_t begin, int64_t end, int compute_units) {
   const int64_t cus = compute_units > 0 ? compute_units : kDefaultComputeUnits;
   WgradProblem p{};
@@ -66,7 +67,7 @@ bool takes_small_tiles(int64_t in, int64_t T, int64_t begin, int64_t end, int co
   p.in = in;
   if (!edge_rows_folded(split_rows(p))) return true;
   const int64_t tiles = small_tiles(in, begin, end);
-  return tiles <= cus * 43 / 10 && tiles * T <= cus * 6600;
+  return tiles <= cus * 43 / 10 && tiles * T <= cus * 4300;
 }
 
 bool group_takes_segment(const WgradProblem& p, bool vector) {

@@ -1,15 +1,15 @@
 // bf16 weight gradient in small tiles, for chunks that the large tiles leave most of the compute units
 // without work on (takes_small_tiles, shape.cpp, says which and what both sides measured).
 //
-// Four waves, each a 32 TB x 32 TB part of a 64 TB x 64 TB tile, slabs of 32 tokens in a ring of NS, moved by
+// Four waves, each a 32 TB x 32 TB part of a 64 TB x 64 TB tile, slabs of BK tokens in a ring of NS, moved by
 // 16-byte LDS loads and taken out by transpose reads as in the kernel with the large tiles, and every element
 // is summed over the tokens in the same order as there.  The rows a chunk begins and ends in are part of the
 // tiles (masked as they leave) instead of an extra block.
 //
 // A workgroup alone on its compute unit is a chain of one LDS latency and one barrier per slab (about 400
-// cycles: both steps of a slab are read at once, under the MFMAs of the slab before; read step by step it was
-// 480); with four to a compute unit the LDS loads bound it, 27 bytes per clock.  A 128 x 128 tile (TB = 2) has
-// half the loads but waits longer per slab: 44 against 27 us for 80 tiles at 4096 tokens, level at 4 Mi elements.
+// cycles for 32 tokens: all steps of a slab are read at once, under the MFMAs of the slab before; read step by
+// step it was 480); with four to a compute unit the LDS loads bound it, 27 bytes per clock.  A 128 x 128 tile (TB = 2) has
+// half the loads but waits longer per slab: 44 against 27 us for 80 tiles at 4096 tokens.
 // A ring of six slabs is slower than four (fewer workgroups per compute unit: 22 against 18 us at 4 Mi).
 #include "tiles.h"
 
@@ -17,9 +17,9 @@ namespace chunkft {
 
 namespace {
 
-template <int TB_, int NS_>
+template <int TB_, int NS_, int BK_>
 struct SmallCfg {
-  static constexpr int TB = TB_, NS = NS_, BM = 64 * TB, BN = 64 * TB, BK = 32, NT = 256;
+  static constexpr int TB = TB_, NS = NS_, BM = 64 * TB, BN = 64 * TB, BK = BK_, KS = BK / 16, NT = 256;
   static constexpr int IMAGE = BK * BM * 2, SLAB_BYTES = 2 * IMAGE;     // dY image, X image behind it
   static constexpr int LPW = IMAGE / 1024 / 4;                          // 1 KB loads of one image per wave
   static constexpr int SLOTS = BM / 8, TPL = 64 / SLOTS;                // 16-byte slots per token, tokens per load
@@ -95,11 +95,11 @@ __global__ __launch_bounds__(C::NT, 2) void wgrad_small_kernel(const TileGrid q)
   // the operands of a slab: two 16-token steps, per step and block the tokens +0..3 and +4..7 of the lane's eight
   // (four tokens on, a token's swizzle is the same)
   struct Operands {
-    bf16x4 a[4 * C::TB], b[4 * C::TB];
+    bf16x4 a[2 * C::KS * C::TB], b[2 * C::KS * C::TB];
   } r0, r1;
   auto read = [&](Operands& r, int slab) {
     const unsigned so = (unsigned)(slab % C::NS) * C::SLAB_BYTES;
-    static_for<2 * C::TB>([&](auto uc) {
+    static_for<C::KS * C::TB>([&](auto uc) {
       constexpr int ks = decltype(uc)::value / C::TB, i = decltype(uc)::value % C::TB, u = 2 * (ks * C::TB + i);
       r.a[u] = lds_tr_read<ks * 16 * C::BM * 2>(addr_a[i] + so);
       r.a[u + 1] = lds_tr_read<(ks * 16 + 4) * C::BM * 2>(addr_a[i] + so);
@@ -108,18 +108,21 @@ __global__ __launch_bounds__(C::NT, 2) void wgrad_small_kernel(const TileGrid q)
     });
   };
   auto landed = [&](Operands& r) {
-    asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(r.a[0]), "+v"(r.a[1]), "+v"(r.a[2]), "+v"(r.a[3]), "+v"(r.b[0]), "+v"(r.b[1]), "+v"(r.b[2]), "+v"(r.b[3])::"memory");
-    if constexpr (C::TB == 2)
-      asm volatile("" : "+v"(r.a[4]), "+v"(r.a[5]), "+v"(r.a[6]), "+v"(r.a[7]), "+v"(r.b[4]), "+v"(r.b[5]), "+v"(r.b[6]), "+v"(r.b[7])::"memory");
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < 2 * C::KS * C::TB; ++i) asm volatile("" : "+v"(r.a[i]), "+v"(r.b[i])::"memory");   // no use before the wait
   };
   auto mask = [&](Operands& r, int slab) {                               // tokens past the end
     if (slab == nk - 1 && (tokens % C::BK) != 0) {
       const int kv = tokens - slab * C::BK - (lane >> 5) * 8;
 #pragma unroll
-      for (int u = 0; u < 4 * C::TB; ++u)
+      for (int u = 0; u < 2 * C::KS * C::TB; ++u)
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-          if (u / (2 * C::TB) * 16 + (u & 1) * 4 + e >= kv) r.a[u][e] = (__bf16)0.f;
+          if (u / (2 * C::TB) * 16 + (u & 1) * 4 + e >= kv) {
+            r.a[u][e] = (__bf16)0.f;
+            r.b[u][e] = (__bf16)0.f;
+          }
     }
   };
   f32x16 acc[C::TB][C::TB];
@@ -131,7 +134,7 @@ __global__ __launch_bounds__(C::NT, 2) void wgrad_small_kernel(const TileGrid q)
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
   auto multiply = [&](const Operands& r) {
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks)
+    for (int ks = 0; ks < C::KS; ++ks)
 #pragma unroll
       for (int i = 0; i < C::TB; ++i)
 #pragma unroll
@@ -210,8 +213,12 @@ int launch_cfg(const WgradProblem& p, int mode, const Sinks& s, hipStream_t st) 
 
 }  // namespace
 
+// Slabs of 64 tokens halve the barriers and the chains of a token count; up to 256 tokens the slabs of 32 start sooner
+// (fused call, 32- / 64-token slabs: 0.25 Mi elements at 256 tokens 6.9 / 7.5 us, 1 Mi 9.0 / 9.3; 1024 tokens: 0.5 Mi
+// 12.3 / 11.6, 1 Mi 16.7 / 15.6; 2048 tokens: 1 Mi 23.9 / 22.1; 4096 tokens: 0.5 Mi in two slabs 25.3 / 23.6).
 int launch_wgrad_small(const WgradProblem& p, int mode, const Sinks& s, void* stream) {
-  return launch_cfg<SmallCfg<1, 4>>(p, mode, s, (hipStream_t)stream);
+  if (p.kslab <= 256) return launch_cfg<SmallCfg<1, 4, 32>>(p, mode, s, (hipStream_t)stream);
+  return launch_cfg<SmallCfg<1, 2, 64>>(p, mode, s, (hipStream_t)stream);
 }
 
 }  // namespace chunkft

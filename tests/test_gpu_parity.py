@@ -297,6 +297,24 @@ def test_bf16_small_tiles(out, n_in, T, split_k):
         _full_check(case, begin, end, split_k=split_k if split_k and T >= 2 * split_k else None, warm=True, step=2)
 
 
+# More than 256 tokens: slabs of 64 in a ring of two, tails of 1 to 63 tokens; inf and NaN in the last token stay in
+# their row and column (tokens past the end count as zeros of both operands).
+@pytest.mark.parametrize("out,n_in,T,split_k", [(72, 136, 257, None), (64, 64, 319, None), (136, 72, 320, None), (200, 264, 321, None),
+                                                (8, 2056, 383, None), (264, 200, 1100, 2)])
+def test_bf16_small_tiles_long(out, n_in, T, split_k):
+    case = WL.linear_case(np.random.default_rng(19 * out + n_in), "s", out, n_in, T, WL.BF16, 1e-3)
+    n = out * n_in
+    for begin, end in {(0, n), (n // 3, n - n // 5)}:
+        _full_check(case, begin, end, split_k=split_k, warm=True, step=2)
+    X, dY = case.X.to(H.DEV), case.dY.to(H.DEV)
+    X[T - 1, 5], dY[T - 1, 3] = float("inf"), float("nan")
+    g = torch.empty(n, dtype=torch.float32, device=H.DEV)
+    B.chunkft_chunk_wgrad(B.make_layer(B.LINEAR, X, dY, out, n_in, split_k=1), 0, n, g)
+    bad = ~torch.isfinite(g.view(out, n_in))
+    assert bad[3].all() and bad[:, 5].all() and int(bad.sum()) == out + n_in - 1
+    assert torch.isinf(g.view(out, n_in)[torch.arange(out, device=H.DEV) != 3, 5]).all()
+
+
 def test_bf16_unaligned_shape_takes_fma_path():
     rng = np.random.default_rng(78)
     case = WL.linear_case(rng, "odd", 137, 100, 53, WL.BF16, 1e-3)   # in, out not multiples of 8
