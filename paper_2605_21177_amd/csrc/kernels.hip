@@ -1310,26 +1310,28 @@ __global__ __launch_bounds__(256) void norm_stats_kernel(const T* X, int64_t ldx
 // ---------------------------------------------------------------------------
 // embedding table gradient: g[r, :] = sum over the tokens t with ids[t] = r of dY[t, :]
 // ---------------------------------------------------------------------------
-// A workgroup of 8 waves owns kEmbRows = 64 consecutive table rows and a block of 1024
-// columns (blockIdx.y).  It first turns the token ids into "which of my rows, if any" in LDS
-// (one coalesced pass over the ids per workgroup), its first wave compacts that in place into
-// the short list of tokens that hit any of the 64 rows (token order kept), and then every
-// wave takes 8 of the rows one after the other: it walks the list, picks the entries of its
-// row and adds their dY rows in ascending token order -- no atomics, the order of the sum is
-// fixed.  The loads of four tokens are issued before their additions, so a row that several
+// A group is kEmbRows = 64 consecutive table rows and a block of 1024 columns; a workgroup of 8 waves takes
+// it, or one of its PARTS runs of rows.  It first turns the token ids into "which of the group's rows, if
+// any" in LDS (every wave a run of the tokens, counted and then written behind the hits of the waves
+// before it), the short list of hits in token order.  Every wave then takes rows in turn: it looks through
+// the list 64 entries at a time (a ballot per 64; entry by entry, as it was, the walk was a chain of LDS
+// latencies as long as the list: 154 us for a 8000 x 512 table at 1024 tokens, now 38) and adds the dY rows
+// of its row in ascending token order -- no atomics, the order of the sum is fixed.  The loads of four
+// tokens are issued before their additions, so a row that several
 // tokens name does not cost one memory latency per token; a row that very many name (token
-// frequencies are heavy-tailed: the commonest token can be a tenth of a batch) is summed by
-// all eight waves together, wave w taking every eighth hit, and the eight partial sums are
-// added in wave order -- still a fixed order.  A lane holds the columns 256 i + 4 lane + e (i < kEmbIter, e < 4), so loads and
+// frequencies are heavy-tailed: the commonest token can be a tenth of a batch, and common tokens
+// can be neighbours in the table) is summed by all eight waves together, wave w taking every eighth hit,
+// and the eight partial sums are added in wave order -- still a fixed order.  A lane holds the columns
+// 256 i + 4 lane + e (i < kEmbIter, e < 4), so loads and
 // stores of a wave are 1 KB (fp32) pieces.  HBM-bound: the rows are written (or updated)
 // once, whether any token names them or not -- except when the result is added to g
-// (accumulation over micro-batches), where only the named rows are touched.
+// (accumulation over micro-batches), where only the named rows are touched.  Fused call, 128 Mi elements of
+// 128256 x 4096 at 4096 tokens: 635 us = 5.5 TB/s (710 with one part, the walk and two shared rows a group at most).
 constexpr int kEmbWaves = 8;
-constexpr int kEmbRows = 64;       // rows per workgroup, kEmbRows / kEmbWaves per wave
+constexpr int kEmbRows = 64;       // rows of a group
 constexpr int kEmbIter = 4;        // 256-column pieces per workgroup
 constexpr int kEmbTok = 8192;      // most tokens per call (their list lives in LDS)
-constexpr int kEmbHot = 32;        // hits from which a row is summed by all waves together ...
-constexpr int kEmbHotMax = 2;      // ... for at most this many rows of a workgroup
+constexpr int kEmbHot = 32;        // hits from which a row is summed by all waves together
 
 template <typename T> __device__ __forceinline__ void load4_as_f32(const T* p, int valid, float (&o)[4]);
 template <> __device__ __forceinline__ void load4_as_f32<float>(const float* p, int valid, float (&o)[4]) {
@@ -1353,42 +1355,54 @@ template <> __device__ __forceinline__ void load4_as_f32<unsigned short>(const u
   }
 }
 
-template <typename T, int MODE>
+template <typename T, int MODE, int PARTS>
 __global__ __launch_bounds__(64 * kEmbWaves) void embed_wgrad_kernel(const WgradProblem p, const Sinks s) {
+  constexpr int kPartRows = kEmbRows / PARTS;
   __shared__ int list[kEmbTok];
-  __shared__ int list_len, n_hot;
-  __shared__ int hits_of[kEmbRows], hot_row[kEmbHotMax];
-  __shared__ float part[kEmbWaves][256 * kEmbIter];
-  __shared__ float hot_sum[kEmbHotMax][256 * kEmbIter];
+  __shared__ unsigned char row_of[kEmbTok];
+  __shared__ int wave_hits[kEmbWaves], hits_of[kEmbRows];
+  __shared__ __attribute__((aligned(16))) float part[kEmbWaves][256 * kEmbIter];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   // column blocks of one group of rows are neighbours in the launch order, so that a row's
   // pieces are touched at about the same time
   const int n_cblk = (int)((p.in + 256 * kEmbIter - 1) / (256 * kEmbIter));
-  const int64_t row_base = p.begin / p.in + (int64_t)(blockIdx.x / n_cblk) * kEmbRows;
+  const int part_id = (int)(blockIdx.x / n_cblk % PARTS);
+  const int64_t row_base = p.begin / p.in + (int64_t)(blockIdx.x / n_cblk / PARTS) * kEmbRows;
   const int64_t row_last = (p.end - 1) / p.in;
   const int64_t cbase = (int64_t)(blockIdx.x % n_cblk) * (256 * kEmbIter);
   const int64_t* ids = (const int64_t*)p.X;
   const T* dY = (const T*)p.dY;
   const int n = (int)p.T;                                   // <= kEmbTok, checked by the launcher
-  for (int i = threadIdx.x; i < n; i += 64 * kEmbWaves) {
-    const int64_t d = ids[i] - row_base;
-    list[i] = (d >= 0 && d < kEmbRows) ? (int)d : -1;
+  // every wave takes a run of whole 64s of the tokens: notes which of the rows each names and counts its hits, then
+  // writes them behind those of the waves before it as entries (token << 6 | row), so that token order is kept
+  const int run = (n + 64 * kEmbWaves - 1) / (64 * kEmbWaves) * 64, t_begin = wave * run;
+  const int t_end = t_begin + run < n ? t_begin + run : n;
+  int count = 0;
+#pragma unroll 4
+  for (int t0 = t_begin; t0 < t_end; t0 += 64) {
+    const int64_t d = t0 + lane < t_end ? ids[t0 + lane] - row_base : -1;
+    const bool hit = d >= 0 && d < kEmbRows;
+    row_of[t0 + lane] = hit ? (unsigned char)d : (unsigned char)255;
+    count += __popcll(__ballot(hit));
   }
+  if (lane == 0) wave_hits[wave] = count;
   __syncthreads();
-  // wave 0: in-place compaction to entries (token << 6 | row), in token order; the write
-  // position never passes the read position
-  if (wave == 0) {
-    int count = 0;
-    for (int t0 = 0; t0 < n; t0 += 64) {
-      const int w = t0 + lane < n ? list[t0 + lane] : -1;
-      const unsigned long long hits = __ballot(w >= 0);
-      if (w >= 0) list[count + __popcll(hits & ((1ull << lane) - 1ull))] = ((t0 + lane) << 6) | w;
-      count += __popcll(hits);
+  int at = 0, len = 0;
+#pragma unroll
+  for (int w = 0; w < kEmbWaves; ++w) {
+    if (w == wave) at = len;
+    len += wave_hits[w];
+  }
+  if (count > 0) {
+#pragma unroll 4
+    for (int t0 = t_begin; t0 < t_end; t0 += 64) {
+      const int r = row_of[t0 + lane];
+      const unsigned long long hits = __ballot(r != 255);
+      if (r != 255) list[at + __popcll(hits & ((1ull << lane) - 1ull))] = ((t0 + lane) << 6) | r;
+      at += __popcll(hits);
     }
-    if (lane == 0) list_len = count;
   }
   __syncthreads();
-  const int len = list_len;
   const int64_t E = p.end - p.begin;
   // adding to g: rows that no token names stay as they are, their traffic is saved
   if (MODE == EMIT_ACCUM && len == 0) return;               // the same for every thread
@@ -1418,17 +1432,19 @@ __global__ __launch_bounds__(64 * kEmbWaves) void embed_wgrad_kernel(const Wgrad
   // Sum of the hits of local row `r` that `mine(ordinal)` selects, ordinal = 0, 1, ... in token order.
   auto gather = [&](float (&into)[kEmbIter][4], int r, auto mine) {
     int q0 = 0, q1 = 0, q2 = 0, pending = 0, ordinal = 0;     // the last tokens found, oldest in q2
-    for (int j = 0; j < len; ++j) {
-      const int e = list[j];                                  // the same for every lane
-      if ((e & 63) != r) continue;
-      if (!mine(ordinal++)) continue;
-      const int t = e >> 6;
-      if (pending == 3) {
-        add_tokens(into, IntC<4>{}, q2, q1, q0, t);
-        pending = 0;
-      } else {
-        q2 = q1; q1 = q0; q0 = t;
-        ++pending;
+    for (int j0 = 0; j0 < len; j0 += 64) {
+      const int e = j0 + lane < len ? list[j0 + lane] : -1;
+      unsigned long long found = __ballot(e >= 0 && (e & 63) == r);
+      for (; found != 0; found &= found - 1) {
+        if (!mine(ordinal++)) continue;
+        const int t = __builtin_amdgcn_readlane(e, __builtin_ctzll(found)) >> 6;
+        if (pending == 3) {
+          add_tokens(into, IntC<4>{}, q2, q1, q0, t);
+          pending = 0;
+        } else {
+          q2 = q1; q1 = q0; q0 = t;
+          ++pending;
+        }
       }
     }
     if (pending == 3) { add_tokens(into, IntC<2>{}, q2, q1, 0, 0); add_tokens(into, IntC<1>{}, q0, 0, 0, 0); }
@@ -1436,87 +1452,41 @@ __global__ __launch_bounds__(64 * kEmbWaves) void embed_wgrad_kernel(const Wgrad
     else if (pending == 1) add_tokens(into, IntC<1>{}, q0, 0, 0, 0);
   };
 
-  // ---- rows with very many hits: all waves together
   for (int i = threadIdx.x; i < kEmbRows; i += 64 * kEmbWaves) hits_of[i] = 0;
   __syncthreads();
   for (int j = threadIdx.x; j < len; j += 64 * kEmbWaves) atomicAdd(&hits_of[list[j] & 63], 1);
   __syncthreads();
-  if (threadIdx.x == 0) {
-    int nh = 0;
-    for (int r = 0; r < kEmbRows && nh < kEmbHotMax; ++r)
-      if (hits_of[r] >= kEmbHot) hot_row[nh++] = r;
-    n_hot = nh;
-  }
-  __syncthreads();
-  const int nh = n_hot;
-  for (int h = 0; h < nh; ++h) {
-    float pacc[kEmbIter][4];
-#pragma unroll
-    for (int i = 0; i < kEmbIter; ++i)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) pacc[i][e] = 0.f;
-    gather(pacc, hot_row[h], [&](int ordinal) { return (ordinal & (kEmbWaves - 1)) == wave; });
-#pragma unroll
-    for (int i = 0; i < kEmbIter; ++i)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) part[wave][i * 256 + 4 * lane + e] = pacc[i][e];
-    __syncthreads();
-    for (int c = threadIdx.x; c < 256 * kEmbIter; c += 64 * kEmbWaves) {
-      float sum = part[0][c];
-#pragma unroll
-      for (int w = 1; w < kEmbWaves; ++w) sum += part[w][c];
-      hot_sum[h][c] = sum;
-    }
-    __syncthreads();
-  }
 
-  for (int sub = 0; sub < kEmbRows / kEmbWaves; ++sub) {
-    const int local = sub * kEmbWaves + wave;               // consecutive rows go to different waves
-    const int64_t row = row_base + local;
-    if (row > row_last) break;
-    if (MODE == EMIT_ACCUM && hits_of[local] == 0) continue;
-    float acc[kEmbIter][4];
-#pragma unroll
-    for (int i = 0; i < kEmbIter; ++i)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) acc[i][e] = 0.f;
-    // The row's state is requested first, so that it travels while the hit list is walked.
+  // One row of the part: where its pieces go, their state requested; and the update from the sums in `acc`.
+  struct Row {
     Vec4Sink d[kEmbIter];
     State4 st[kEmbIter];
     bool whole[kEmbIter];
+  };
+  auto request = [&](Row& w, int64_t row) {
 #pragma unroll
     for (int i = 0; i < kEmbIter; ++i) {
       const int64_t c = cbase + i * 256 + 4 * lane;
       const int64_t flat = row * p.in + c;
-      whole[i] = c + 4 <= p.in && flat >= p.begin && flat + 4 <= p.end;
+      w.whole[i] = c + 4 <= p.in && flat >= p.begin && flat + 4 <= p.end;
       const int64_t k = flat - p.begin;
-      d[i].g = s.g + k;
-      d[i].master = s.master + k;
-      d[i].m = s.m + k;
-      d[i].v = s.v + k;
-      d[i].W = s.w_kind == W_BF16 ? (void*)((unsigned short*)s.W + flat) : (void*)((float*)s.W + flat);
-      if (whole[i]) st[i] = load_state4<MODE>(d[i]);
+      w.d[i].g = s.g + k;
+      w.d[i].master = s.master + k;
+      w.d[i].m = s.m + k;
+      w.d[i].v = s.v + k;
+      w.d[i].W = s.w_kind == W_BF16 ? (void*)((unsigned short*)s.W + flat) : (void*)((float*)s.W + flat);
+      if (w.whole[i]) w.st[i] = load_state4<MODE>(w.d[i]);
     }
-    int hot = -1;
-    for (int h = 0; h < nh; ++h)
-      if (hot_row[h] == local) hot = h;
-    if (hot >= 0) {
-#pragma unroll
-      for (int i = 0; i < kEmbIter; ++i)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) acc[i][e] = hot_sum[hot][i * 256 + 4 * lane + e];
-    } else {
-      gather(acc, local, [](int) { return true; });
-    }
-
+  };
+  auto finish = [&](Row& w, int64_t row, const float (&acc)[kEmbIter][4]) {
 #pragma unroll
     for (int i = 0; i < kEmbIter; ++i) {
       const int64_t c = cbase + i * 256 + 4 * lane;
       if (c >= p.in) continue;
       const int64_t flat = row * p.in + c;
-      if (whole[i]) {
+      if (w.whole[i]) {
         const f32x4_u val = {acc[i][0], acc[i][1], acc[i][2], acc[i][3]};
-        finish4<MODE>(d[i], s.w_kind, s.c, val, st[i]);
+        finish4<MODE>(w.d[i], s.w_kind, s.c, val, w.st[i]);
       } else {
 #pragma unroll
         for (int e = 0; e < 4; ++e)
@@ -1524,6 +1494,52 @@ __global__ __launch_bounds__(64 * kEmbWaves) void embed_wgrad_kernel(const Wgrad
             emit<MODE>(s, E, 0, flat + e - p.begin, flat + e, acc[i][e]);
       }
     }
+  };
+
+  // ---- rows with very many hits: summed by all waves together, updated by one of them
+  for (int local = part_id * kPartRows; local < (part_id + 1) * kPartRows; ++local) {
+    if (hits_of[local] < kEmbHot) continue;                 // the same for every thread
+    float acc[kEmbIter][4];
+#pragma unroll
+    for (int i = 0; i < kEmbIter; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[i][e] = 0.f;
+    gather(acc, local, [&](int ordinal) { return (ordinal & (kEmbWaves - 1)) == wave; });
+#pragma unroll
+    for (int i = 0; i < kEmbIter; ++i) *(float4*)&part[wave][i * 256 + 4 * lane] = float4{acc[i][0], acc[i][1], acc[i][2], acc[i][3]};
+    __syncthreads();
+    if (wave == (local & (kEmbWaves - 1))) {
+      Row w;
+      request(w, row_base + local);
+#pragma unroll
+      for (int i = 0; i < kEmbIter; ++i) {
+        float4 sum = *(const float4*)&part[0][i * 256 + 4 * lane];
+#pragma unroll
+        for (int k = 1; k < kEmbWaves; ++k) {
+          const float4 x = *(const float4*)&part[k][i * 256 + 4 * lane];
+          sum.x += x.x; sum.y += x.y; sum.z += x.z; sum.w += x.w;
+        }
+        acc[i][0] = sum.x; acc[i][1] = sum.y; acc[i][2] = sum.z; acc[i][3] = sum.w;
+      }
+      finish(w, row_base + local, acc);
+    }
+    __syncthreads();
+  }
+
+  for (int sub = 0; sub < kPartRows / kEmbWaves; ++sub) {
+    const int local = part_id * kPartRows + sub * kEmbWaves + wave;     // consecutive rows go to different waves
+    const int64_t row = row_base + local;
+    if (row > row_last) break;
+    if (hits_of[local] >= kEmbHot || (MODE == EMIT_ACCUM && hits_of[local] == 0)) continue;
+    float acc[kEmbIter][4];
+#pragma unroll
+    for (int i = 0; i < kEmbIter; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[i][e] = 0.f;
+    Row w;
+    request(w, row);                                        // travels while the hit list is walked
+    if (hits_of[local] > 0) gather(acc, local, [](int) { return true; });
+    finish(w, row, acc);
   }
 }
 
@@ -1831,27 +1847,31 @@ int launch_norm_wgrad(const WgradProblem& p, int dtype, bool subtract_mean, floa
                     : launch_colsum_t<unsigned short, 1>(p, mode, s, stats, st);
 }
 
-template <typename T>
-static int launch_embed_t(const WgradProblem& p, dim3 grid, int mode, const Sinks& s, hipStream_t st) {
-  // The update streams seven arrays: it runs 8 % faster with one workgroup per CU than with the
-  // two that fit (4.06 against 3.73 TB/s), so that mode asks for LDS it does not use; the plain
-  // gradient only writes and is faster with two.
-  const size_t pad = mode == EMIT_ADAMW ? 40 * 1024 : 0;
-  switch (mode) {
-    case EMIT_STORE: hipLaunchKernelGGL((embed_wgrad_kernel<T, EMIT_STORE>), grid, dim3(64 * kEmbWaves), pad, st, p, s); break;
-    case EMIT_ACCUM: hipLaunchKernelGGL((embed_wgrad_kernel<T, EMIT_ACCUM>), grid, dim3(64 * kEmbWaves), pad, st, p, s); break;
-    default: hipLaunchKernelGGL((embed_wgrad_kernel<T, EMIT_ADAMW>), grid, dim3(64 * kEmbWaves), pad, st, p, s); break;
-  }
+// A row group as one workgroup or as four.  The update takes four: a part of 16 rows evens out the device, and what it
+// repeats (the pass over the ids) is little beside 26 bytes per element.  The gradient alone takes one where the row
+// groups already give every compute unit more than four.  One / four parts, in us, 4096 tokens: 128 Mi elements of a
+// 128256 x 4096 table, updated 695 / 635, written 210 / 263, added to 94 / 183; 32 Mi of 32000 x 4096 207 / 168, 125 / 68,
+// 79 / 60; 4000 x 8192 435 / 187, 362 / 170, 366 / 169.  (Two parts: 724, 180 and 247 updated.)
+template <typename T, int MODE>
+static int launch_embed_mode(const WgradProblem& p, int64_t groups, const Sinks& s, hipStream_t st) {
+  const dim3 threads(64 * kEmbWaves);
+  if (MODE != EMIT_ADAMW && groups > 4 * (int64_t)device_compute_units())
+    hipLaunchKernelGGL((embed_wgrad_kernel<T, MODE, 1>), dim3((unsigned)groups), threads, 0, st, p, s);
+  else
+    hipLaunchKernelGGL((embed_wgrad_kernel<T, MODE, 4>), dim3((unsigned)groups * 4), threads, 0, st, p, s);
   return (int)hipGetLastError();
 }
 
 int launch_embed_wgrad(const WgradProblem& p, int dtype, int mode, const Sinks& s, void* stream) {
   const int64_t rows = (p.end - 1) / p.in - p.begin / p.in + 1;
   const int64_t gx = ceil_div(rows, kEmbRows), gy = ceil_div(p.in, 256 * kEmbIter);
-  if (gy > 65535 || gx > 0x7fffffff / gy || p.T > kEmbTok) return (int)hipErrorInvalidValue;
-  const dim3 grid((unsigned)(gx * gy));
-  return dtype == 0 ? launch_embed_t<float>(p, grid, mode, s, (hipStream_t)stream)
-                    : launch_embed_t<unsigned short>(p, grid, mode, s, (hipStream_t)stream);
+  if (gy > 65535 || gx > 0x7fffffff / 4 / gy || p.T > kEmbTok) return (int)hipErrorInvalidValue;
+  const hipStream_t st = (hipStream_t)stream;
+  switch (mode) {
+    case EMIT_STORE: return dtype == 0 ? launch_embed_mode<float, EMIT_STORE>(p, gx * gy, s, st) : launch_embed_mode<unsigned short, EMIT_STORE>(p, gx * gy, s, st);
+    case EMIT_ACCUM: return dtype == 0 ? launch_embed_mode<float, EMIT_ACCUM>(p, gx * gy, s, st) : launch_embed_mode<unsigned short, EMIT_ACCUM>(p, gx * gy, s, st);
+    default: return dtype == 0 ? launch_embed_mode<float, EMIT_ADAMW>(p, gx * gy, s, st) : launch_embed_mode<unsigned short, EMIT_ADAMW>(p, gx * gy, s, st);
+  }
 }
 
 static int launch_elem(ElemParams& q, int mode, hipStream_t st) {

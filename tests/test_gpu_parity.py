@@ -492,6 +492,24 @@ def test_embedding_kind(dtype):
     _full_check(same, 0, 40 * 64)
 
 
+# Token counts around the runs of whole 64s that the eight waves take; neighbouring rows that very many tokens name (31
+# to 33 of them: on either side of the shared sum), one of them the first and the last row of the range.
+@pytest.mark.parametrize("rows,width,T", [(70, 264, 1), (70, 264, 63), (130, 40, 65), (200, 1032, 511), (65, 1028, 513),
+                                          (300, 24, 1025), (129, 264, 8191), (64, 264, 8192)])
+def test_embedding_runs_and_neighbouring_hot_rows(rows, width, T):
+    rng = np.random.default_rng(rows + T)
+    for dtype in (WL.BF16, WL.F32):
+        case = WL.embedding_case(rng, "hot", rows, width, T, dtype, 1e-3)
+        at = 0
+        for row, hits in ((0, 40), (1, 31), (2, 32), (3, 33), (17, 100), (rows - 1, 64)):
+            if at + hits < T:
+                case.X[at:at + hits] = row
+                at += hits
+        case.X[:] = case.X[torch.from_numpy(rng.permutation(T))]
+        _full_check(case, 0, rows * width, warm=True, step=2)
+        _full_check(case, width // 2 + 1, (rows - 1) * width + 5, warm=True, step=2)
+
+
 @pytest.mark.parametrize("kind", [WL.RMSNORM, WL.LAYERNORM])
 def test_self_normalising_scale_vectors(kind):
     rng = np.random.default_rng(83)
