@@ -11,6 +11,7 @@
 // step it was 480); with four to a compute unit the LDS loads bound it, 27 bytes per clock.  A 128 x 128 tile (TB = 2) has
 // half the loads but waits longer per slab: 44 against 27 us for 80 tiles at 4096 tokens.
 // A ring of six slabs is slower than four (fewer workgroups per compute unit: 22 against 18 us at 4 Mi).
+#include "slab_offset.h"
 #include "tiles.h"
 
 namespace chunkft {
@@ -54,7 +55,6 @@ __global__ __launch_bounds__(C::NT, 2) void wgrad_small_kernel(const TileGrid q)
   const int tk = lane / C::SLOTS, slot = swizzle<C>(lane % C::SLOTS, tk);
   const int64_t ra = w.row_b + slot * 8, cb = w.col_b + slot * 8;
   const unsigned ca = (unsigned)(ra < p.out ? ra : w.row_b) * 2u, cbo = (unsigned)(cb < p.in ? cb : w.col_b) * 2u;
-  const unsigned va = ca + (unsigned)tk * lda, vb = cbo + (unsigned)tk * ldb;
   const char* ga = (const char*)p.dY + w.k_begin * p.lddy * 2;
   const char* gb = (const char*)p.X + w.k_begin * p.ldx * 2;
   const unsigned base = (unsigned)(uintptr_t)lds;
@@ -69,14 +69,10 @@ __global__ __launch_bounds__(C::NT, 2) void wgrad_small_kernel(const TileGrid q)
 #pragma unroll
     for (int j = 0; j < C::LPW; ++j) {
       const int load = wave * C::LPW + j;
-      unsigned oa = va, ob = vb;
-      if (left < C::BK) {
-        const int t = load * C::TPL + tk, back = t < left ? 0 : t - (left - 1);
-        oa -= (unsigned)back * lda;
-        ob -= (unsigned)back * ldb;
-      }
-      to_lds(ga, oa, (unsigned)(load * C::TPL) * lda, dst + load * 1024);
-      to_lds(gb, ob, (unsigned)(load * C::TPL) * ldb, dst + C::IMAGE + load * 1024);
+      const LoadOffset oa = slab_offset(ca, lda, load * C::TPL, tk, left, C::BK);
+      const LoadOffset ob = slab_offset(cbo, ldb, load * C::TPL, tk, left, C::BK);
+      to_lds(ga, oa.lane, oa.scalar, dst + load * 1024);
+      to_lds(gb, ob.lane, ob.scalar, dst + C::IMAGE + load * 1024);
     }
     ga += (int64_t)C::BK * p.lddy * 2;
     gb += (int64_t)C::BK * p.ldx * 2;

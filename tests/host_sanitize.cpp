@@ -13,6 +13,7 @@
 
 #include "chunkft.h"
 #include "internal.h"
+#include "slab_offset.h"
 
 namespace {
 long g_launches = 0;
@@ -89,7 +90,31 @@ int launch_fused_group(const GroupSegment* segs, int n, bool, void*) {
 int launch_adamw(const float*, int64_t n, const Sinks&, void*, void*) { ++g_launches; expect(n > 0, "adamw size"); return 0; }
 }  // namespace chunkft
 
+// Every load of every slab, as the kernels that fetch by slab_offset() cut it: slabs of `slab` tokens, loads of
+// `tokens` tokens.  Each lane must name a token of the slab, its own one where that is there and the last one past the
+// end, with both parts of the offset non-negative: their sum, taken without wrapping, is the address.
+bool slab_offsets_ok(int slab, int tokens, unsigned column, unsigned token_bytes) {
+  for (int left = 1; left <= slab + 1; ++left)
+    for (int first = 0; first < slab; first += tokens)
+      for (int k = 0; k < tokens; ++k) {
+        const chunkft::LoadOffset o = chunkft::slab_offset(column, token_bytes, first, k, left, slab);
+        const uint64_t token = first + k < left ? first + k : left - 1;
+        if ((uint64_t)o.lane + o.scalar != column + token * token_bytes) {
+          printf("slab of %d tokens, %d left, load of token %d, lane token %d: offset %llu, token %llu is at %llu\n", slab, left, first, k,
+                 (unsigned long long)o.lane + o.scalar, (unsigned long long)token, (unsigned long long)(column + token * token_bytes));
+          return false;
+        }
+      }
+  return true;
+}
+
 int main() {
+  // slabs of 32 and 64 tokens in loads of 8 are the kernel's; token strides up to the largest of the path (64 tokens below 4 GiB)
+  for (const int slab : {8, 32, 64})
+    for (const int tokens : {4, 8})
+      for (const unsigned token_bytes : {16u, 8192u, 256512u, 66060288u})
+        for (const unsigned column : {0u, 4080u})
+          if (!slab_offsets_ok(slab, tokens, column, token_bytes)) return 1;
   std::mt19937_64 rng(1234);
   long plans = 0, calls = 0, accepted = 0;
   // ---- planner, plan summary, schedule
