@@ -47,7 +47,8 @@ __global__ __launch_bounds__(C::NT, C::WK == 1 && MODE != EMIT_ADAMW ? 3 : 2) vo
   const int group = wave / (C::WM * C::WN), in_group = wave % (C::WM * C::WN);
   const int wm = in_group / C::WN, wn = in_group % C::WN, gtid = (int)threadIdx.x % C::GT;
   // every group does the same number of slabs (the barriers are the workgroup's); tokens past a group's
-  // share or past the end count as zero rows of dY
+  // share or past the end count as zeros of both operands (with zeros in dY alone an infinity in X times them would
+  // be NaN)
   const int tokens = (int)(w.k_end - w.k_begin);
   const int nk = ((tokens + C::BK - 1) / C::BK + C::WK - 1) / C::WK;
   const int64_t k0 = w.k_begin + (int64_t)group * nk * C::BK;
@@ -87,7 +88,7 @@ __global__ __launch_bounds__(C::NT, C::WK == 1 && MODE != EMIT_ADAMW ? 3 : 2) vo
       for (int i = 0; i < C::NA; ++i) a[i] = *(const u32x4_a2*)(ga + i * TA * lda2 + va);
 #pragma unroll
       for (int i = 0; i < C::NB; ++i) b[i] = *(const u32x4_a2*)(gb + i * TB * ldb2 + vb);
-    } else {                                  // tokens past the end: the last one, zeroed when it is stored
+    } else {                                  // tokens past the end: the last one, both sides zeroed when they are stored
       const int64_t tl = t0 < last_t ? t0 : last_t;
       const int left = (int)(last_t - tl);
       const char* const ga = (const char*)p.dY + tl * lda2;
@@ -104,18 +105,38 @@ __global__ __launch_bounds__(C::NT, C::WK == 1 && MODE != EMIT_ADAMW ? 3 : 2) vo
       }
     }
   };
+  // Tokens past the end become zeros in registers, in slabs that are cut (64 x 128 and 64 x 64 tiles: no slower than without
+  // the zeros in X).  On the 128 x 128 tile that form costs the fused call 6 % (4097 x 4095, 2048 tokens: 219 -> 233 us); there dY
+  // is selected piece by piece and X overwritten behind its stores (224 us).  The gradient alone: 112 us in each form.
   auto store = [&](u32x4_t (&a)[C::NA], u32x4_t (&b)[C::NB], int kt) {
     unsigned char* const dst = mine + (kt & 1) * C::SLAB_BYTES;
+    const int64_t t0 = k0 + (int64_t)kt * C::BK;
+    const bool cut = t0 + C::BK > w.k_end;
+    const u32x4_t zeros = {0u, 0u, 0u, 0u};
+    if constexpr (C::WK > 1) {
+      if (cut) {
+        const int left = (int)(w.k_end - t0);
+#pragma unroll
+        for (int i = 0; i < C::NA; ++i)
+          if (ka + i * TA >= left) a[i] = zeros;
+#pragma unroll
+        for (int i = 0; i < C::NB; ++i)
+          if (kb + i * TB >= left) b[i] = zeros;
+      }
+    }
+    auto slot_a = [&](int k) { return (u32x4_t*)(dst + k * (C::BM * 2) + swizzle<C::BM>(sa, k) * 16); };
+    auto slot_b = [&](int k) { return (u32x4_t*)(dst + C::A_BYTES + k * (C::BN * 2) + swizzle<C::BN>(sb, k) * 16); };
 #pragma unroll
     for (int i = 0; i < C::NA; ++i) {
-      const int k = ka + i * TA;
-      if (k0 + (int64_t)kt * C::BK + k > last_t) a[i] = u32x4_t{0u, 0u, 0u, 0u};
-      *(u32x4_t*)(dst + k * (C::BM * 2) + swizzle<C::BM>(sa, k) * 16) = a[i];
+      if (C::WK == 1 && t0 + ka + i * TA > last_t) a[i] = zeros;
+      *slot_a(ka + i * TA) = a[i];
     }
 #pragma unroll
-    for (int i = 0; i < C::NB; ++i) {
-      const int k = kb + i * TB;
-      *(u32x4_t*)(dst + C::A_BYTES + k * (C::BN * 2) + swizzle<C::BN>(sb, k) * 16) = b[i];
+    for (int i = 0; i < C::NB; ++i) *slot_b(kb + i * TB) = b[i];
+    if (C::WK == 1 && cut) {
+#pragma unroll
+      for (int i = 0; i < C::NB; ++i)
+        if (t0 + kb + i * TB > last_t) *slot_b(kb + i * TB) = zeros;
     }
   };
 

@@ -284,6 +284,36 @@ def test_bf16_random_shapes_and_ranges():
                     step=1 + case_no % 3)
 
 
+def _check_infinities_in_the_last_tokens(case, split_k):
+    """An infinity in X and a NaN in dY at the last token of every slab: the gradient is infinite (with the sign of dY)
+    in the columns of the infinities and NaN in the rows of the NaNs, and finite everywhere else -- tokens past the end of
+    a slab count as zeros of both operands."""
+    out, n_in, T = case.out, case.n_in, case.X.shape[0]
+    X, dY = case.X.to(H.DEV), case.dY.to(H.DEV)
+    layer = B.make_layer(B.LINEAR, X, dY, out, n_in, split_k=split_k)
+    S = B.chunkft_split_k(layer, 0, out * n_in)
+    unit = 32 if case.dtype == WL.BF16 and out % 8 == 0 and n_in % 8 == 0 else 16      # a slab is a multiple of this
+    slab = -(-(-(-T // S)) // unit) * unit
+    lasts = [min((i + 1) * slab, T) - 1 for i in range(S)]
+    assert lasts[-1] == T - 1 and len(set(lasts)) == S == split_k and S < min(out, n_in)
+    want = torch.zeros(out, n_in, device=H.DEV)
+    for i, t in enumerate(lasts):
+        dY[t][dY[t] == 0] = 1e-3
+        X[t, i] = float("inf")
+        want[:, i] = torch.sign(dY[t].float()) * float("inf")
+    for i, t in enumerate(lasts):
+        dY[t, out - 1 - i] = float("nan")
+        want[out - 1 - i] = float("nan")
+    full, g = H.guarded(out * n_in)
+    ws = H.workspace_for(layer, 0, out * n_in)
+    B.chunkft_chunk_wgrad(layer, 0, out * n_in, g, ws=ws)
+    torch.cuda.synchronize()
+    assert H.guards_intact(full) and H.workspace_intact(ws)
+    got = g.view(out, n_in)
+    assert torch.equal(torch.isnan(got), torch.isnan(want)), "NaN where the NaNs of dY do not reach"
+    assert torch.equal(torch.where(torch.isinf(got), got, 0.0), torch.where(torch.isinf(want), want, 0.0))
+
+
 # Chunks of few tiles go to 64 x 64 tiles with a ring of four 32-token slabs: tensors smaller than a tile, a row
 # group or a column group more or less than one, ranges inside one row, token counts below, at and above a slab and the
 # ring, forced slabs and the ones the library picks (T = 2048 and 4160: several).
@@ -306,13 +336,7 @@ def test_bf16_small_tiles_long(out, n_in, T, split_k):
     n = out * n_in
     for begin, end in {(0, n), (n // 3, n - n // 5)}:
         _full_check(case, begin, end, split_k=split_k, warm=True, step=2)
-    X, dY = case.X.to(H.DEV), case.dY.to(H.DEV)
-    X[T - 1, 5], dY[T - 1, 3] = float("inf"), float("nan")
-    g = torch.empty(n, dtype=torch.float32, device=H.DEV)
-    B.chunkft_chunk_wgrad(B.make_layer(B.LINEAR, X, dY, out, n_in, split_k=1), 0, n, g)
-    bad = ~torch.isfinite(g.view(out, n_in))
-    assert bad[3].all() and bad[:, 5].all() and int(bad.sum()) == out + n_in - 1
-    assert torch.isinf(g.view(out, n_in)[torch.arange(out, device=H.DEV) != 3, 5]).all()
+    _check_infinities_in_the_last_tokens(case, split_k or 1)
 
 
 def test_bf16_unaligned_shape_takes_fma_path():
@@ -334,6 +358,17 @@ def test_bf16_rows_without_alignment(out, n_in, T, split_k):
     n = out * n_in
     for begin, end in ({(0, n), (n // 3, n - n // 5)} if n < 1 << 20 else {(1, n - 1)}):
         _full_check(case, begin, end, split_k=split_k if split_k and T >= 2 * split_k else None, warm=True, step=2)
+
+
+# The same tiles, and the fp32 kernels (LDS ring with few and with more tiles, registers with few and with more):
+# what tokens past the end of a slab multiply must be zeros on both sides.
+@pytest.mark.parametrize("dtype,out,n_in,T,split_k", [
+    (WL.BF16, 63, 200, 40, 1), (WL.BF16, 137, 101, 53, 1), (WL.BF16, 65, 64, 31, 1), (WL.BF16, 130, 131, 129, 3), (WL.BF16, 2051, 2053, 45, 1),
+    (WL.BF16, 2049, 2178, 161, 2), (WL.BF16, 2047, 2050, 1601, 1), (WL.F32, 100, 128, 257, 1), (WL.F32, 100, 128, 257, 3),
+    (WL.F32, 548, 1028, 69, 1), (WL.F32, 33, 129, 131, 1), (WL.F32, 33, 31, 17, 1), (WL.F32, 547, 1027, 33, 1), (WL.F32, 547, 1027, 101, 2)])
+def test_infinities_in_the_last_token_of_a_slab(dtype, out, n_in, T, split_k):
+    case = WL.linear_case(np.random.default_rng(23 * out + n_in), "i", out, n_in, T, dtype, 1e-3)
+    _check_infinities_in_the_last_tokens(case, split_k)
 
 
 def test_bf16_strided_operands():
