@@ -37,8 +37,8 @@ RowSplit split_rows(const WgradProblem& p) {
 }
 
 // The edge rows ride in the large-tile kernel if it has the tile rows that carry them (more than 128 body
-// rows = two tile rows of the 128 x 256 tile); a chunk with a shorter body goes to the small tiles, which
-// have no edge rows.
+// rows = two tile rows of the 128 x 256 tile); a chunk with edge rows and a shorter body goes to the small
+// tiles, which have no edge rows.
 bool edge_rows_folded(const RowSplit& rs) { return rs.rb1 - rs.rb0 > 128; }
 
 namespace {
@@ -59,15 +59,21 @@ int64_t small_tiles(int64_t in, int64_t begin, int64_t end) {
 //   tiles) 22 - 24, 1 Mi (272) 34 - 31, 2 Mi 51 - 42;   8192 tokens: 0.25 Mi 27 - 28, 0.5 Mi 36 - 36, 1 Mi 55 - 41;
 //   184-wide rows, 3620 tokens, 1.2 Mi (324 tiles) 44 - 38.  The gradient by itself crosses at the same products of tiles
 //   and tokens.
+// Bodies of at most 128 rows: with edge rows the large kernel cannot take them at all.  Without, it can, and the line is the
+// same (72 - 128 rows; 512 tiles 2048 tokens 27 - 37, 4096 tokens 43 - 38, 2048 tiles 1024 tokens 52 - 45, 8192 tokens 389 -
+// 280), but a body of at most 64 rows fills half a large tile and all of a small one: twice the line (64 rows; 256 tiles
+// 8192 tokens 54 - 67, 1024 tiles 1024 tokens 43 - 43, 2048 tokens 65 - 61, 4096 tokens 136 - 106).
 bool takes_small_tiles(int64_t in, int64_t T, int64_t begin, int64_t end, int compute_units) {
   const int64_t cus = compute_units > 0 ? compute_units : kDefaultComputeUnits;
   WgradProblem p{};
   p.begin = begin;
   p.end = end;
   p.in = in;
-  if (!edge_rows_folded(split_rows(p))) return true;
+  const RowSplit rs = split_rows(p);
+  const int64_t body = rs.rb1 - rs.rb0;
+  if (body <= 0 || ((rs.lead_base >= 0 || rs.trail_row >= 0) && !edge_rows_folded(rs))) return true;
   const int64_t tiles = small_tiles(in, begin, end);
-  return tiles <= cus * 43 / 10 && tiles * T <= cus * 4300;
+  return tiles <= cus * 43 / 10 && tiles * T <= cus * (body <= 64 ? 8600 : 4300);
 }
 
 bool group_takes_segment(const WgradProblem& p, bool vector) {

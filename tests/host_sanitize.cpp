@@ -108,6 +108,36 @@ bool slab_offsets_ok(int slab, int tokens, unsigned column, unsigned token_bytes
   return true;
 }
 
+// Which tile a chunk takes: what the large kernel cannot carry (no body row, edge rows beside a body of at most 128
+// rows) goes to the small tiles whatever its size, and nothing else does beyond the line in tiles and tokens, however
+// short its body is.
+bool tile_rule_ok(std::mt19937_64& rng) {
+  const int cus = chunkft::kDefaultComputeUnits;
+  for (int it = 0; it < 200000; ++it) {
+    chunkft::WgradProblem p{};
+    p.in = 8 * (1 + (int64_t)(rng() % (rng() % 2 ? 600 : 20000)));
+    p.T = 1 + (int64_t)(rng() % 16384);
+    const int64_t r0 = (int64_t)(rng() % 300), rows = 1 + (int64_t)(rng() % (rng() % 2 ? 150 : 3000));
+    p.begin = r0 * p.in;
+    p.end = (r0 + rows) * p.in;
+    if (rng() % 2) p.begin += (int64_t)(rng() % (uint64_t)p.in);                 // from mid-row
+    if (rng() % 2) p.end -= (int64_t)(rng() % (uint64_t)(p.in - (rows == 1 ? p.begin % p.in : 0)));
+    const chunkft::RowSplit rs = chunkft::split_rows(p);
+    const int64_t body = rs.rb1 - rs.rb0;
+    const bool edges = rs.lead_base >= 0 || rs.trail_row >= 0;
+    const bool carried = body > 0 && (!edges || chunkft::edge_rows_folded(rs));
+    const bool small = chunkft::takes_small_tiles(p.in, p.T, p.begin, p.end, cus);
+    const int64_t tiles = ((p.end - 1) / p.in - p.begin / p.in / 8 * 8 + 1 + 63) / 64 * ((p.in + 63) / 64);
+    const bool beyond = tiles > cus * 43 / 10 || tiles * p.T > cus * (body <= 64 ? 8600 : 4300);
+    if (carried ? small == beyond : !small) {
+      printf("[%ld, %ld) of %ld-wide rows, %ld tokens: body of %ld rows, %ld tiles, small tiles %d\n", (long)p.begin, (long)p.end, (long)p.in,
+             (long)p.T, (long)body, (long)tiles, (int)small);
+      return false;
+    }
+  }
+  return true;
+}
+
 int main() {
   // slabs of 32 and 64 tokens in loads of 8 are the kernel's; token strides up to the largest of the path (64 tokens below 4 GiB)
   for (const int slab : {8, 32, 64})
@@ -115,6 +145,8 @@ int main() {
       for (const unsigned token_bytes : {16u, 8192u, 256512u, 66060288u})
         for (const unsigned column : {0u, 4080u})
           if (!slab_offsets_ok(slab, tokens, column, token_bytes)) return 1;
+  std::mt19937_64 rule_rng(77);
+  if (!tile_rule_ok(rule_rng)) return 1;
   std::mt19937_64 rng(1234);
   long plans = 0, calls = 0, accepted = 0;
   // ---- planner, plan summary, schedule

@@ -327,6 +327,14 @@ def test_bf16_small_tiles(out, n_in, T, split_k):
         _full_check(case, begin, end, split_k=split_k if split_k and T >= 2 * split_k else None, warm=True, step=2)
 
 
+# Bodies of at most 128 rows without edge rows, too wide for the small tiles (more than 4.3 of them per compute unit): the
+# large kernel takes them, as a whole tensor or as whole rows in the middle of one, with a cut last column tile.
+@pytest.mark.parametrize("out,n_in,T,r0,r1", [(128, 35208, 40, 0, 128), (128, 35208, 33, 8, 108), (72, 70408, 31, 0, 64)])
+def test_bf16_short_wide_bodies(out, n_in, T, r0, r1):
+    case = WL.linear_case(np.random.default_rng(29 * out + T), "w", out, n_in, T, WL.BF16, 1e-3)
+    _full_check(case, r0 * n_in, r1 * n_in, warm=True, step=2)
+
+
 # More than 256 tokens: slabs of 64 in a ring of two, tails of 1 to 63 tokens; inf and NaN in the last token stay in
 # their row and column (tokens past the end count as zeros of both operands).
 @pytest.mark.parametrize("out,n_in,T,split_k", [(72, 136, 257, None), (64, 64, 319, None), (136, 72, 320, None), (200, 264, 321, None),
