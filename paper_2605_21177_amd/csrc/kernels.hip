@@ -296,7 +296,7 @@ __device__ __forceinline__ void mfma_tile(const MfmaParams& q, const int item, u
   // costs the matrix cores about 25 cycles, while the scalar-base form costs them nothing.
   // Rows / columns past the tensor are redirected to the tile's first ones (valid
   // memory, results masked in the epilogue); tokens past the end are clamped to
-  // the last token and zeroed in the A fragments (mask_halves).
+  // the last token and zeroed in the fragments of both operands (mask_halves).
   unsigned voa[C::LA], vob[C::LB];
   int ka[C::LA], kb[C::LB];
   const unsigned lddy2 = (unsigned)(p.lddy * 2), ldx2 = (unsigned)(p.ldx * 2);    // bytes per token
@@ -473,7 +473,7 @@ __device__ __forceinline__ void mfma_tile(const MfmaParams& q, const int item, u
     if (kt == nk - 1 && (klen % C::BK) != 0) {
       const int kv = klen - kt * C::BK - ks * 16 - (lane >> 5) * 8;   // valid tokens among this lane's 8
 #pragma unroll
-      for (int u = 0; u < 8; ++u)
+      for (int u = 0; u < 12; ++u)
 #pragma unroll
         for (int e = 0; e < 4; ++e)
           if ((u & 1) * 4 + e >= kv) h[u][e] = (__bf16)0.f;
@@ -594,10 +594,8 @@ __device__ __forceinline__ void mfma_tile(const MfmaParams& q, const int item, u
     if (fetch) next_slab();
     if constexpr (EDGE) edge_mma(he1, h1);
     __builtin_amdgcn_sched_barrier(0);
-    if (more) {
-      if constexpr (EDGE) WAIT_HALVES_E(h0, he0); else WAIT_HALVES(h0);
-      if constexpr (!FAST) mask_halves(h0, he0, kt + 1, 0);
-    }
+    if constexpr (EDGE) WAIT_HALVES_E(h0, he0); else WAIT_HALVES(h0);
+    if constexpr (!FAST) mask_halves(h0, he0, kt + 1, 0);
   };
 
   // Steady state: slabs whose fetch (of slab kt + NS) exists and is complete, in
@@ -856,12 +854,12 @@ __device__ __forceinline__ void mfma_tile16(const MfmaParams& q, const int item,
   auto frag = [&](const bf16x4* h, int u) {
     return __builtin_shufflevector(h[u], h[u + 1], 0, 1, 2, 3, 4, 5, 6, 7);
   };
-  // tokens past the end of a ragged last slab: zero in the row-block operands
-  auto mask_units = [&](bf16x4* h, int kt) {
+  // tokens past the end of a ragged last slab: zero in the operands (units [U0, U1) of h)
+  auto mask_units = [&](bf16x4* h, int kt, auto u0c, auto u1c) {
     if (kt == nk - 1 && (klen % C::BK) != 0) {
       const int kv = klen - kt * C::BK - blk * 8;            // valid tokens among this lane's 8
 #pragma unroll
-      for (int u = 0; u < 8; ++u)
+      for (int u = decltype(u0c)::value; u < decltype(u1c)::value; ++u)
 #pragma unroll
         for (int e = 0; e < 4; ++e)
           if ((u & 1) * 4 + e >= kv) h[u][e] = (__bf16)0.f;
@@ -910,7 +908,8 @@ __device__ __forceinline__ void mfma_tile16(const MfmaParams& q, const int item,
   he[0] = he[1] = bf16x4{};
   if (has_edge) read_e(0);
   WAIT8_8_2(ha0, hb, he);
-  mask_units(ha0, 0);
+  mask_units(ha0, 0, IntC<0>{}, IntC<8>{});
+  mask_units(hb, 0, IntC<0>{}, IntC<8>{});
   mask_edge(0);
   TIMELINE_STAMP(q, item, 1);
 
@@ -944,7 +943,10 @@ __device__ __forceinline__ void mfma_tile16(const MfmaParams& q, const int item,
     constexpr int ST_NEXT = FAST ? (KM + 1) % C::NS : 0;
     static_for<16>([&](auto ic) {
       constexpr int i = decltype(ic)::value, b = i / 4, a = (b & 1) ? 3 - i % 4 : i % 4;
-      if constexpr (i == 12) WAIT2_BEFORE8(hb);   // (nothing to wait for in slab 0: the prologue waited for everything)
+      if constexpr (i == 12) {
+        WAIT2_BEFORE8(hb);                         // (nothing to wait for in slab 0: the prologue waited for everything)
+        if constexpr (!FAST) mask_units(hb, kt, IntC<6>{}, IntC<8>{});
+      }
       __builtin_amdgcn_sched_barrier(0);
       acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(frag(ha0, 2 * a), frag(hb, 2 * b), acc[a][b], 0, 0, 0);
       __builtin_amdgcn_sched_barrier(0);
@@ -959,7 +961,7 @@ __device__ __forceinline__ void mfma_tile16(const MfmaParams& q, const int item,
     if constexpr (EDGE) edge_mma();
     __builtin_amdgcn_sched_barrier(0);
     WAIT8(ha1);
-    if constexpr (!FAST) mask_units(ha1, kt);
+    if constexpr (!FAST) mask_units(ha1, kt, IntC<0>{}, IntC<8>{});
     if (FAST || kt + C::NS - 1 < nk) {
       if (EDGE && wave == 0) wait_vmcnt<(C::NS - 2) * (C::L + 1)>(); else wait_vmcnt<(C::NS - 2) * C::L>();
     } else {
@@ -1003,12 +1005,11 @@ __device__ __forceinline__ void mfma_tile16(const MfmaParams& q, const int item,
     });
     if (fetch) next_slab();
     __builtin_amdgcn_sched_barrier(0);
-    if (more) {
-      WAIT8_6_2_BUT2(ha0, hb, he);
-      if constexpr (!FAST) {
-        mask_units(ha0, kt + 1);
-        if constexpr (EDGE) mask_edge(kt + 1);
-      }
+    WAIT8_6_2_BUT2(ha0, hb, he);
+    if constexpr (!FAST) {
+      mask_units(ha0, kt + 1, IntC<0>{}, IntC<8>{});
+      mask_units(hb, kt + 1, IntC<0>{}, IntC<6>{});
+      if constexpr (EDGE) mask_edge(kt + 1);
     }
   };
 

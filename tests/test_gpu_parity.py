@@ -284,14 +284,15 @@ def test_bf16_random_shapes_and_ranges():
                     step=1 + case_no % 3)
 
 
-def _check_infinities_in_the_last_tokens(case, split_k):
+def _check_infinities_in_the_last_tokens(case, split_k, begin=0, end=None):
     """An infinity in X and a NaN in dY at the last token of every slab: the gradient is infinite (with the sign of dY)
     in the columns of the infinities and NaN in the rows of the NaNs, and finite everywhere else -- tokens past the end of
     a slab count as zeros of both operands."""
     out, n_in, T = case.out, case.n_in, case.X.shape[0]
+    end = out * n_in if end is None else end
     X, dY = case.X.to(H.DEV), case.dY.to(H.DEV)
     layer = B.make_layer(B.LINEAR, X, dY, out, n_in, split_k=split_k)
-    S = B.chunkft_split_k(layer, 0, out * n_in)
+    S = B.chunkft_split_k(layer, begin, end)
     unit = 32 if case.dtype == WL.BF16 and out % 8 == 0 and n_in % 8 == 0 else 16      # a slab is a multiple of this
     slab = -(-(-(-T // S)) // unit) * unit
     lasts = [min((i + 1) * slab, T) - 1 for i in range(S)]
@@ -304,12 +305,12 @@ def _check_infinities_in_the_last_tokens(case, split_k):
     for i, t in enumerate(lasts):
         dY[t, out - 1 - i] = float("nan")
         want[out - 1 - i] = float("nan")
-    full, g = H.guarded(out * n_in)
-    ws = H.workspace_for(layer, 0, out * n_in)
-    B.chunkft_chunk_wgrad(layer, 0, out * n_in, g, ws=ws)
+    want = want.view(-1)[begin:end]
+    full, got = H.guarded(end - begin)
+    ws = H.workspace_for(layer, begin, end)
+    B.chunkft_chunk_wgrad(layer, begin, end, got, ws=ws)
     torch.cuda.synchronize()
     assert H.guards_intact(full) and H.workspace_intact(ws)
-    got = g.view(out, n_in)
     assert torch.equal(torch.isnan(got), torch.isnan(want)), "NaN where the NaNs of dY do not reach"
     assert torch.equal(torch.where(torch.isinf(got), got, 0.0), torch.where(torch.isinf(want), want, 0.0))
 
@@ -377,6 +378,16 @@ def test_bf16_rows_without_alignment(out, n_in, T, split_k):
 def test_infinities_in_the_last_token_of_a_slab(dtype, out, n_in, T, split_k):
     case = WL.linear_case(np.random.default_rng(23 * out + n_in), "i", out, n_in, T, dtype, 1e-3)
     _check_infinities_in_the_last_tokens(case, split_k)
+
+
+# The large tiles: 128 x 256 (short token counts, a split) and 256 x 256 (1100 tokens on), a slab that is one of the first, a
+# last slab of 1 to 31 tokens, with edge rows (begin and end mid-row) and without, a short wide body.
+@pytest.mark.parametrize("out,n_in,T,split_k,edges", [
+    (2400, 4096, 1, 1, True), (2400, 4096, 70, 1, True), (2400, 4096, 95, 1, False), (2400, 4096, 2049, 1, True), (2400, 4096, 2070, 1, False),
+    (2400, 4096, 31, 1, True), (2400, 4096, 170, 3, True), (128, 35208, 33, 1, False)])
+def test_infinities_in_the_last_token_on_the_large_tiles(out, n_in, T, split_k, edges):
+    case = WL.linear_case(np.random.default_rng(37 * out + T), "i", out, n_in, T, WL.BF16, 1e-3)
+    _check_infinities_in_the_last_tokens(case, split_k, *((3 * n_in + 77, (out - 3) * n_in + 5) if edges else ()))
 
 
 def test_bf16_strided_operands():
