@@ -65,6 +65,12 @@ bool plain_takes_large_tile(int64_t large_tiles, int64_t slab_tokens, int comput
 bool edge_rows_folded(const RowSplit& rs);                // the large-tile kernel carries the edge rows itself
 bool takes_small_tiles(int64_t in, int64_t T, int64_t begin, int64_t end, int compute_units);   // 64 x 64 tiles
 
+// A kernel launch counts its threads in 32 bits.
+constexpr int64_t kMaxLaunchThreads = 0xffffffff;
+// Into how many workgroups of kEmbedThreads threads a row group of the embedding gradient goes (1 or 4; 0: the launch cannot count them).
+constexpr int kEmbedThreads = 512;
+int embed_parts(bool update, int64_t groups, int compute_units);
+
 // Tile of the plain MFMA gradient, and of calls off its path: what the token split is chosen from.
 constexpr int64_t kMainTileM = 256, kMainTileN = 256, kMainTileK = 32;
 constexpr int64_t kSimtTileM = 64, kSimtTileN = 64, kSimtTileK = 16;

@@ -1333,6 +1333,7 @@ constexpr int kEmbRows = 64;       // rows of a group
 constexpr int kEmbIter = 4;        // 256-column pieces per workgroup
 constexpr int kEmbTok = 8192;      // most tokens per call (their list lives in LDS)
 constexpr int kEmbHot = 32;        // hits from which a row is summed by all waves together
+static_assert(64 * kEmbWaves == kEmbedThreads, "embed_parts counts the threads of a launch");
 
 template <typename T> __device__ __forceinline__ void load4_as_f32(const T* p, int valid, float (&o)[4]);
 template <> __device__ __forceinline__ void load4_as_f32<float>(const float* p, int valid, float (&o)[4]) {
@@ -1848,25 +1849,20 @@ int launch_norm_wgrad(const WgradProblem& p, int dtype, bool subtract_mean, floa
                     : launch_colsum_t<unsigned short, 1>(p, mode, s, stats, st);
 }
 
-// A row group as one workgroup or as four.  The update takes four: a part of 16 rows evens out the device, and what it
-// repeats (the pass over the ids) is little beside 26 bytes per element.  The gradient alone takes one where the row
-// groups already give every compute unit more than four.  One / four parts, in us, 4096 tokens: 128 Mi elements of a
-// 128256 x 4096 table, updated 695 / 635, written 210 / 263, added to 94 / 183; 32 Mi of 32000 x 4096 207 / 168, 125 / 68,
-// 79 / 60; 4000 x 8192 435 / 187, 362 / 170, 366 / 169.  (Two parts: 724, 180 and 247 updated.)
 template <typename T, int MODE>
 static int launch_embed_mode(const WgradProblem& p, int64_t groups, const Sinks& s, hipStream_t st) {
   const dim3 threads(64 * kEmbWaves);
-  if (MODE != EMIT_ADAMW && groups > 4 * (int64_t)device_compute_units())
-    hipLaunchKernelGGL((embed_wgrad_kernel<T, MODE, 1>), dim3((unsigned)groups), threads, 0, st, p, s);
-  else
-    hipLaunchKernelGGL((embed_wgrad_kernel<T, MODE, 4>), dim3((unsigned)groups * 4), threads, 0, st, p, s);
+  const int parts = embed_parts(MODE == EMIT_ADAMW, groups, device_compute_units());
+  if (parts == 1) hipLaunchKernelGGL((embed_wgrad_kernel<T, MODE, 1>), dim3((unsigned)groups), threads, 0, st, p, s);
+  else if (parts == 4) hipLaunchKernelGGL((embed_wgrad_kernel<T, MODE, 4>), dim3((unsigned)groups * 4), threads, 0, st, p, s);
+  else return (int)hipErrorInvalidValue;
   return (int)hipGetLastError();
 }
 
 int launch_embed_wgrad(const WgradProblem& p, int dtype, int mode, const Sinks& s, void* stream) {
   const int64_t rows = (p.end - 1) / p.in - p.begin / p.in + 1;
   const int64_t gx = ceil_div(rows, kEmbRows), gy = ceil_div(p.in, 256 * kEmbIter);
-  if (gy > 65535 || gx > 0x7fffffff / 4 / gy || p.T > kEmbTok) return (int)hipErrorInvalidValue;
+  if (gy > 65535 || gx > 0x7fffffff / gy || p.T > kEmbTok) return (int)hipErrorInvalidValue;
   const hipStream_t st = (hipStream_t)stream;
   switch (mode) {
     case EMIT_STORE: return dtype == 0 ? launch_embed_mode<float, EMIT_STORE>(p, gx * gy, s, st) : launch_embed_mode<unsigned short, EMIT_STORE>(p, gx * gy, s, st);

@@ -129,6 +129,18 @@ bool fused_takes_large_tile(const WgradProblem& p, int compute_units) {
   return round_ratio * round_cost(w) / (round_cost(2.0 * w) / 2.0) < 0.99;
 }
 
+// A row group as one workgroup or as four.  The update takes four: a part of 16 rows evens out the device, and what it
+// repeats (the pass over the ids) is little beside 26 bytes per element.  The gradient alone takes one where the row
+// groups already give every compute unit more than four.  One / four parts, in us, 4096 tokens: 128 Mi elements of a
+// 128256 x 4096 table, updated 695 / 635, written 210 / 263, added to 94 / 183; 32 Mi of 32000 x 4096 207 / 168, 125 / 68,
+// 79 / 60; 4000 x 8192 435 / 187, 362 / 170, 366 / 169.  (Two parts: 724, 180 and 247 updated.)  Where a launch cannot
+// count the threads of four parts (2^21 row groups, 128 Mi narrow rows) it is one; the sums are the same either way.
+int embed_parts(bool update, int64_t groups, int compute_units) {
+  const int64_t cus = compute_units > 0 ? compute_units : kDefaultComputeUnits, most = kMaxLaunchThreads / kEmbedThreads;
+  if (groups > most) return 0;
+  return (!update && groups > 4 * cus) || groups > most / 4 ? 1 : 4;
+}
+
 Split pick_split(int32_t kind, int32_t dtype, int64_t out, int64_t in, int64_t T, int64_t begin,
                  int64_t end, int32_t forced, bool mfma, int compute_units) {
   (void)out; (void)dtype;

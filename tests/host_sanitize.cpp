@@ -138,7 +138,22 @@ bool tile_rule_ok(std::mt19937_64& rng) {
   return true;
 }
 
+// The embedding gradient takes every number of row groups that a launch can count, in one part at least; never more.
+bool embed_parts_ok() {
+  const int64_t most = chunkft::kMaxLaunchThreads / chunkft::kEmbedThreads;
+  for (const bool update : {false, true})
+    for (const int64_t groups : {(int64_t)1, (int64_t)1024, (int64_t)1025, most / 4 - 1, most / 4, most / 4 + 1, most - 1, most, most + 1, most * 2}) {
+      const int parts = chunkft::embed_parts(update, groups, 256);
+      if ((parts != 0) != (groups <= most) || groups * parts * chunkft::kEmbedThreads > chunkft::kMaxLaunchThreads) {
+        printf("embedding: %ld row groups in %d parts\n", (long)groups, parts);
+        return false;
+      }
+    }
+  return true;
+}
+
 int main() {
+  if (!embed_parts_ok()) return 1;
   // slabs of 32 and 64 tokens in loads of 8 are the kernel's; token strides up to the largest of the path (64 tokens below 4 GiB)
   for (const int slab : {8, 32, 64})
     for (const int tokens : {4, 8})

@@ -466,3 +466,41 @@ def test_flat_element_indices_beyond_32_bits():
     hit = (ids >= r0) & (ids <= r1)
     g_ref = O.embedding_wgrad(ids[hit] - r0, WL.as_f64(dYe)[hit], r1 - r0 + 1, begin - r0 * n_in, end - r0 * n_in)
     run(B.EMBEDDING, torch.from_numpy(ids.astype(np.int64)), dYe, g_ref, "embedding table")
+
+
+# ------------------------------------------------------------ launches near the thread count that 32 bits hold
+def _fused_equals_gradient_then_adamw(layer, n, g, dtype=torch.bfloat16):
+    """The fused call on all n elements of a tensor against AdamW on its gradient g, bit for bit, on the device."""
+    outcome = []
+    for fused in (True, False):
+        W = torch.zeros(n, dtype=dtype, device=H.DEV)
+        master, m, v = (torch.full((n,), c, device=H.DEV) for c in (0.5, 1e-3, 1e-6))
+        hp = B.hparams(step=2, **HP)
+        if fused:
+            B.chunkft_wgrad_adamw_fused(layer, 0, n, W, master, m, v, hp)
+        else:
+            B.chunkft_adamw_chunk(g, master, m, v, W, n, hp, w_dtype=B.BF16 if dtype == torch.bfloat16 else B.F32)
+        torch.cuda.synchronize()
+        outcome.append((W, master, m, v))
+    for a, b in zip(*outcome):
+        assert torch.equal(a, b)
+
+
+def test_embedding_table_of_more_rows_than_four_parts_of_a_group_can_be_launched_for():
+    """2^27 + 200 rows of one element: 2^21 + 4 groups of 64 rows, in four workgroups of 512 threads each more than
+    2^32 threads.  The gradient against a scatter of the tokens, the update against the gradient."""
+    rows, T = (1 << 27) + 200, 64
+    rng = np.random.default_rng(1234)
+    ids = torch.from_numpy(rng.integers(0, rows, size=T))
+    ids[:6] = torch.tensor([rows - 1, 0, rows - 1, rows - 70, 1 << 27, 63])
+    dY = WL.normal(rng, (T, 1), 1e-3, WL.BF16).to(H.DEV)
+    ids = ids.to(H.DEV)
+    layer = B.make_layer(B.EMBEDDING, ids, dY, rows, 1)
+    full, g = H.guarded(rows)
+    B.chunkft_chunk_wgrad(layer, 0, rows, g)
+    torch.cuda.synchronize()
+    want = torch.zeros(rows, device=H.DEV)
+    for t in range(T):                                     # in token order, as the sum is defined
+        want[ids[t]] += dY[t, 0].float()
+    assert H.guards_intact(full) and torch.equal(g, want)
+    _fused_equals_gradient_then_adamw(layer, rows, g)
