@@ -67,6 +67,9 @@ bool takes_small_tiles(int64_t in, int64_t T, int64_t begin, int64_t end, int co
 
 // A kernel launch counts its threads in 32 bits.
 constexpr int64_t kMaxLaunchThreads = 0xffffffff;
+// Longest run of elements, from anywhere in a row, whose BM x BN tiles times S slabs a launch of `threads` threads a
+// tile can count; 0 if one row is too many.
+int64_t countable_run(int64_t in, int32_t S, int64_t bm, int64_t bn, int threads);
 // Into how many workgroups of kEmbedThreads threads a row group of the embedding gradient goes (1 or 4; 0: the launch cannot count them).
 constexpr int kEmbedThreads = 512;
 int embed_parts(bool update, int64_t groups, int compute_units);

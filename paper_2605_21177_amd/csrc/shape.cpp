@@ -129,6 +129,12 @@ bool fused_takes_large_tile(const WgradProblem& p, int compute_units) {
   return round_ratio * round_cost(w) / (round_cost(2.0 * w) / 2.0) < 0.99;
 }
 
+int64_t countable_run(int64_t in, int32_t S, int64_t bm, int64_t bn, int threads) {
+  const int64_t tiles = kMaxLaunchThreads / threads / 8 * 8 / S;             // the grid is a multiple of the 8 XCDs
+  const int64_t rows = tiles / ceil_div(in, bn) * bm - 8;      // a run of whole rows touches one more; the first tile may begin 7 earlier
+  return rows <= 0 ? 0 : rows <= INT64_MAX / in ? rows * in : INT64_MAX;
+}
+
 // A row group as one workgroup or as four.  The update takes four: a part of 16 rows evens out the device, and what it
 // repeats (the pass over the ids) is little beside 26 bytes per element.  The gradient alone takes one where the row
 // groups already give every compute unit more than four.  One / four parts, in us, 4096 tokens: 128 Mi elements of a

@@ -336,7 +336,13 @@ int launch_mode(const TileGrid& q, hipStream_t st) {
 template <class C>
 int launch_cfg(const WgradProblem& p, int mode, const Sinks& s, hipStream_t st) {
   TileGrid q;
-  if (!fill_grid<C::BM, C::BN>(q, p, s, C::ROW_STEP)) return (int)hipErrorInvalidValue;
+  if (!fill_grid<C::BM, C::BN>(q, p, s, C::ROW_STEP) || (int64_t)(q.n_items + 7) / 8 * 8 * C::NT > kMaxLaunchThreads) {
+    // more tiles than a launch can count: narrow layers of very many rows (128 Mi rows of up to 32 columns in 32 x 32
+    // tiles of 1024 threads) go in pieces
+    const int64_t most = countable_run(p.in, p.S, C::BM, C::BN, C::NT);
+    if (most >= p.end - p.begin) return (int)hipErrorInvalidValue;
+    return in_pieces(p, s, most, [&](const WgradProblem& piece, const Sinks& to) { return launch_cfg<C>(piece, mode, to, st); });
+  }
   switch (mode) {
     case EMIT_STORE: return launch_mode<C, EMIT_STORE>(q, st);
     case EMIT_ACCUM: return launch_mode<C, EMIT_ACCUM>(q, st);

@@ -152,6 +152,25 @@ bool embed_parts_ok() {
   return true;
 }
 
+// A run of countable_run() elements from the last column of a row, its first tile beginning up to 7 rows earlier, fits a launch.
+bool countable_runs_ok(std::mt19937_64& rng) {
+  for (int it = 0; it < 200000; ++it) {
+    const int64_t in = 1 + (int64_t)(rng() >> (rng() % 64 < 20 ? 44 : 58 - rng() % 10)), bm = 32 << (rng() % 3), bn = 32 << (rng() % 4);
+    const int32_t S = rng() % 2 ? 1 : 1 + (int32_t)(rng() % 64);
+    const int threads = 256 << (rng() % 3);
+    const int64_t run = chunkft::countable_run(in, S, bm, bn, threads);
+    if (run < 0 || run % in != 0) { printf("run %ld of %ld-wide rows\n", (long)run, (long)in); return false; }
+    if (run == 0) continue;
+    const int64_t rows = run / in + (in > 1 ? 1 : 0) + 7, tiles = (rows + bm - 1) / bm * ((in + bn - 1) / bn);
+    if ((tiles * S + 7) / 8 * 8 * threads > chunkft::kMaxLaunchThreads) {
+      printf("%ld elements of %ld-wide rows in %ld x %ld tiles, %d slabs, %d threads: %ld tiles\n", (long)run, (long)in, (long)bm, (long)bn, S, threads,
+             (long)tiles);
+      return false;
+    }
+  }
+  return chunkft::countable_run(1, 1, 32, 32, 1024) < ((int64_t)1 << 27) && chunkft::countable_run(4096, 1, 32, 64, 256) > ((int64_t)1 << 34);
+}
+
 int main() {
   if (!embed_parts_ok()) return 1;
   // slabs of 32 and 64 tokens in loads of 8 are the kernel's; token strides up to the largest of the path (64 tokens below 4 GiB)
@@ -161,7 +180,7 @@ int main() {
         for (const unsigned column : {0u, 4080u})
           if (!slab_offsets_ok(slab, tokens, column, token_bytes)) return 1;
   std::mt19937_64 rule_rng(77);
-  if (!tile_rule_ok(rule_rng)) return 1;
+  if (!tile_rule_ok(rule_rng) || !countable_runs_ok(rule_rng)) return 1;
   std::mt19937_64 rng(1234);
   long plans = 0, calls = 0, accepted = 0;
   // ---- planner, plan summary, schedule

@@ -504,3 +504,21 @@ def test_embedding_table_of_more_rows_than_four_parts_of_a_group_can_be_launched
         want[ids[t]] += dY[t, 0].float()
     assert H.guards_intact(full) and torch.equal(g, want)
     _fused_equals_gradient_then_adamw(layer, rows, g)
+
+
+def test_fp32_layer_of_more_narrow_rows_than_one_launch_takes():
+    """2^27 + 1000 rows of one fp32 element: in 32 x 32 tiles of 1024 threads more than 2^32 threads.  One token, a
+    product; two, a sum of two products; both exact to a rounding each; the update against the gradient."""
+    rows = (1 << 27) + 1000
+    gen = torch.Generator(device=H.DEV).manual_seed(55)
+    for T in (1, 2):
+        X = torch.randn(T, 1, generator=gen, device=H.DEV)
+        dY = torch.randn(T, rows, generator=gen, device=H.DEV)
+        layer = B.make_layer(B.LINEAR, X, dY, rows, 1)
+        full, g = H.guarded(rows)
+        B.chunkft_chunk_wgrad(layer, 0, rows, g)
+        torch.cuda.synchronize()
+        want = (dY.double() * X.double()).sum(0)
+        size = (dY.double() * X.double()).abs().sum(0)
+        assert H.guards_intact(full) and bool(((g.double() - want).abs() <= 2.0 ** -23 * size).all())
+        _fused_equals_gradient_then_adamw(layer, rows, g, torch.float32)
