@@ -1798,8 +1798,11 @@ int launch_wgrad_simt(const WgradProblem& p, int dtype, int mode, const Sinks& s
 
 template <typename T, int NORM, int CB>
 static int launch_colsum_cb(const WgradProblem& p, int mode, const Sinks& s, const float* stats, hipStream_t st) {
+  // vectors of more blocks than a launch can count (2^27 fp32 or 2^28 bf16 elements) go in pieces
+  constexpr int64_t most = kMaxLaunchThreads / kColsumThreads<T, CB> / 8 * 8 * CB;
+  if (p.end - p.begin > most)
+    return in_pieces(p, s, most, [&](const WgradProblem& q, const Sinks& to) { return launch_colsum_cb<T, NORM, CB>(q, mode, to, stats, st); });
   const int64_t blocks = ceil_div(p.end - p.begin, CB);
-  if (blocks > 0x7ffffff0) return (int)hipErrorInvalidValue;
   const dim3 grid((unsigned)((blocks + 7) / 8 * 8)), threads((kColsumThreads<T, CB>));
   const int n = (int)blocks;
   switch (mode) {

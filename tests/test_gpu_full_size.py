@@ -522,3 +522,25 @@ def test_fp32_layer_of_more_narrow_rows_than_one_launch_takes():
         size = (dY.double() * X.double()).abs().sum(0)
         assert H.guards_intact(full) and bool(((g.double() - want).abs() <= 2.0 ** -23 * size).all())
         _fused_equals_gradient_then_adamw(layer, rows, g, torch.float32)
+
+
+@pytest.mark.parametrize("dtype,n", [(torch.float32, (1 << 27) + 77), (torch.bfloat16, (1 << 28) + 77)])
+def test_scale_vector_of_more_blocks_than_one_launch_takes(dtype, n):
+    """One block of 1024 threads takes 32 fp32 or 64 bf16 elements: 2^27 (2^28) elements are 2^32 threads."""
+    gen = torch.Generator(device=H.DEV).manual_seed(56)
+    T = 3
+    X = torch.randn(T, n, generator=gen, device=H.DEV, dtype=dtype)
+    dY = torch.randn(T, n, generator=gen, device=H.DEV, dtype=dtype)
+    layer = B.make_layer(B.VECTOR, X, dY, 1, n)
+    full, g = H.guarded(n)
+    B.chunkft_chunk_wgrad(layer, 0, n, g)
+    torch.cuda.synchronize()
+    want, size = torch.zeros(n, dtype=torch.float64, device=H.DEV), torch.zeros(n, dtype=torch.float64, device=H.DEV)
+    for t in range(T):
+        prod = X[t].double() * dY[t].double()
+        want += prod
+        size += prod.abs_()
+    # three products, each rounded at most once, and their sum
+    assert H.guards_intact(full) and bool(((g.double() - want).abs() <= 3 * 2.0 ** -23 * size).all())
+    del want, size, prod
+    _fused_equals_gradient_then_adamw(layer, n, g, dtype)
