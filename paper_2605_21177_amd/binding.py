@@ -281,17 +281,17 @@ def make_layer(kind: int, X, dY, out: int, n_in: int, split_k: int = 0, norm_eps
     if not (X.is_cuda and dY.is_cuda):
         raise ValueError("X and dY must live on the GPU")
     d = _torch_dtype_code(dY)
-    x_strides, tokens = X.stride(), X.shape[0]
+    x_strides = X.stride()
     if kind == EMBEDDING:
-        if len(x_strides) != 1 or X.dtype is not _torch.int64 or x_strides[0] != 1 or tokens != dY.shape[0]:
+        if len(x_strides) != 1 or X.dtype is not _torch.int64 or x_strides[0] != 1 or X.shape[0] != dY.shape[0]:
             raise ValueError("token ids must be a contiguous 1-D int64 tensor with one id per row of dY")
-        return Layer(kind, d, out, n_in, tokens, X.data_ptr(), 1, dY.data_ptr(), dy_strides[0], split_k, 0, 0.0)
+        return Layer(kind, d, out, n_in, X.shape[0], X.data_ptr(), 1, dY.data_ptr(), dy_strides[0], split_k, 0, 0.0)
     if len(x_strides) != 2 or x_strides[1] != 1:
         raise ValueError("X must be 2-D with unit inner stride")
     if X.dtype is not dY.dtype:
         raise TypeError("X and dY must share a dtype")
-    return Layer(kind, d, out, n_in, tokens, X.data_ptr(), x_strides[0], dY.data_ptr(), dy_strides[0],
-                 split_k, 0, norm_eps)
+    return Layer(kind, d, out, n_in, X.shape[0], X.data_ptr(), x_strides[0], dY.data_ptr(), dy_strides[0],
+                 split_k, 0, float(norm_eps))
 
 
 def chunk_array(n: int, begin: int, device="cuda", fill=None):

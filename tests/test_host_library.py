@@ -485,6 +485,40 @@ def test_plan_counts_astronomic_chunk_numbers_at_once():
     assert ns.value == -(-(1 << 60) // 50) + 1
 
 
+class _OnDevice:
+    """A host tensor that says it is on the GPU: what make_layer looks at, without one."""
+
+    is_cuda = True
+
+    def __init__(self, t):
+        self.t = t
+
+    def __getattr__(self, name):
+        return getattr(self.t, name)
+
+
+def test_make_layer_refuses_operands_of_the_wrong_rank_or_type_and_converts_eps():
+    import torch
+    dY = _OnDevice(torch.zeros(5, 8))
+    for X in (torch.zeros(()), torch.zeros(8), torch.zeros(5, 4, 2), torch.zeros(5, 16)[:, ::2]):
+        with pytest.raises(ValueError):
+            B.make_layer(B.LINEAR, _OnDevice(X), dY, 8, 8)
+    for ids in (torch.zeros((), dtype=torch.int64), torch.zeros(5, 1, dtype=torch.int64), torch.zeros(4, dtype=torch.int64),
+                torch.zeros(5, dtype=torch.int32), torch.zeros(10, dtype=torch.int64)[::2]):
+        with pytest.raises(ValueError):
+            B.make_layer(B.EMBEDDING, _OnDevice(ids), dY, 8, 8)
+    for bad in (torch.zeros(()), torch.zeros(8), torch.zeros(5, 16)[:, ::2]):
+        with pytest.raises(ValueError):
+            B.make_layer(B.LINEAR, _OnDevice(torch.zeros(5, 8)), _OnDevice(bad), 8, 8)
+    with pytest.raises(ValueError):
+        B.make_layer(B.LINEAR, torch.zeros(5, 8), dY, 8, 8)
+    with pytest.raises(TypeError):
+        B.make_layer(B.LINEAR, _OnDevice(torch.zeros(5, 8, dtype=torch.bfloat16)), dY, 8, 8)
+    for eps in ("1e-5", np.float32(1e-5), torch.tensor(1e-5), 1e-5):
+        layer = B.make_layer(B.RMSNORM, _OnDevice(torch.zeros(5, 8)), dY, 1, 8, norm_eps=eps)
+        assert abs(layer.norm_eps - 1e-5) < 1e-11 and layer.T == 5 and layer.ldx == 8
+
+
 def test_host_code_under_address_and_undefined_behaviour_sanitizers(tmp_path):
     """plan.cpp, api.cpp and shape.cpp built for the CPU with -fsanitize=address,undefined and driven
     by tests/host_sanitize.cpp: random plans (count-then-fill, coverage, budgets near int64), plan
