@@ -252,12 +252,14 @@ def chunkft_plan_stats(chunks: Sequence[Tuple[int, int, int, int]], resident_byt
 
 # ---------------------------------------------------------- device calls
 _torch = None         # torch, imported by the first device call (the planner works without it)
+_raw_stream = None    # device index -> hipStream_t of its current stream, where this torch has such a function
 
 
 def _torch_module():
-    global _torch
+    global _torch, _raw_stream
     if _torch is None:
         import torch
+        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
         _torch = torch
     return _torch
 
@@ -325,12 +327,14 @@ def chunk_state(n: int, begin: int, device="cuda", count: int = 3):
 
 
 def _stream_ptr(stream) -> int:
-    """The hipStream_t of `stream`, or of the current device's current stream.  The raw handle is asked for: a
-    Stream object built for it costs 3 us, as much as the launch itself."""
+    """The hipStream_t of `stream`, or of the current device's current stream.  The raw handle is asked for where
+    torch has the (private) function for it: a Stream object built for it costs 3 us, as much as the launch itself."""
     if stream is not None:
         return stream.cuda_stream
     torch = _torch or _torch_module()
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _ptr(t) -> Optional[int]:

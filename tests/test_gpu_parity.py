@@ -950,6 +950,21 @@ def test_rotating_schedule_trajectory():
         assert np.abs(bits - ref).max() <= 1
 
 
+def test_calls_go_to_the_current_stream_with_and_without_the_raw_handle(monkeypatch):
+    """Without a stream argument the handle is that of torch's current stream, also where torch has no function for the
+    raw one."""
+    side = torch.cuda.Stream()
+    B.lib()
+    for raw in (True, False):
+        B._torch_module()
+        if not raw:
+            monkeypatch.setattr(B, "_raw_stream", None)
+        assert B._stream_ptr(None) == torch.cuda.current_stream().cuda_stream
+        with torch.cuda.stream(side):
+            assert B._stream_ptr(None) == side.cuda_stream
+        assert B._stream_ptr(side) == side.cuda_stream
+
+
 def test_calls_replay_from_a_captured_graph():
     """The device entry points only enqueue kernels on the caller's stream, so a caller may
     capture them into a HIP graph.  Each replay (with fresh inputs written in place and eager
