@@ -70,9 +70,10 @@ constexpr int64_t kMaxLaunchThreads = 0xffffffff;
 // Longest run of elements, from anywhere in a row, whose BM x BN tiles times S slabs a launch of `threads` threads a
 // tile can count; 0 if one row is too many.
 int64_t countable_run(int64_t in, int32_t S, int64_t bm, int64_t bn, int threads);
-// Into how many workgroups of kEmbedThreads threads a row group of the embedding gradient goes (1 or 4; 0: the launch cannot count them).
+// Into how many workgroups of kEmbedThreads threads a row group of the embedding gradient goes (1 or 4; 0: the launch cannot
+// count them).  groups: row groups times column blocks; T tokens, a table of rows x in.
 constexpr int kEmbedThreads = 512;
-int embed_parts(bool update, int64_t groups, int compute_units);
+int embed_parts(bool update, int64_t groups, int64_t rows, int64_t in, int64_t T, int compute_units);
 
 // Tile of the plain MFMA gradient, and of calls off its path: what the token split is chosen from.
 constexpr int64_t kMainTileM = 256, kMainTileN = 256, kMainTileK = 32;

@@ -1333,6 +1333,7 @@ constexpr int kEmbRows = 64;       // rows of a group
 constexpr int kEmbIter = 4;        // 256-column pieces per workgroup
 constexpr int kEmbTok = 8192;      // most tokens per call (their list lives in LDS)
 constexpr int kEmbHot = 32;        // hits from which a row is summed by all waves together
+static_assert(kEmbRows == 64, "a row is a bit of a ballot");
 static_assert(64 * kEmbWaves == kEmbedThreads, "embed_parts counts the threads of a launch");
 
 template <typename T> __device__ __forceinline__ void load4_as_f32(const T* p, int valid, float (&o)[4]);
@@ -1454,10 +1455,18 @@ __global__ __launch_bounds__(64 * kEmbWaves) void embed_wgrad_kernel(const Wgrad
     else if (pending == 1) add_tokens(into, IntC<1>{}, q0, 0, 0, 0);
   };
 
-  for (int i = threadIdx.x; i < kEmbRows; i += 64 * kEmbWaves) hits_of[i] = 0;
-  __syncthreads();
-  for (int j = threadIdx.x; j < len; j += 64 * kEmbWaves) atomicAdd(&hits_of[list[j] & 63], 1);
-  __syncthreads();
+  // which rows of the group have hits, and very many: a bit each, the same in every wave (a look at a row's count in
+  // LDS where it is asked for was a latency per row and pass: 3 us a workgroup, as much as all its work on a narrow table)
+  unsigned long long named = 0, hot = 0;
+  if (len > 0) {                                            // the same for every thread
+    for (int i = threadIdx.x; i < kEmbRows; i += 64 * kEmbWaves) hits_of[i] = 0;
+    __syncthreads();
+    for (int j = threadIdx.x; j < len; j += 64 * kEmbWaves) atomicAdd(&hits_of[list[j] & 63], 1);
+    __syncthreads();
+    const int hits = hits_of[lane];
+    named = __ballot(hits > 0);
+    hot = __ballot(hits >= kEmbHot);
+  }
 
   // One row of the part: where its pieces go, their state requested; and the update from the sums in `acc`.
   struct Row {
@@ -1499,8 +1508,9 @@ __global__ __launch_bounds__(64 * kEmbWaves) void embed_wgrad_kernel(const Wgrad
   };
 
   // ---- rows with very many hits: summed by all waves together, updated by one of them
-  for (int local = part_id * kPartRows; local < (part_id + 1) * kPartRows; ++local) {
-    if (hits_of[local] < kEmbHot) continue;                 // the same for every thread
+  constexpr unsigned long long kPartMask = kPartRows == 64 ? ~0ull : (1ull << kPartRows) - 1ull;
+  for (unsigned long long left = hot & (kPartMask << (part_id * kPartRows)); left != 0; left &= left - 1) {
+    const int local = __builtin_ctzll(left);
     float acc[kEmbIter][4];
 #pragma unroll
     for (int i = 0; i < kEmbIter; ++i)
@@ -1532,7 +1542,8 @@ __global__ __launch_bounds__(64 * kEmbWaves) void embed_wgrad_kernel(const Wgrad
     const int local = part_id * kPartRows + sub * kEmbWaves + wave;     // consecutive rows go to different waves
     const int64_t row = row_base + local;
     if (row > row_last) break;
-    if (hits_of[local] >= kEmbHot || (MODE == EMIT_ACCUM && hits_of[local] == 0)) continue;
+    const bool is_named = (named >> local & 1) != 0;
+    if ((hot >> local & 1) != 0 || (MODE == EMIT_ACCUM && !is_named)) continue;
     float acc[kEmbIter][4];
 #pragma unroll
     for (int i = 0; i < kEmbIter; ++i)
@@ -1540,7 +1551,7 @@ __global__ __launch_bounds__(64 * kEmbWaves) void embed_wgrad_kernel(const Wgrad
       for (int e = 0; e < 4; ++e) acc[i][e] = 0.f;
     Row w;
     request(w, row);                                        // travels while the hit list is walked
-    if (hits_of[local] > 0) gather(acc, local, [](int) { return true; });
+    if (is_named) gather(acc, local, [](int) { return true; });
     finish(w, row, acc);
   }
 }
@@ -1855,7 +1866,7 @@ int launch_norm_wgrad(const WgradProblem& p, int dtype, bool subtract_mean, floa
 template <typename T, int MODE>
 static int launch_embed_mode(const WgradProblem& p, int64_t groups, const Sinks& s, hipStream_t st) {
   const dim3 threads(64 * kEmbWaves);
-  const int parts = embed_parts(MODE == EMIT_ADAMW, groups, device_compute_units());
+  const int parts = embed_parts(MODE == EMIT_ADAMW, groups, p.out, p.in, p.T, device_compute_units());
   if (parts == 1) hipLaunchKernelGGL((embed_wgrad_kernel<T, MODE, 1>), dim3((unsigned)groups), threads, 0, st, p, s);
   else if (parts == 4) hipLaunchKernelGGL((embed_wgrad_kernel<T, MODE, 4>), dim3((unsigned)groups * 4), threads, 0, st, p, s);
   else return (int)hipErrorInvalidValue;

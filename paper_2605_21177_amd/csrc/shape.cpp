@@ -135,16 +135,25 @@ int64_t countable_run(int64_t in, int32_t S, int64_t bm, int64_t bn, int threads
   return rows <= 0 ? 0 : rows <= INT64_MAX / in ? rows * in : INT64_MAX;
 }
 
-// A row group as one workgroup or as four.  The update takes four: a part of 16 rows evens out the device, and what it
-// repeats (the pass over the ids) is little beside 26 bytes per element.  The gradient alone takes one where the row
-// groups already give every compute unit more than four.  One / four parts, in us, 4096 tokens: 128 Mi elements of a
-// 128256 x 4096 table, updated 695 / 635, written 210 / 263, added to 94 / 183; 32 Mi of 32000 x 4096 207 / 168, 125 / 68,
-// 79 / 60; 4000 x 8192 435 / 187, 362 / 170, 366 / 169.  (Two parts: 724, 180 and 247 updated.)  Where a launch cannot
-// count the threads of four parts (2^21 row groups, 128 Mi narrow rows) it is one; the sums are the same either way.
-int embed_parts(bool update, int64_t groups, int compute_units) {
+// A row group as one workgroup or as four.  A part of 16 rows evens out the device and spreads the rows that many tokens
+// name; what it repeats is the pass over the ids.  Times in us, one / four parts, of the update, the gradient, the gradient
+// added to g; ids heavy-tailed as in text unless said otherwise:
+//   The update takes four from 448 columns on, where 26 bytes per element outweigh the pass: 128 Mi elements of 128256 x
+//   4096, 4096 tokens 665 / 631; 50257 x 768 227 / 199; 300000 rows, 64 and 4096 uniform ids: 512 wide 510 / 463 and 510 /
+//   473, 448 wide 448 / 390 and 445 / 429, 384 wide 554 / 517 and 563 / 600, 320 wide 463 / 460 and 481 / 572, 93 wide 264 / 326.
+//   Any call takes four when one would leave compute units without a group: 8000 x 512 (125 groups) 53 / 45, 42 / 36,
+//   33 / 35; 2000 x 64, 8192 tokens 31 / 15, 27 / 14, 28 / 14; 300 x 4096, 8192 tokens 653 / 311, 612 / 304, 628 / 308.
+//   The gradient also where two groups a compute unit meet eight or more tokens each: 32 Mi of 32000 x 4096 111 / 67, 77 / 48;
+//   4000 x 8192 340 / 162, 345 / 163; 32000 x 1024 107 / 85, 64 / 62 (uniform ids 36 / 57, 28 / 50).  Else one: 128 Mi of 128256 x
+//   4096 179 / 244, 64 / 140; 50257 x 768 65 / 90, 41 / 72; 111484 x 1137, 4 tokens 19 / 26, 6 / 9.
+// Where a launch cannot count the threads of four parts (2^21 row groups, 128 Mi narrow rows) it is one; the sums are the
+// same either way.
+int embed_parts(bool update, int64_t groups, int64_t rows, int64_t in, int64_t T, int compute_units) {
   const int64_t cus = compute_units > 0 ? compute_units : kDefaultComputeUnits, most = kMaxLaunchThreads / kEmbedThreads;
   if (groups > most) return 0;
-  return (!update && groups > 4 * cus) || groups > most / 4 ? 1 : 4;
+  if (groups > most / 4) return 1;
+  if (groups <= cus) return 4;
+  return update ? (in >= 448 ? 4 : 1) : groups <= cus * 9 / 4 && T >= rows / 8 ? 4 : 1;
 }
 
 Split pick_split(int32_t kind, int32_t dtype, int64_t out, int64_t in, int64_t T, int64_t begin,

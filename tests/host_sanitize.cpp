@@ -138,17 +138,26 @@ bool tile_rule_ok(std::mt19937_64& rng) {
   return true;
 }
 
-// The embedding gradient takes every number of row groups that a launch can count, in one part at least; never more.
+// The embedding gradient takes every number of row groups that a launch can count, in one part at least; never more.  Narrow
+// tables of many groups are updated in one part, sparse gradients of many groups taken in one.
 bool embed_parts_ok() {
   const int64_t most = chunkft::kMaxLaunchThreads / chunkft::kEmbedThreads;
   for (const bool update : {false, true})
     for (const int64_t groups : {(int64_t)1, (int64_t)1024, (int64_t)1025, most / 4 - 1, most / 4, most / 4 + 1, most - 1, most, most + 1, most * 2}) {
-      const int parts = chunkft::embed_parts(update, groups, 256);
+      const int parts = chunkft::embed_parts(update, groups, 64 * groups, 1024, 8192, 256);
       if ((parts != 0) != (groups <= most) || groups * parts * chunkft::kEmbedThreads > chunkft::kMaxLaunchThreads) {
         printf("embedding: %ld row groups in %d parts\n", (long)groups, parts);
         return false;
       }
     }
+  const auto parts = [](bool update, int64_t rows, int64_t in, int64_t T) {
+    return chunkft::embed_parts(update, (rows + 63) / 64 * ((in + 1023) / 1024), rows, in, T, 256);
+  };
+  if (parts(true, 400000, 176, 1) != 1 || parts(false, 29000, 1137, 4) != 1 || parts(false, 128256, 4096, 4096) != 1 ||
+      parts(true, 128256, 4096, 4096) != 4 || parts(false, 4000, 8192, 4096) != 4 || parts(true, 8000, 64, 16) != 4) {
+    printf("embedding: parts of a row group\n");
+    return false;
+  }
   return true;
 }
 

@@ -549,7 +549,9 @@ def test_embedding_kind(dtype):
 # Token counts around the runs of whole 64s that the eight waves take; neighbouring rows that very many tokens name (31
 # to 33 of them: on either side of the shared sum), one of them the first and the last row of the range.
 @pytest.mark.parametrize("rows,width,T", [(70, 264, 1), (70, 264, 63), (130, 40, 65), (200, 1032, 511), (65, 1028, 513),
-                                          (300, 24, 1025), (129, 264, 8191), (64, 264, 8192)])
+                                          (300, 24, 1025), (129, 264, 8191), (64, 264, 8192),
+                                          # more groups than compute units: updated in one part, the gradient in one and in four
+                                          (20000, 24, 700), (20000, 24, 3000)])
 def test_embedding_runs_and_neighbouring_hot_rows(rows, width, T):
     rng = np.random.default_rng(rows + T)
     for dtype in (WL.BF16, WL.F32):
