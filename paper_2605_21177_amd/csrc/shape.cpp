@@ -169,12 +169,16 @@ Split pick_split(int32_t kind, int32_t dtype, int64_t out, int64_t in, int64_t T
     // bytes per element and slab at 5 TB/s.  The cheapest S up to 8 with at least 512 tokens per slab is within
     // 15 % of the best of 1 - 32 slabs in 30 measured cases (16 - 576 tiles, 1024 - 8192 tokens), e.g. 80 tiles,
     // 4096 tokens: 16 us with 5 or 6 slabs against 27 with one; 272 tiles, 2048 tokens: 19 with one, 21 with two.
+    // In a long slab it needs 0.27 us per 32 (one slab, 256 tiles: 14 us at 2100 tokens, 16 at 2500, 26 at 3000, 34 at 4096; with rows
+    // that are not whole 128-byte lines 20, 25, 30): the fused call on 260 tiles at 3000 tokens takes 34 us with one slab, 27
+    // with two, 30 on the large tiles.
     const double tiles = (double)small_tiles(in, begin, end), elems = (double)(end - begin);
     const double room = 1.6 * (compute_units > 0 ? compute_units : kDefaultComputeUnits);
+    const int64_t long_slab = in % 64 == 0 ? 2688 : 2304;
     double best = 0.0;
     for (int64_t k = 1; k <= 8 && (k == 1 || T / k >= 512); ++k) {
-      const double crowd = tiles * (double)k / room;
-      const double cost = 0.2 * (double)T / 32.0 / (double)k * (crowd > 1.0 ? crowd : 1.0) +
+      const double crowd = tiles * (double)k / room, per32 = tiles <= room && T / k > long_slab ? 0.27 : 0.2;
+      const double cost = per32 * (double)T / 32.0 / (double)k * (crowd > 1.0 ? crowd : 1.0) +
                           (k > 1 ? 4.0 + (double)k * elems * 8.0 / 5e6 : 0.0);
       if (k == 1 || cost < best) {
         best = cost;

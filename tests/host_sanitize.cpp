@@ -180,6 +180,27 @@ bool countable_runs_ok(std::mt19937_64& rng) {
   return chunkft::countable_run(1, 1, 32, 32, 1024) < ((int64_t)1 << 27) && chunkft::countable_run(4096, 1, 32, 64, 256) > ((int64_t)1 << 34);
 }
 
+// The split that the small tiles' cost picks: long slabs are cut where that pays, and its partial sums always fit the library's
+// static workspace.
+bool small_splits_ok(std::mt19937_64& rng) {
+  const auto split = [](int64_t rows, int64_t in, int64_t T) { return chunkft::pick_split(0, 1, rows, in, T, 0, rows * in, 0, true, 256).S; };
+  if (split(256, 4104, 3000) != 2 || split(1000, 1000, 2500) != 2 || split(256, 4096, 3000) != 2 || split(256, 4096, 2500) != 1 || split(256, 4096, 1024) != 1) {
+    printf("slabs of the small tiles\n");
+    return false;
+  }
+  for (int it = 0; it < 100000; ++it) {
+    const int64_t in = 8 * (1 + (int64_t)(rng() >> (rng() % 2 ? 54 : 46))), rows = 1 + (int64_t)(rng() % (rng() % 2 ? 150 : 4000)), T = 1 + (int64_t)(rng() % 20000);
+    const int64_t begin = rng() % 2 ? 0 : (int64_t)(rng() % (uint64_t)in), end = rows * in;
+    if (!chunkft::takes_small_tiles(in, T, begin, end, 256)) continue;
+    const chunkft::Split s = chunkft::pick_split(0, 1, rows, in, T, begin, end, 0, true, 256);
+    if (s.S > 1 && (int64_t)s.S * (end - begin + 32) * 4 > (int64_t)CHUNKFT_STATIC_WORKSPACE_BYTES) {
+      printf("%ld x %ld, %ld tokens: %d slabs\n", (long)rows, (long)in, (long)T, s.S);
+      return false;
+    }
+  }
+  return true;
+}
+
 int main() {
   if (!embed_parts_ok()) return 1;
   // slabs of 32 and 64 tokens in loads of 8 are the kernel's; token strides up to the largest of the path (64 tokens below 4 GiB)
@@ -189,7 +210,7 @@ int main() {
         for (const unsigned column : {0u, 4080u})
           if (!slab_offsets_ok(slab, tokens, column, token_bytes)) return 1;
   std::mt19937_64 rule_rng(77);
-  if (!tile_rule_ok(rule_rng) || !countable_runs_ok(rule_rng)) return 1;
+  if (!tile_rule_ok(rule_rng) || !countable_runs_ok(rule_rng) || !small_splits_ok(rule_rng)) return 1;
   std::mt19937_64 rng(1234);
   long plans = 0, calls = 0, accepted = 0;
   // ---- planner, plan summary, schedule
