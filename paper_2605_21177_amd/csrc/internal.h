@@ -75,6 +75,9 @@ int64_t countable_run(int64_t in, int32_t S, int64_t bm, int64_t bn, int threads
 constexpr int kEmbedThreads = 512;
 int embed_parts(bool update, int64_t groups, int64_t rows, int64_t in, int64_t T, int compute_units);
 
+// A gradient by itself (store, add, partial sums) leaves the small tiles where one round does not hold them.
+bool plain_leaves_small_tiles(const WgradProblem& p, int compute_units);
+
 // Tile of the plain MFMA gradient, and of calls off its path: what the token split is chosen from.
 constexpr int64_t kMainTileM = 256, kMainTileN = 256, kMainTileK = 32;
 constexpr int64_t kSimtTileM = 64, kSimtTileN = 64, kSimtTileK = 16;

@@ -1741,7 +1741,9 @@ int launch_mfma_cfg(const WgradProblem& p, int mode, const Sinks& s, hipStream_t
 }
 
 int launch_wgrad_bf16_mfma(const WgradProblem& p, int mode, const Sinks& s, void* stream) {
-  if (takes_small_tiles(p.in, p.T, p.begin, p.end, device_compute_units())) return launch_wgrad_small(p, mode, s, stream);
+  if (takes_small_tiles(p.in, p.T, p.begin, p.end, device_compute_units()) &&
+      (mode == EMIT_ADAMW || !plain_leaves_small_tiles(p, device_compute_units())))
+    return launch_wgrad_small(p, mode, s, stream);
   // The plain gradient (short epilogue) is a little faster on the large tile; the fused call,
   // whose epilogue moves 26 bytes per element, gains from two workgroups per compute unit.
   if (mode == EMIT_ADAMW) {

@@ -76,6 +76,21 @@ bool takes_small_tiles(int64_t in, int64_t T, int64_t begin, int64_t end, int co
   return tiles <= cus * 43 / 10 && tiles * T <= cus * (body <= 64 ? 8600 : 4300);
 }
 
+// Four small tiles share a compute unit; the gradient has nothing but its loop to run under a fifth one's.  Small tiles against the
+// large ones, gradient in us (the fused call, whose update does run under it, gains to the end of the line): 1050 tiles of 280 x
+// 13408 200 tokens 11.4 - 11.6, 436 tokens 15.6 - 13.9, 1000 tokens 26 - 19 (fused 40 - 43); 1088 of 1032 x 4096 436 tokens
+// 14.6 - 14.2, 1000 tokens 25 - 19; 1024 of 1024 x 4096 700 tokens 14.2 - 15.8, 1000 tokens 17.8 - 18.9.  Rows that are not whole
+// 128-byte lines get there a little earlier: 968 of 1400 x 2800 436 tokens 13.3 - 14.1, 1000 tokens 22 - 19; 768 of 1024 x 3016
+// 1400 tokens 20 - 22.
+bool plain_leaves_small_tiles(const WgradProblem& p, int compute_units) {
+  const int64_t cus = compute_units > 0 ? compute_units : kDefaultComputeUnits;
+  const RowSplit rs = split_rows(p);
+  if (rs.rb1 <= rs.rb0 || !(edge_rows_folded(rs) || (rs.lead_base < 0 && rs.trail_row < 0))) return false;   // only they can take it
+  const int64_t tiles = small_tiles(p.in, p.begin, p.end), slab_tokens = p.S > 1 ? p.kslab : p.T;
+  const bool whole_lines = p.ldx % 64 == 0 && (reinterpret_cast<uintptr_t>(p.X) & 127u) == 0;
+  return (tiles > 4 * cus && slab_tokens > 256) || (!whole_lines && tiles > cus * 15 / 4 && slab_tokens > 440);
+}
+
 bool group_takes_segment(const WgradProblem& p, bool vector) {
   if (vector) return true;
   const RowSplit rs = split_rows(p);

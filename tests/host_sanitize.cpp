@@ -129,6 +129,7 @@ bool tile_rule_ok(std::mt19937_64& rng) {
     const bool small = chunkft::takes_small_tiles(p.in, p.T, p.begin, p.end, cus);
     const int64_t tiles = ((p.end - 1) / p.in - p.begin / p.in / 8 * 8 + 1 + 63) / 64 * ((p.in + 63) / 64);
     const bool beyond = tiles > cus * 43 / 10 || tiles * p.T > cus * (body <= 64 ? 8600 : 4300);
+    if (chunkft::plain_leaves_small_tiles(p, cus) && !carried) { printf("a gradient sent to a kernel that cannot carry it\n"); return false; }
     if (carried ? small == beyond : !small) {
       printf("[%ld, %ld) of %ld-wide rows, %ld tokens: body of %ld rows, %ld tiles, small tiles %d\n", (long)p.begin, (long)p.end, (long)p.in,
              (long)p.T, (long)body, (long)tiles, (int)small);
@@ -180,6 +181,19 @@ bool countable_runs_ok(std::mt19937_64& rng) {
   return chunkft::countable_run(1, 1, 32, 32, 1024) < ((int64_t)1 << 27) && chunkft::countable_run(4096, 1, 32, 64, 256) > ((int64_t)1 << 34);
 }
 
+// Gradients of more than four small tiles a compute unit go to the large ones, others stay.
+bool plain_line_ok() {
+  const auto leaves = [](int64_t rows, int64_t in, int64_t T, int64_t begin) {
+    chunkft::WgradProblem p{};
+    p.out = rows; p.in = p.ldx = in; p.lddy = rows; p.T = p.kslab = T; p.S = 1; p.begin = begin; p.end = rows * in;
+    return chunkft::plain_leaves_small_tiles(p, 256);
+  };
+  const bool ok = leaves(280, 13408, 436, 0) && leaves(280, 13408, 700, 0) && leaves(1032, 4096, 700, 0) && !leaves(1024, 4096, 1000, 0) &&
+                  !leaves(280, 13408, 200, 0) && leaves(1400, 2800, 700, 0) && !leaves(1024, 3016, 1400, 0) && !leaves(100, 70400, 1000, 8);
+  if (!ok) printf("line of the plain gradient\n");
+  return ok;
+}
+
 // The split that the small tiles' cost picks: long slabs are cut where that pays, and its partial sums always fit the library's
 // static workspace.
 bool small_splits_ok(std::mt19937_64& rng) {
@@ -210,7 +224,7 @@ int main() {
         for (const unsigned column : {0u, 4080u})
           if (!slab_offsets_ok(slab, tokens, column, token_bytes)) return 1;
   std::mt19937_64 rule_rng(77);
-  if (!tile_rule_ok(rule_rng) || !countable_runs_ok(rule_rng) || !small_splits_ok(rule_rng)) return 1;
+  if (!tile_rule_ok(rule_rng) || !countable_runs_ok(rule_rng) || !small_splits_ok(rule_rng) || !plain_line_ok()) return 1;
   std::mt19937_64 rng(1234);
   long plans = 0, calls = 0, accepted = 0;
   // ---- planner, plan summary, schedule
