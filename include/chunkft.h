@@ -245,8 +245,9 @@ size_t chunkft_workspace_bytes(const chunkft_layer* L, int64_t begin, int64_t en
  *              rstd[t] = 1 / sqrt(var[t] + eps), biased variance
  * (the paper names the last three operators without formulas; these are the
  * textbook gradients of the forms given with chunkft_kind).
- * Products and sums are fp32 (bf16 inputs are multiplied exactly); the sum
- * over tokens is taken slab by slab in a fixed order.
+ * Products and sums are fp32 (bf16 inputs are multiplied exactly; subnormal inputs
+ * and results are kept); the sum over tokens is taken slab by slab in a fixed order.
+ * LINEAR: an infinity or NaN reaches the elements whose sum contains it and no others.
  *
  * g (device, out)   end - begin floats.  accumulate = 0: overwritten;
  *                   accumulate = 1: g += result (gradient accumulation over

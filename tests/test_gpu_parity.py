@@ -392,6 +392,31 @@ def test_infinities_in_the_last_token_on_the_large_tiles(out, n_in, T, split_k, 
     _check_infinities_in_the_last_tokens(case, split_k, *((3 * n_in + 77, (out - 3) * n_in + 5) if edges else ()))
 
 
+# Subnormal operands and results are kept on every path.  A subnormal factor times 2^20 leaves products that are exact (bf16) or
+# rounded once: _full_check's fp32 bound.  A sum of T products that lies among the subnormals is off by at most half a
+# step of 2^-149 per addition and product.
+@pytest.mark.parametrize("dtype,out,n_in,T", [
+    (WL.BF16, 2400, 4096, 64), (WL.BF16, 2400, 4096, 2080), (WL.BF16, 72, 136, 100), (WL.BF16, 72, 136, 300), (WL.BF16, 137, 101, 100), (WL.BF16, 63, 200, 40),
+    (WL.BF16, 2051, 2053, 45), (WL.BF16, 2047, 2050, 1601), (WL.F32, 100, 128, 257), (WL.F32, 548, 1028, 69), (WL.F32, 33, 129, 131), (WL.F32, 547, 1027, 33)])
+def test_subnormal_operands_and_results_are_kept(dtype, out, n_in, T):
+    dt = torch.float32 if dtype == WL.F32 else torch.bfloat16
+    rows = min(out, 140)                                                # all tiles, the first rows compared
+    for x_scale, dy_scale in ((2.0 ** -131, 2.0 ** 20), (2.0 ** 20, 2.0 ** -131), (2.0 ** -64, 2.0 ** -70)):
+        gen = torch.Generator(device=H.DEV).manual_seed(out + T)
+        X = (torch.randn(T, n_in, generator=gen, device=H.DEV, dtype=torch.float64) * x_scale).to(dt)
+        dY = (torch.randn(T, out, generator=gen, device=H.DEV, dtype=torch.float64) * dy_scale).to(dt)
+        layer = B.make_layer(B.LINEAR, X, dY, out, n_in)
+        g = torch.empty(out * n_in, device=H.DEV)
+        B.chunkft_chunk_wgrad(layer, 0, out * n_in, g, ws=H.workspace_for(layer, 0, out * n_in))
+        torch.cuda.synchronize()
+        want = dY[:, :rows].double().cpu().T.matmul(X.double().cpu())
+        got = g.view(out, n_in)[:rows].double().cpu()
+        if x_scale * dy_scale < 2.0 ** -126:
+            assert float((got - want).abs().max()) <= 2 * T * 2.0 ** -150 and float((got != 0).double().mean()) > 0.99
+        else:
+            assert float((got - want).norm() / want.norm()) <= 1e-5
+
+
 def test_bf16_strided_operands():
     """Row strides larger than the row length (views into wider buffers)."""
     rng = np.random.default_rng(79)
