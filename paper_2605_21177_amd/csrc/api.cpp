@@ -122,7 +122,8 @@ int run_wgrad(const chunkft_layer* L, const Checked& c, int mode, const Sinks& s
     e = launch_norm_wgrad(c.p, L->dtype, L->kind == CHUNKFT_LAYERNORM, static_cast<float>(L->norm_eps), s.ws,
                           mode, s, stream);
   else if (c.mfma) e = launch_wgrad_bf16_mfma(c.p, mode, s, stream);
-  else e = launch_wgrad_simt(c.p, L->dtype, mode, s, stream);
+  else if (L->dtype == CHUNKFT_F32) e = launch_wgrad_f32(c.p, mode, s, stream);
+  else e = launch_wgrad_ragged(c.p, mode, s, stream);
   return e == 0 ? CHUNKFT_OK : CHUNKFT_ERR_HIP;
 }
 

@@ -78,9 +78,10 @@ int embed_parts(bool update, int64_t groups, int64_t rows, int64_t in, int64_t T
 // A gradient by itself (store, add, partial sums) leaves the small tiles where one round does not hold them.
 bool plain_leaves_small_tiles(const WgradProblem& p, int compute_units);
 
-// Tile of the plain MFMA gradient, and of calls off its path: what the token split is chosen from.
+// Tile of the plain MFMA gradient, from which the token split is chosen; slabs are whole multiples of its tokens,
+// of calls off its path (never split unless the caller asks) of 16.
 constexpr int64_t kMainTileM = 256, kMainTileN = 256, kMainTileK = 32;
-constexpr int64_t kSimtTileM = 64, kSimtTileN = 64, kSimtTileK = 16;
+constexpr int64_t kOtherTileK = 16;
 
 constexpr int kMaxDevices = 64;
 constexpr int kDefaultComputeUnits = 256;                 // MI355X
@@ -110,9 +111,7 @@ int launch_fused_group(const GroupSegment* segs, int n, bool large_tile, void* s
 
 // All launchers return a hipError_t as int (0 = success).
 int launch_wgrad_bf16_mfma(const WgradProblem& p, int mode, const Sinks& s, void* stream);
-// Matrices without 16-byte bf16 rows: fp32 ones go to launch_wgrad_f32, bf16 ones to launch_wgrad_ragged.
-int launch_wgrad_simt(const WgradProblem& p, int dtype, int mode, const Sinks& s, void* stream);
-// A bf16 matrix in 64 x 64 tiles.
+// A bf16 matrix in 64 x 64 tiles; an fp32 matrix; a bf16 matrix whose rows are not 16-byte pieces.
 int launch_wgrad_small(const WgradProblem& p, int mode, const Sinks& s, void* stream);
 int launch_wgrad_f32(const WgradProblem& p, int mode, const Sinks& s, void* stream);
 int launch_wgrad_ragged(const WgradProblem& p, int mode, const Sinks& s, void* stream);

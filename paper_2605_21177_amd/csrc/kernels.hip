@@ -1235,7 +1235,7 @@ __global__ __launch_bounds__((kColsumThreads<T, CB>)) void colsum_kernel(const W
 // ---------------------------------------------------------------------------
 // The work items of up to kGroupMax segments are laid end to end: the tiles of each bf16 matrix
 // segment (parameters as for wgrad_mfma_kernel) and, for a bf16 scale-vector segment (tiles_m = 0),
-// blocks of 64 elements.  A workgroup finds its segment by its item number and then does exactly
+// blocks of kColsumCols elements.  A workgroup finds its segment by its item number and then does exactly
 // what the single-segment kernels do, in the same order, so the results are theirs bit for bit.
 constexpr int kGroupMax = 12;
 
@@ -1779,7 +1779,7 @@ static int launch_group_cfg(const GroupSegment* segs, int n, hipStream_t st) {
         q.p = g.p;
         q.s = g.s;
         q.tiles_m = 0;
-        items += ceil_div(g.p.end - g.p.begin, 64);
+        items += ceil_div(g.p.end - g.p.begin, kColsumCols);
       } else {
         if (!fill_mfma_params<C>(g.p, EMIT_ADAMW, g.s, split_rows(g.p), q)) return (int)hipErrorInvalidValue;
         gp.stagger = q.stagger;
@@ -1803,10 +1803,6 @@ int launch_fused_group(const GroupSegment* segs, int n, bool large_tile, void* s
   if (n <= 0) return 0;
   return large_tile ? launch_group_cfg<MainCfg>(segs, n, (hipStream_t)stream)
                     : launch_group_cfg<FusedCfg>(segs, n, (hipStream_t)stream);
-}
-
-int launch_wgrad_simt(const WgradProblem& p, int dtype, int mode, const Sinks& s, void* stream) {
-  return dtype == 0 ? launch_wgrad_f32(p, mode, s, stream) : launch_wgrad_ragged(p, mode, s, stream);
 }
 
 template <typename T, int NORM, int CB>

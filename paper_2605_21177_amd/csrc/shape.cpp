@@ -175,8 +175,7 @@ Split pick_split(int32_t kind, int32_t dtype, int64_t out, int64_t in, int64_t T
                  int64_t end, int32_t forced, bool mfma, int compute_units) {
   (void)out; (void)dtype;
   if (kind != 0) return {1, T};                       // only linear layers are ever split
-  const int64_t bm = mfma ? kMainTileM : kSimtTileM, bn = mfma ? kMainTileN : kSimtTileN;
-  const int64_t bk = mfma ? kMainTileK : kSimtTileK;
+  const int64_t bk = mfma ? kMainTileK : kOtherTileK;
   int64_t S = forced;
   if (S <= 0 && mfma && takes_small_tiles(in, T, begin, end, compute_units)) {
     // Small tiles: a workgroup needs about 0.2 us per 32 tokens while no more than 1.6 of them share a
@@ -201,32 +200,29 @@ Split pick_split(int32_t kind, int32_t dtype, int64_t out, int64_t in, int64_t T
       }
     }
   }
-  if (S <= 0) {
-    int64_t rows = (end - 1) / in - begin / in + 1;
-    if (mfma) {                                       // the MFMA kernel tiles the body rows only
-      WgradProblem tmp{};
-      tmp.begin = begin;
-      tmp.end = end;
-      tmp.in = in;
-      const RowSplit rs = split_rows(tmp);
-      rows = rs.rb1 > rs.rb0 ? rs.rb1 - rs.rb0 : 1;
-    }
-    const int64_t tiles = ceil_div(rows, bm) * ceil_div(in, bn);
-    S = 1;
+  if (S <= 0 && mfma) {
+    WgradProblem tmp{};                               // the large tiles hold the body rows
+    tmp.begin = begin;
+    tmp.end = end;
+    tmp.in = in;
+    const RowSplit rs = split_rows(tmp);
+    const int64_t rows = rs.rb1 > rs.rb0 ? rs.rb1 - rs.rb0 : 1;
+    const int64_t tiles = ceil_div(rows, kMainTileM) * ceil_div(in, kMainTileN);
     const int64_t slots = compute_units > 0 ? compute_units : kDefaultComputeUnits;   // resident workgroups
-    if (mfma && tiles <= slots / 4) {
+    S = 1;
+    if (tiles <= slots / 4) {
       // Splitting pays only when the 256 x 256 tiles fill at most a quarter of the compute units.
       // A slab costs its tokens' share of the loop, every further slab 8 bytes per element of
       // partial traffic plus one more set-up and epilogue per tile: time ~ a T / S + b S tiles,
       // least at S = sqrt(a T / (b tiles)).  a / b = 1 / 12 fits the measured grid (16 - 192
       // tiles x 1024 - 8192 tokens x 1 - 16 slabs, plain and fused call, in = 4096); more than 8
       // slabs never won, and from 128 tiles on one slab is best.
-      S = 1;
       while ((S + 1) * (S + 1) * 12 * tiles <= T && S < 8) ++S;
       if (S > slots / tiles) S = slots / tiles;
       if (S > T / 256) S = T / 256 > 0 ? T / 256 : 1;    // never slabs of fewer than 256 tokens
     }
   }
+  if (S <= 0) S = 1;                                  // fp32 and ragged layers are split only on request
   int64_t kslab = ceil_div(ceil_div(T, S), bk) * bk;
   S = ceil_div(T, kslab);                             // no empty slab
   return {(int32_t)S, kslab};

@@ -2,9 +2,9 @@
 //
 // Both operands have the contraction index (the token) outermost, and that is what this instruction
 // wants: a lane holds ONE token's value of its row (column).  So there is nothing to transpose, and a wave
-// that takes TM x TN blocks gives lane l the rows TM * (l % 32) ... + TM - 1: TM consecutive floats.
+// that takes 1 x TN blocks gives lane l the columns TN * (l % 32) ... + TN - 1: TN consecutive floats.
 //
-// A workgroup is WK waves on ONE 32 TM x 32 TN tile, each taking a contiguous WK-th of the slab's tokens;
+// A workgroup is WK waves on ONE 32 x 32 TN tile, each taking a contiguous WK-th of the slab's tokens;
 // their partial tiles meet in LDS and are added in wave order while the tile leaves row by row, 16 bytes
 // per lane.  Splitting the tokens instead of the tile inside the workgroup keeps the tile small: the
 // number of tiles, and not the size of a layer, decides whether the compute units are filled and how even
@@ -21,22 +21,22 @@ namespace chunkft {
 
 namespace {
 
-template <int TM_, int TN_, int WK_>
+template <int TN_, int WK_>
 struct F32Cfg {
-  static constexpr int TM = TM_, TN = TN_, WK = WK_, BM = 32 * TM, BN = 32 * TN, NT = 64 * WK;
+  static constexpr int TN = TN_, WK = WK_, BM = 32, BN = 32 * TN, NT = 64 * WK;
   static constexpr int ROW_STEP = 1;
   static constexpr int U = 8;                       // two-token steps whose operands are loaded together
   static constexpr int PITCH = BN + 4;              // staged row: 16-byte aligned, rows shifted by 4 banks
   static constexpr size_t LDS_BYTES = (size_t)WK * BM * PITCH * 4;
 };
 
-template <int TM_, int TN_, int WK_, int NS_>
+template <int TN_, int WK_, int NS_>
 struct F32RingCfg {
-  static constexpr int TM = TM_, TN = TN_, WK = WK_, BM = 32 * TM, BN = 32 * TN, NT = 64 * WK;
+  static constexpr int TN = TN_, WK = WK_, BM = 32, BN = 32 * TN, NT = 64 * WK;
   static constexpr int ROW_STEP = 4;                // tiles begin at whole 16-byte pieces of dY
   static constexpr int KS = 8, U = KS / 2, NS = NS_;
   static constexpr int A_BYTES = KS * BM * 4, B_BYTES = KS * BN * 4, SLAB_BYTES = A_BYTES + B_BYTES;
-  static constexpr int L = TM + TN;                 // 1 KB loads per slab
+  static constexpr int L = 1 + TN;                  // 1 KB loads per slab
   static constexpr int PITCH = BN + 4;
   static constexpr size_t STAGE_BYTES = (size_t)WK * BM * PITCH * 4, RING_BYTES = (size_t)WK * NS * SLAB_BYTES;
   static constexpr size_t LDS_BYTES = STAGE_BYTES > RING_BYTES ? STAGE_BYTES : RING_BYTES;
@@ -52,38 +52,31 @@ __device__ __forceinline__ float element(float v, int) { return v; }
 template <class V> __device__ __forceinline__ float element(V v, int i) { return v[i]; }
 
 template <class C>
-__device__ __forceinline__ void clear(f32x16 (&acc)[C::TM][C::TN]) {
+__device__ __forceinline__ void clear(f32x16 (&acc)[C::TN]) {
 #pragma unroll
-  for (int i = 0; i < C::TM; ++i)
+  for (int j = 0; j < C::TN; ++j)
 #pragma unroll
-    for (int j = 0; j < C::TN; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+    for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
 }
 
 template <class C>
-__device__ __forceinline__ void mma(f32x16 (&acc)[C::TM][C::TN], typename FloatN<C::TM>::reg a,
-                                    typename FloatN<C::TN>::reg b) {
+__device__ __forceinline__ void mma(f32x16 (&acc)[C::TN], float a, typename FloatN<C::TN>::reg b) {
 #pragma unroll
-  for (int i = 0; i < C::TM; ++i)
-#pragma unroll
-    for (int j = 0; j < C::TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(element(a, i), element(b, j), acc[i][j], 0, 0, 0);
+  for (int j = 0; j < C::TN; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, element(b, j), acc[j], 0, 0, 0);
 }
 
 // The waves' partial tiles meet in LDS and leave row by row.
 template <class C, int MODE>
-__device__ __forceinline__ void finish_tile(const TileGrid& q, const Place& w, const f32x16 (&acc)[C::TM][C::TN],
+__device__ __forceinline__ void finish_tile(const TileGrid& q, const Place& w, const f32x16 (&acc)[C::TN],
                                             float* staged, int wave, int lane) {
-  // register v of block (i, j) is row TM * ((v / 4) * 8 + (lane / 32) * 4 + v % 4) + i, column TN * (lane % 32) + j
+  // register v of block j is row (v / 4) * 8 + (lane / 32) * 4 + v % 4, column TN * (lane % 32) + j
   float* const mine = staged + wave * (C::BM * C::PITCH) + C::TN * (lane & 31);
 #pragma unroll
-  for (int i = 0; i < C::TM; ++i)
+  for (int v = 0; v < 16; ++v) {
+    float* dst = mine + ((v >> 2) * 8 + (lane >> 5) * 4 + (v & 3)) * C::PITCH;
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      float* dst = mine + (C::TM * ((v >> 2) * 8 + (lane >> 5) * 4 + (v & 3)) + i) * C::PITCH;
-#pragma unroll
-      for (int j = 0; j < C::TN; ++j) dst[j] = acc[i][j][v];
-    }
+    for (int j = 0; j < C::TN; ++j) dst[j] = acc[j][v];
+  }
   __syncthreads();
   emit_rows<MODE, C::BM, C::BN, C::PITCH, C::NT, C::WK>(q, w, staged, [](int rr) { return rr; });
 }
@@ -92,7 +85,6 @@ __device__ __forceinline__ void finish_tile(const TileGrid& q, const Place& w, c
 template <class C, int MODE>
 __global__ __launch_bounds__(C::NT) void wgrad_f32_kernel(const TileGrid q) {
   extern __shared__ __attribute__((aligned(16))) float staged[];        // [WK][BM][PITCH]
-  typedef typename FloatN<C::TM>::reg VA;
   typedef typename FloatN<C::TN>::reg VB;
   const int item = xcd_work_item(q.n_items);
   if (item < 0) return;
@@ -106,25 +98,25 @@ __global__ __launch_bounds__(C::NT) void wgrad_f32_kernel(const TileGrid q) {
   const int step1 = step0 + per_wave < steps ? step0 + per_wave : steps;
   const int64_t t_last = w.k_end - 1;
 
-  int64_t ra = w.row_b + C::TM * (lane & 31), cb = w.col_b + C::TN * (lane & 31);
-  if constexpr (C::TM == 1) ra = ra < p.out ? ra : p.out - 1;
+  int64_t ra = w.row_b + (lane & 31), cb = w.col_b + C::TN * (lane & 31);
+  ra = ra < p.out ? ra : p.out - 1;
   if constexpr (C::TN == 1) cb = cb < p.in ? cb : p.in - 1;
   const float* const pa = (const float*)p.dY + ra;
   const float* const pb = (const float*)p.X + cb;
-  f32x16 acc[C::TM][C::TN];
+  f32x16 acc[C::TN];
   clear<C>(acc);
 
-  auto load = [&](VA (&a)[C::U], VB (&b)[C::U], int s) {              // steps s ... s + U - 1, all complete
+  auto load = [&](float (&a)[C::U], VB (&b)[C::U], int s) {              // steps s ... s + U - 1, all complete
     const int64_t t = w.k_begin + 2 * (int64_t)s + half;
     const float* qa = pa + t * p.lddy;
     const float* qb = pb + t * p.ldx;
 #pragma unroll
     for (int u = 0; u < C::U; ++u) {
-      a[u] = *(const typename FloatN<C::TM>::mem*)(qa + (int64_t)(2 * u) * p.lddy);
+      a[u] = qa[(int64_t)(2 * u) * p.lddy];
       b[u] = *(const typename FloatN<C::TN>::mem*)(qb + (int64_t)(2 * u) * p.ldx);
     }
   };
-  auto mma_all = [&](const VA (&a)[C::U], const VB (&b)[C::U]) {
+  auto mma_all = [&](const float (&a)[C::U], const VB (&b)[C::U]) {
 #pragma unroll
     for (int u = 0; u < C::U; ++u) mma<C>(acc, a[u], b[u]);
   };
@@ -135,7 +127,7 @@ __global__ __launch_bounds__(C::NT) void wgrad_f32_kernel(const TileGrid q) {
   const int n_full = (step1 - step0 - (odd_end ? 1 : 0)) / C::U;
   int s = step0;
   if (n_full > 0) {
-    VA a0[C::U], a1[C::U];
+    float a0[C::U], a1[C::U];
     VB b0[C::U], b1[C::U];
     load(a0, b0, s);
     int g = 0;
@@ -162,20 +154,20 @@ __global__ __launch_bounds__(C::NT) void wgrad_f32_kernel(const TileGrid q) {
     }
   }
   for (; s < step1; s += C::U) {                                      // fewer than U steps, or U with one token short
-    VA a[C::U];
+    float a[C::U];
     VB b[C::U];
 #pragma unroll
     for (int u = 0; u < C::U; ++u) {
       const int64_t t = w.k_begin + 2 * (int64_t)(s + u) + half;
       const int64_t tc = t < t_last ? t : t_last;                     // past the end: the last token, zeroed below
-      a[u] = *(const typename FloatN<C::TM>::mem*)(pa + tc * p.lddy);
+      a[u] = pa[tc * p.lddy];
       b[u] = *(const typename FloatN<C::TN>::mem*)(pb + tc * p.ldx);
     }
 #pragma unroll
     for (int u = 0; u < C::U; ++u) {
       if (s + u >= step1) break;
       if (w.k_begin + 2 * (int64_t)(s + u) + half > t_last) {
-        a[u] = VA{};
+        a[u] = 0.f;
         b[u] = VB{};
       }
       mma<C>(acc, a[u], b[u]);
@@ -200,7 +192,6 @@ __device__ __forceinline__ typename FloatN<N>::reg lds_read(unsigned addr) {
 template <class C, int MODE>
 __global__ __launch_bounds__(C::NT, 2) void wgrad_f32_ring_kernel(const TileGrid q) {
   extern __shared__ __attribute__((aligned(1024))) float staged[];
-  typedef typename FloatN<C::TM>::reg VA;
   typedef typename FloatN<C::TN>::reg VB;
   const int item = xcd_work_item(q.n_items);
   if (item < 0) return;
@@ -219,7 +210,7 @@ __global__ __launch_bounds__(C::NT, 2) void wgrad_f32_ring_kernel(const TileGrid
   // ---- memory -> LDS: load j of an operand holds its tokens j * TPL ... + TPL - 1, lane l the 16-byte
   // piece l % LPT of token l / LPT; the source is a scalar base that moves one slab per fetch plus a
   // per-lane offset that never changes
-  constexpr int LPT_A = C::BM / 4, TPL_A = 64 / LPT_A, LPT_B = C::BN / 4, TPL_B = 64 / LPT_B;
+  constexpr int LPT_A = C::BM / 4, LPT_B = C::BN / 4, TPL_B = 64 / LPT_B;
   const unsigned lda = (unsigned)(p.lddy * 4), ldb = (unsigned)(p.ldx * 4);
   const unsigned va = (unsigned)(lane / LPT_A) * lda + (unsigned)(w.row_b + lane % LPT_A * 4) * 4u;
   const unsigned vb = (unsigned)(lane / LPT_B) * ldb + (unsigned)(w.col_b + lane % LPT_B * 4) * 4u;
@@ -235,16 +226,12 @@ __global__ __launch_bounds__(C::NT, 2) void wgrad_f32_ring_kernel(const TileGrid
     const unsigned dst = ring + slot * C::SLAB_BYTES;
     const int left = valid - fetched * C::KS;              // tokens past the end step back to the last one
     if (left >= C::KS) {
-#pragma unroll
-      for (int j = 0; j < C::TM; ++j) to_lds(ga, va, (unsigned)(j * TPL_A) * lda, dst + j * 1024);
+      to_lds(ga, va, 0, dst);
 #pragma unroll
       for (int j = 0; j < C::TN; ++j) to_lds(gb, vb, (unsigned)(j * TPL_B) * ldb, dst + C::A_BYTES + j * 1024);
     } else {
-#pragma unroll
-      for (int j = 0; j < C::TM; ++j) {
-        const int t = j * TPL_A + lane / LPT_A, tc = t < left ? t : left - 1;
-        to_lds(ga, (unsigned)tc * lda + (unsigned)(w.row_b + lane % LPT_A * 4) * 4u, 0, dst + j * 1024);
-      }
+      const int ta = lane / LPT_A < left ? lane / LPT_A : left - 1;
+      to_lds(ga, (unsigned)ta * lda + (unsigned)(w.row_b + lane % LPT_A * 4) * 4u, 0, dst);
 #pragma unroll
       for (int j = 0; j < C::TN; ++j) {
         const int t = j * TPL_B + lane / LPT_B, tc = t < left ? t : left - 1;
@@ -257,22 +244,22 @@ __global__ __launch_bounds__(C::NT, 2) void wgrad_f32_ring_kernel(const TileGrid
   };
 
   // ---- LDS -> registers: step u of a slab is tokens 2u, 2u + 1, the lane's is 2u + lane / 32
-  const unsigned ra = ring + half * (C::BM * 4) + (lane & 31) * (C::TM * 4);
+  const unsigned ra = ring + half * (C::BM * 4) + (lane & 31) * 4;
   const unsigned rb = ring + C::A_BYTES + half * (C::BN * 4) + (lane & 31) * (C::TN * 4);
-  auto read = [&](VA (&a)[C::U], VB (&b)[C::U], int slot) {
+  auto read = [&](float (&a)[C::U], VB (&b)[C::U], int slot) {
     const unsigned so = slot * C::SLAB_BYTES;
     static_for<C::U>([&](auto uc) {
       constexpr int u = decltype(uc)::value;
-      a[u] = lds_read<C::TM, u * 2 * C::BM * 4>(ra + so);
+      a[u] = lds_read<1, u * 2 * C::BM * 4>(ra + so);
       b[u] = lds_read<C::TN, u * 2 * C::BN * 4>(rb + so);
     });
   };
-  auto landed = [&](VA (&a)[C::U], VB (&b)[C::U]) {         // the reads have returned
+  auto landed = [&](float (&a)[C::U], VB (&b)[C::U]) {         // the reads have returned
     asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(b[0]), "+v"(b[1]), "+v"(b[2]), "+v"(b[3])::"memory");
   };
-  f32x16 acc[C::TM][C::TN];
+  f32x16 acc[C::TN];
   clear<C>(acc);
-  VA a0[C::U], a1[C::U];
+  float a0[C::U], a1[C::U];
   VB b0[C::U], b1[C::U];
   if (nk > 0) {
 #pragma unroll
@@ -283,7 +270,7 @@ __global__ __launch_bounds__(C::NT, 2) void wgrad_f32_ring_kernel(const TileGrid
     landed(a0, b0);
     // one slab: refill the slot whose reads have returned, make sure the next slab is there and request its
     // operands, multiply
-    auto slab = [&](int k, VA (&a)[C::U], VB (&b)[C::U], VA (&an)[C::U], VB (&bn)[C::U]) {
+    auto slab = [&](int k, float (&a)[C::U], VB (&b)[C::U], float (&an)[C::U], VB (&bn)[C::U]) {
       if (k + C::NS < nk) {
         fetch(k % C::NS);
         wait_vmcnt<(C::NS - 1) * C::L>();
@@ -294,7 +281,7 @@ __global__ __launch_bounds__(C::NT, 2) void wgrad_f32_ring_kernel(const TileGrid
 #pragma unroll
         for (int u = 0; u < C::U; ++u)
           if (k * C::KS + 2 * u + half >= valid) {
-            a[u] = VA{};
+            a[u] = 0.f;
             b[u] = VB{};
           }
       }
@@ -317,7 +304,7 @@ __global__ __launch_bounds__(C::NT, 2) void wgrad_f32_ring_kernel(const TileGrid
 }
 
 template <class C> constexpr bool is_ring = false;
-template <int TM, int TN, int WK, int NS> constexpr bool is_ring<F32RingCfg<TM, TN, WK, NS>> = true;
+template <int TN, int WK, int NS> constexpr bool is_ring<F32RingCfg<TN, WK, NS>> = true;
 
 template <auto Kern, class C>
 int launch_kernel(const TileGrid& q, hipStream_t st) {
@@ -363,7 +350,7 @@ bool ring_ok(const WgradProblem& p) {
 // Which kernel and tile (times on 4096 x 4096, 8 Mi elements from mid-row, 1024 tokens, gradient / fused call;
 // 112 us are the instructions alone, the scalar-FMA kernel that was here before needed 490 us fused):
 //   - 16-byte rows go through the LDS ring, 32 x 64 tiles of four waves (139 / 157 us; 64 x 64 tiles 170 / 184,
-//     64 x 128 189 / 213: fewer bytes per flop, but 36 KB of ring and 77 registers let three to four
+//     64 x 128 189 / 213: fewer bytes per flop, but a 34 KB staging area over 24 KB of ring and 69 registers let four
 //     workgroups share a compute unit, which evens out the rounds and puts the AdamW stream of one under the
 //     loop of another; two slabs of ring are as good as four, for the same reason);
 //   - other rows straight to registers, 32 x 128 tiles (200 / 212 us; 64 x 64: 222 / 227, 32 x 64: 367): the
@@ -377,9 +364,9 @@ int launch_wgrad_f32(const WgradProblem& p, int mode, const Sinks& s, void* stre
   const int64_t rows = (p.end - 1) / p.in - p.begin / p.in + 1;
   const bool few = ceil_div(rows, 32) * ceil_div(p.in, 64) * p.S <= device_compute_units();
   if (p.out >= 32 && p.in >= 64 && ring_ok(p))
-    return few ? launch_cfg<F32RingCfg<1, 1, 8, 3>>(p, mode, s, st) : launch_cfg<F32RingCfg<1, 2, 4, 2>>(p, mode, s, st);
-  if (few || p.in < 128) return launch_cfg<F32Cfg<1, 1, 16>>(p, mode, s, st);
-  return launch_cfg<F32Cfg<1, 4, 4>>(p, mode, s, st);
+    return few ? launch_cfg<F32RingCfg<1, 8, 3>>(p, mode, s, st) : launch_cfg<F32RingCfg<2, 4, 2>>(p, mode, s, st);
+  if (few || p.in < 128) return launch_cfg<F32Cfg<1, 16>>(p, mode, s, st);
+  return launch_cfg<F32Cfg<4, 4>>(p, mode, s, st);
 }
 
 }  // namespace chunkft

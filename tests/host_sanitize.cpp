@@ -55,12 +55,13 @@ int launch_wgrad_bf16_mfma(const WgradProblem& p, int mode, const Sinks& s, void
   if (mode == EMIT_PARTIAL) check_partials(p, s);
   return 0;
 }
-int launch_wgrad_simt(const WgradProblem& p, int, int mode, const Sinks& s, void*) {
+int launch_wgrad_ragged(const WgradProblem& p, int mode, const Sinks& s, void*) {
   ++g_launches;
   check_problem(p);
   if (mode == EMIT_PARTIAL) check_partials(p, s);
   return 0;
 }
+int launch_wgrad_f32(const WgradProblem& p, int mode, const Sinks& s, void* stream) { return launch_wgrad_ragged(p, mode, s, stream); }
 int launch_colsum(const WgradProblem& p, int, int, const Sinks&, void*) { ++g_launches; check_problem(p); expect(p.S == 1, "vector split"); return 0; }
 int launch_norm_wgrad(const WgradProblem& p, int, bool, float, float* stats, int, const Sinks&, void*) {
   ++g_launches;
