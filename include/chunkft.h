@@ -339,9 +339,9 @@ int chunkft_wgrad_adamw_fused(const chunkft_layer* L, int64_t begin, int64_t end
  * slab when the group's matrix segments together have more 256 x 256 tiles than a
  * quarter of the compute units (the single call's rule applied to the sum), else
  * what the single call would choose; split_k >= 1 is obeyed.  Segments the one-launch
- * kernel cannot take (fp32, more than one token slab, shapes off the MFMA path, bodies
- * of a few rows, EMBEDDING / RMSNORM / LAYERNORM) are run by themselves inside this
- * call, one after the other on `stream`, sharing `ws`.
+ * kernel cannot take (fp32, more than one token slab, shapes off the MFMA path, ranges
+ * that begin or end mid-row around at most 128 whole rows, EMBEDDING / RMSNORM /
+ * LAYERNORM) are run by themselves inside this call, one after the other on `stream`, sharing `ws`.
  *
  * segs (host, in)   n_segs >= 1 (at most 4096) segments; ranges on the same tensor
  *                   must not overlap, and no two segments may share state elements.

@@ -1,5 +1,5 @@
 // C ABI of libchunkft: argument validation and dispatch to the gfx950 kernels.
-// Nothing here computes; every step of the path runs in kernels.hip.
+// Nothing here computes; every step of the path runs in the kernels (kernels.hip, wgrad_*.hip).
 
 #include "chunkft.h"
 
@@ -251,8 +251,8 @@ struct GroupPlan {
 // Validates every segment and decides which ones the one-launch kernel takes.  Matrix segments
 // whose split_k is 0 take one token slab when the group as a whole has the tiles to fill the
 // device (more than a quarter of its compute units, the rule of the single call, applied to the
-// sum); a segment the kernel cannot take (fp32, a forced split, a shape off the MFMA path, a body
-// of a few rows, the other kinds) runs by itself, exactly as chunkft_wgrad_adamw_fused would.
+// sum); a segment the kernel cannot take (fp32, a forced split, a shape off the MFMA path, edge rows
+// beside a body of at most 128 rows, the other kinds) runs by itself, exactly as chunkft_wgrad_adamw_fused would.
 GroupPlan plan_group(const chunkft_group_segment* segs, int32_t n) {
   GroupPlan g;
   g.checked.resize(static_cast<size_t>(n));

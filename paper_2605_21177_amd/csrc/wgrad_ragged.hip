@@ -254,7 +254,7 @@ int launch_cfg(const WgradProblem& p, int mode, const Sinks& s, hipStream_t st) 
 // Which tile (times: gradient / fused call; a scalar-FMA tile was here before, 807 us on the first):
 //   32003 x 4096, 16 Mi elements, 1024 tokens: 64 x 128 in two token groups 75 / 123 us, 128 x 128 71 / 139,
 //   64 x 64 in four token groups 103 / 143;
-//   4097 x 4095, 2048 tokens: 155 / 212, 115 / 217, 193 / 257 us;
+//   4097 x 4095, 2048 tokens: 155 / 212, 112 / 224, 193 / 257 us;
 //   2705 x 2907, 1.5 Mi elements, 1024 tokens (115 tiles of 128 x 128): 16.6 / 32.8, 19.7 / 42.5, 16.3 / 27.7 us;
 //   32003 x 4096, 12 Mi elements, 1536 tokens: 80 / 121, 67 / 118 us;
 //   1001 x 1003, 1024 tokens (64 tiles): 15.4 / 26.4, 20.3 / 45.6, 12.2 / 18.7 us.

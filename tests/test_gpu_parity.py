@@ -1,7 +1,8 @@
 """GPU parity: libchunkft (through its C ABI) against the CPU oracle, element by
 element on the same seeded inputs.  Sizes here are ones the oracle finishes in
-seconds while still spanning several tiles, ragged tails and both code paths
-(MFMA body + FMA edge rows, FMA fallback, split over tokens)."""
+seconds while still spanning several tiles and ragged tails of every path (large
+bf16 tiles with the edge rows they carry, small ones, rows that are not 16-byte
+pieces, fp32 through the LDS ring and through registers, split over tokens)."""
 
 import numpy as np
 import pytest
@@ -197,7 +198,7 @@ RANGES_520x264 = [
     (0, 264 * 4 + 100),             # from the tensor's first row: four complete rows, the partial one in the same 8-row group
     (0, 264 * 100 + 77),            # from the first row: a body of at most 128 rows and a partial last row
     (264 * 8, 264 * 11 + 5),        # begin on an 8-aligned row boundary, three complete rows, a partial one
-    (264 * 16, 264 * 120 + 9),      # the same with a longer body that still leaves the edge rows to their own kernel
+    (264 * 16, 264 * 120 + 9),      # the same with a longer body, still too short for the large tiles to carry edge rows
 ]
 
 
@@ -350,7 +351,7 @@ def test_bf16_small_tiles_long(out, n_in, T, split_k):
     _check_infinities_in_the_last_tokens(case, split_k or 1)
 
 
-def test_bf16_unaligned_shape_takes_fma_path():
+def test_bf16_unaligned_shape():
     rng = np.random.default_rng(78)
     case = WL.linear_case(rng, "odd", 137, 100, 53, WL.BF16, 1e-3)   # in, out not multiples of 8
     for begin, end in ((0, 13700), (101, 9999), (5, 6)):
@@ -441,7 +442,7 @@ def test_bf16_strided_operands():
 def test_bf16_very_large_row_strides(log2_stride):
     """The global->LDS loads address a lane's data as a 32-bit byte offset from a per-slab base: a dY row
     stride of 2^24 elements (offsets up to 2^30 bytes) stays on the MFMA path, one of 2^25 is beyond what
-    the library accepts for it and takes the FMA kernel; both must give the gradient."""
+    the library accepts for it and goes element by element (64-bit addresses); both must give the gradient."""
     rng = np.random.default_rng(83 + log2_stride)
     out, n_in, T = 264, 136, 40 if log2_stride == 24 else 3
     case = WL.linear_case(rng, "wide-stride", out, n_in, T, WL.BF16, 1e-3)
@@ -505,8 +506,8 @@ def test_bf16_random_shapes_strides_ranges_and_splits(seed):
 
 @pytest.mark.parametrize("seed", [201, 202])
 def test_random_cases_of_every_kind_cold_and_warm(seed):
-    """Seeded random layers of every kind and dtype (fp32 and odd-shaped bf16 matrices on the plain-FMA
-    path, bf16 matrices on the MFMA path with forced splits, scale vectors, embedding tables, the two
+    """Seeded random layers of every kind and dtype (fp32 matrices, odd-shaped bf16 ones without 16-byte
+    rows, aligned bf16 ones with forced splits, scale vectors, embedding tables, the two
     self-normalising vectors), ranges that often start at the tensor's first element or on a row boundary
     and are often only a few rows long, half of them with warm moments: everything _full_check checks."""
     rng = np.random.default_rng(seed)
