@@ -162,7 +162,11 @@ __global__ __launch_bounds__(C::NT, C::WK == 1 && MODE != EMIT_ADAMW ? 3 : 2) vo
     }
     return __builtin_shufflevector(h[0], h[1], 0, 1, 2, 3, 4, 5, 6, 7);
   };
-  auto multiply = [&](int kt) {
+  // `between` runs between the two 16-token steps: the loop stores the next slab there, under the matrix instructions of
+  // the second step (behind them the barrier waited for the LDS writes: fused call, 12 Mi elements of 32003 x 4096 at 1536
+  // tokens 119 -> 113 us, 7 Mi of 2705 x 2907 at 1024 tokens 89 -> 83; in front of the first step, or with the fragments of both
+  // steps read at once, 114 - 116 and 83 - 84).
+  auto multiply = [&](int kt, auto&& between) {
     const unsigned char* const src = mine + (kt & 1) * C::SLAB_BYTES;
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) {
@@ -175,6 +179,7 @@ __global__ __launch_bounds__(C::NT, C::WK == 1 && MODE != EMIT_ADAMW ? 3 : 2) vo
       for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+      if (ks == 0) between();
     }
   };
 
@@ -198,19 +203,17 @@ __global__ __launch_bounds__(C::NT, C::WK == 1 && MODE != EMIT_ADAMW ? 3 : 2) vo
   int kt = 0;
   for (; kt + 2 < nk; kt += 2) {
     load(a0, b0, kt + 2);
-    multiply(kt);
-    store(a1, b1, kt + 1);
+    multiply(kt, [&] { store(a1, b1, kt + 1); });
     __syncthreads();
     load(a1, b1, kt + 3);                     // may be past the end: clamped, never multiplied
-    multiply(kt + 1);
-    store(a0, b0, kt + 2);
+    multiply(kt + 1, [&] { store(a0, b0, kt + 2); });
     __syncthreads();
   }
-  multiply(kt);
+  multiply(kt, [] {});
   if (kt + 1 < nk) {
     store(a1, b1, kt + 1);
     __syncthreads();
-    multiply(kt + 1);
+    multiply(kt + 1, [] {});
   }
 
   // register v of a block is row (v / 4) * 8 + (lane / 32) * 4 + v % 4, column lane % 32; half h of the tile is
@@ -258,7 +261,8 @@ int launch_cfg(const WgradProblem& p, int mode, const Sinks& s, hipStream_t st) 
 //   2705 x 2907, 1.5 Mi elements, 1024 tokens (115 tiles of 128 x 128): 16.6 / 32.8, 19.7 / 42.5, 16.3 / 27.7 us;
 //   32003 x 4096, 12 Mi elements, 1536 tokens: 80 / 121, 67 / 118 us;
 //   1001 x 1003, 1024 tokens (64 tiles): 15.4 / 26.4, 20.3 / 45.6, 12.2 / 18.7 us.
-// The update's streams (82 us of the 123) run under the loops of the other workgroups of a compute unit, of
+// (Before the slab was stored between the steps; since then 122, 214, 27, 113 and 18 us for the tiles chosen.)
+// The update's streams (82 us of the 122) run under the loops of the other workgroups of a compute unit, of
 // which the 64 x 128 tile leaves more room for; with more tokens the loop decides, and the larger tile reads
 // its operands fewer times.  Every mode of a call takes the same tile: the order of the sum is the same.
 int launch_wgrad_ragged(const WgradProblem& p, int mode, const Sinks& s, void* stream) {
