@@ -18,6 +18,7 @@ typedef __attribute__((ext_vector_type(4))) unsigned int u32x4_t;
 typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));   // 16 bytes at any dword
 typedef unsigned int u32x2_a2 __attribute__((ext_vector_type(2), aligned(2)));   // 8 bytes at any bf16
 #define LDS_PTR(T) __attribute__((address_space(3))) T*
+#define GLOBAL_PTR(T) __attribute__((address_space(1))) T*
 
 // Compile-time loop: the body sees its index as a constant, so register arrays
 // indexed by it never fall back to scratch memory.
@@ -135,6 +136,24 @@ __device__ __forceinline__ State4 load_state4(const Vec4Sink& d) {
   return st;
 }
 
+constexpr int kNonTemporal = 2;   // the nt bit in the cache policy of a buffer access
+
+__device__ __forceinline__ void update4(f32x4_u val, State4& st, const AdamWConsts& c) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    float t = st.th[e], a = st.mm[e], b = st.vv[e];
+    adamw_update(val[e], t, a, b, c);
+    st.th[e] = t; st.mm[e] = a; st.vv[e] = b;
+  }
+}
+
+__device__ __forceinline__ u32x2_a2 pack_bf16(f32x4_u x) {
+  u32x2_a2 pk;
+  pk[0] = (unsigned int)f32_to_bf16_rne(x[0]) | ((unsigned int)f32_to_bf16_rne(x[1]) << 16);
+  pk[1] = (unsigned int)f32_to_bf16_rne(x[2]) | ((unsigned int)f32_to_bf16_rne(x[3]) << 16);
+  return pk;
+}
+
 template <int MODE>
 __device__ __forceinline__ void finish4(const Vec4Sink& d, int w_kind, const AdamWConsts& c, f32x4_u val,
                                         State4 st) {
@@ -146,20 +165,12 @@ __device__ __forceinline__ void finish4(const Vec4Sink& d, int w_kind, const Ada
     st.th += val;
     *(f32x4_u*)d.g = st.th;
   } else {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      float t = st.th[e], a = st.mm[e], b = st.vv[e];
-      adamw_update(val[e], t, a, b, c);
-      st.th[e] = t; st.mm[e] = a; st.vv[e] = b;
-    }
+    update4(val, st, c);
     __builtin_nontemporal_store(st.th, (f32x4_u*)d.master);
     __builtin_nontemporal_store(st.mm, (f32x4_u*)d.m);
     __builtin_nontemporal_store(st.vv, (f32x4_u*)d.v);
     if (w_kind == W_BF16) {
-      u32x2_a2 pk;
-      pk[0] = (unsigned int)f32_to_bf16_rne(st.th[0]) | ((unsigned int)f32_to_bf16_rne(st.th[1]) << 16);
-      pk[1] = (unsigned int)f32_to_bf16_rne(st.th[2]) | ((unsigned int)f32_to_bf16_rne(st.th[3]) << 16);
-      __builtin_nontemporal_store(pk, (u32x2_a2*)d.W);
+      __builtin_nontemporal_store(pack_bf16(st.th), (u32x2_a2*)d.W);
     } else if (w_kind == W_F32) {
       __builtin_nontemporal_store(st.th, (f32x4_u*)d.W);
     }

@@ -81,8 +81,9 @@ struct MfmaParams {
 //   compute unit, so the store-bound epilogue of one runs under the MFMA loop of the other;
 //   WM = 2, NS = 4: 256 x 256 tiles, 8 waves, 132 KB -- one workgroup per compute unit,
 //   a third less operand traffic per flop.
-template <int WM_, int NS_, int MI_ = 32>
+template <int WM_, int NS_, int MI_ = 32, bool AHEAD_ = true>
 struct RingCfg {
+  static constexpr bool AHEAD = AHEAD_;               // how the update reads its state (tile_epilogue)
   static constexpr int WM = WM_, WN = 4, BM = 128 * WM, BN = 256, BK = 32, NS = NS_;
   static constexpr int MI = MI_;                      // MFMA shape: 32 (32x32x16) or 16 (16x16x32)
   static constexpr int NW = WM * WN, NT = 64 * NW;
@@ -163,9 +164,94 @@ __device__ __forceinline__ void tile_epilogue(const MfmaParams& q, unsigned char
                                : (void*)((float*)q.s.W + i + p.begin);
     return d;
   };
-  emit_edge(E);
+  // Rows that are read before they are written.  AHEAD (the sum into g; the update on 256-row tiles, and on 128-row tiles over few tokens): batches
+  // of RPT rows in a pipeline, the state of the next batch requested before the present one is finished, across the two
+  // halves, the first before the tile is staged; a batch's stores are then younger than the next batch's loads, whose
+  // wait does not include them.  The accesses are buffer forms whose range check drops what is not there (a row past the
+  // body, a group of four past the row), so that no branch lies between a load and its use and the compiler can count what
+  // is in flight.  32 Mi elements of 4096-wide rows, fused call: 512 tokens 176.8 -> 167.3 us, 1024 tokens 182.5 ->
+  // 179.5; two gradients and the optimizer pass 335 -> 330.  Else (the update of 128-row tiles over more tokens) a batch is requested, awaited and
+  // finished: the loops decide there, and with twice the requests in flight the update takes more of the memory from
+  // the loop beside it than it gains (2048 tokens 218 us, with the pipeline 223; 40 Mi of 14336-wide rows 309 against 326).
+  constexpr bool AHEAD = MODE == EMIT_ACCUM || (MODE == EMIT_ADAMW && C::AHEAD);
+  constexpr int RPT = MODE == EMIT_ACCUM ? 8 : 4, NB = HALF_ROWS / C::NW / RPT;
+  static_assert(NB * RPT * C::NW == HALF_ROWS, "whole batches");
+  constexpr int kNowhere = (int)0x80000000;                        // past every descriptor's end
+  // (read once into scalar registers: a value that the compiler fetches again behind a lane-dependent branch makes
+  // it treat the descriptors as lane-dependent too)
+  auto scalar = [](uint64_t x) {
+    const uint64_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)x), hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(x >> 32));
+    return hi << 32 | lo;
+  };
+  auto desc = [&](float* base) {     // a tile spans less than 255 rows of 2^21 elements: 2^31 bytes
+    return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(scalar(reinterpret_cast<uint64_t>(base + origin))), 0, 0x7fffffff, 0x00020000);
+  };
+  const unsigned pitch = (unsigned)__builtin_amdgcn_readfirstlane((int)p.in);      // elements from row to row
+  const bool low = MODE == EMIT_ADAMW && q.s.w_kind == W_BF16;
+  auto* const low_copy = (GLOBAL_PTR(unsigned short))scalar(reinterpret_cast<uint64_t>((unsigned short*)q.s.W + p.begin + origin));   // the tile corner's
+  const __amdgpu_buffer_rsrc_t first = desc(MODE == EMIT_ADAMW ? q.s.master : q.s.g);
+  const __amdgpu_buffer_rsrc_t second = desc(q.s.m), third = desc(q.s.v);
+  const int lane_off = vec_lane && c4 + 4 <= cols_valid ? c4 * 4 : kNowhere;
+  auto batch_row = [&](int h, int j) {
+    const int rr = j * C::NW + wave;                               // staged row, 0..HALF_ROWS-1
+    return (rr / WR) * (2 * WR) + h * WR + rr % WR;
+  };
+  State4 ahead[2][RPT];
+  auto request = [&](auto nc) {
+    constexpr int n = decltype(nc)::value, h = n / NB;
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
+    for (int u = 0; u < RPT; ++u) {
+      const int tile_row = batch_row(h, (n % NB) * RPT + u);
+      const int vo = tile_row < rows_valid ? lane_off : kNowhere;
+      const int so = (int)((unsigned)tile_row * pitch * 4u);
+      auto get = [&](__amdgpu_buffer_rsrc_t from) { return __builtin_bit_cast(f32x4_u, __builtin_amdgcn_raw_buffer_load_b128(from, vo, so, kNonTemporal)); };
+      State4& st = ahead[n & 1][u];
+      st.th = get(first);
+      if constexpr (MODE == EMIT_ADAMW) {
+        st.mm = get(second);
+        st.vv = get(third);
+      }
+    }
+  };
+  auto finish = [&](auto nc) {
+    constexpr int n = decltype(nc)::value, h = n / NB;
+    u32x2_a2 packed[RPT];
+#pragma unroll
+    for (int u = 0; u < RPT; ++u) {
+      const int j = (n % NB) * RPT + u, tile_row = batch_row(h, j);
+      const int vo = tile_row < rows_valid ? (int)((unsigned)lane_off + (unsigned)tile_row * pitch * 4u) : kNowhere;
+      auto put = [&](__amdgpu_buffer_rsrc_t to, f32x4_u x) {
+        // The row goes into the lane offset, not into the scalar one: behind a 16-byte store with a register as its scalar
+        // offset the compiler keeps no wait state, and where the next instruction wrote the first data register this
+        // device stored the new value (every fourth m and v of the 256-row tile).
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, x), to, vo, 0, MODE == EMIT_ACCUM ? 0 : kNonTemporal);
+      };
+      const float4 q4 = *reinterpret_cast<const float4*>(stage + (j * C::NW + wave) * C::EPI_PITCH + sft + c4);
+      const f32x4_u val = {q4.x, q4.y, q4.z, q4.w};
+      State4& st = ahead[n & 1][u];
+      if constexpr (MODE == EMIT_ACCUM) {
+        st.th += val;
+        put(first, st.th);
+      } else {
+        update4(val, st, q.s.c);
+        put(first, st.th);
+        put(second, st.mm);
+        put(third, st.vv);
+        packed[u] = pack_bf16(st.th);
+      }
+    }
+    if constexpr (MODE == EMIT_ADAMW) {
+      if (low && lane_off != kNowhere) {
+#pragma unroll
+        for (int u = 0; u < RPT; ++u) {
+          const int tile_row = batch_row(h, (n % NB) * RPT + u);
+          if (tile_row < rows_valid)
+            __builtin_nontemporal_store(packed[u], (GLOBAL_PTR(u32x2_a2))(low_copy + (unsigned)tile_row * pitch + c4));
+        }
+      }
+    }
+  };
+  auto half = [&](int h, auto&& rows) __attribute__((always_inline)) {     // rows(): the staged rows of the half leave
     __syncthreads();                       // ring reads / previous half's row reads are done
     stage_half(h, stage + (wmi * WR) * C::EPI_PITCH + sft + wn0);
     __syncthreads();
@@ -190,32 +276,7 @@ __device__ __forceinline__ void tile_epilogue(const MfmaParams& q, unsigned char
         }
       }
     }
-    if (vec_lane && c4 + 4 <= cols_valid) {
-      // RPT rows per trip: their state loads are issued together, then the updates
-      // (four measured best for the fused call: 226 us against 228 / 248 us with two / one)
-      constexpr int RPT = 4;
-      for (int j0 = 0; j0 < HALF_ROWS / C::NW; j0 += RPT) {
-        Vec4Sink d[RPT];
-        State4 st[RPT];
-        bool ok[RPT];
-#pragma unroll
-        for (int u = 0; u < RPT; ++u) {
-          const int rr = (j0 + u) * C::NW + wave;                        // staged row, 0..HALF_ROWS-1
-          const int tile_row = (rr / WR) * (2 * WR) + h * WR + rr % WR;
-          ok[u] = tile_row < rows_valid;
-          d[u] = sink_at(origin + (int64_t)tile_row * p.in + c4);
-          if (ok[u]) st[u] = load_state4<MODE>(d[u]);
-        }
-#pragma unroll
-        for (int u = 0; u < RPT; ++u) {
-          if (ok[u]) {
-            const float4 q4 = *reinterpret_cast<const float4*>(stage + ((j0 + u) * C::NW + wave) * C::EPI_PITCH + sft + c4);
-            const f32x4_u val = {q4.x, q4.y, q4.z, q4.w};
-            finish4<MODE>(d[u], q.s.w_kind, q.s.c, val, st[u]);
-          }
-        }
-      }
-    }
+    rows();
     if (lo_ok) {
       if constexpr (MODE == EMIT_ADAMW) {
         adamw_update(lo_val, lo_th, lo_m, lo_v, q.s.c);
@@ -228,6 +289,46 @@ __device__ __forceinline__ void tile_epilogue(const MfmaParams& q, unsigned char
         emit<MODE>(q.s, E, slab, lo_i, lo_i + p.begin, lo_val);
       }
     }
+  };
+  if constexpr (AHEAD) {
+    request(IntC<0>{});
+    emit_edge(E);
+    static_for<2>([&](auto hc) {
+      half(decltype(hc)::value, [&] {
+        static_for<NB>([&](auto bc) {
+          constexpr int n = decltype(hc)::value * NB + decltype(bc)::value;
+          if constexpr (n + 1 < 2 * NB) request(IntC<n + 1>{});
+          finish(IntC<n>{});
+        });
+      });
+    });
+  } else {
+    emit_edge(E);
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      half(h, [&] {
+        if (!(vec_lane && c4 + 4 <= cols_valid)) return;
+        for (int j0 = 0; j0 < HALF_ROWS / C::NW; j0 += RPT) {
+          Vec4Sink d[RPT];
+          State4 st[RPT];
+          bool ok[RPT];
+#pragma unroll
+          for (int u = 0; u < RPT; ++u) {
+            const int tile_row = batch_row(h, j0 + u);
+            ok[u] = tile_row < rows_valid;
+            d[u] = sink_at(origin + (int64_t)tile_row * p.in + c4);
+            if (ok[u]) st[u] = load_state4<MODE>(d[u]);
+          }
+#pragma unroll
+          for (int u = 0; u < RPT; ++u) {
+            if (ok[u]) {
+              const float4 q4 = *reinterpret_cast<const float4*>(stage + ((j0 + u) * C::NW + wave) * C::EPI_PITCH + sft + c4);
+              const f32x4_u val = {q4.x, q4.y, q4.z, q4.w};
+              finish4<MODE>(d[u], q.s.w_kind, q.s.c, val, st[u]);
+            }
+          }
+        }
+      });
   }
 }
 
@@ -1062,15 +1163,11 @@ __device__ __forceinline__ void mfma_tile16(const MfmaParams& q, const int item,
 // together and then their HBM-bound epilogues together; with stagger > 0 the second
 // one of each pair (workgroups are dealt to the 32 compute units of an XCD in order:
 // the first 32 fill one slot each, the next 32 the other) starts late instead, so that
-// one tends to be in its loop while the other is in its epilogue.  With one workgroup per
-// compute unit (the large tile, fused call only) every second compute unit starts late.
-template <class C, int MODE>
+// one tends to be in its loop while the other is in its epilogue.
+template <class C>
 __device__ __forceinline__ void start_offset(int stagger) {
   const int j = (int)(blockIdx.x >> 3);
-  bool late = false;
-  if constexpr (C::WM == 1) late = j >= 32 && j < 64;
-  else if constexpr (MODE == EMIT_ADAMW) late = j < 32 && (j & 1);
-  if (late)
+  if (C::WM == 1 && j >= 32 && j < 64)
     for (int i = 0; i < stagger; ++i) __builtin_amdgcn_s_sleep(127);
 }
 
@@ -1090,15 +1187,7 @@ __global__ __launch_bounds__(C::NT, 2) void wgrad_mfma_kernel(const MfmaArgs arg
   const int per_xcd = (n_items + 7) >> 3;
   const int item = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
   if (item >= n_items) return;
-  if constexpr (C::WM == 1) {
-    const int j = (int)(blockIdx.x >> 3);
-    if (j >= 32 && j < 64)
-      for (int i = 0; i < q.stagger; ++i) __builtin_amdgcn_s_sleep(127);
-  } else if constexpr (MODE == EMIT_ADAMW) {
-    const int j = (int)(blockIdx.x >> 3);
-    if (j < 32 && (j & 1))
-      for (int i = 0; i < q.stagger; ++i) __builtin_amdgcn_s_sleep(127);
-  }
+  start_offset<C>(q.stagger);
   if constexpr (C::MI == 16) mfma_tile16<C, MODE>(q, item, ldsb);
   else mfma_tile<C, MODE>(q, item, ldsb);
 }
@@ -1251,7 +1340,7 @@ __global__ __launch_bounds__(C::NT, 2) void wgrad_group_kernel(const GroupParams
   extern __shared__ __attribute__((aligned(1024))) unsigned char ldsb[];
   const int item = xcd_work_item(gp.n_items);
   if (item < 0) return;
-  start_offset<C, EMIT_ADAMW>(gp.stagger);
+  start_offset<C>(gp.stagger);
   int si = 0;
   while (si + 1 < gp.n_segs && item >= gp.item_start[si + 1]) ++si;
   const MfmaParams& q = gp.seg[si];
@@ -1643,15 +1732,16 @@ __global__ __launch_bounds__(256) void elementwise_kernel(const ElemParams q) {
 // ---------------------------------------------------------------------------
 namespace {
 
-// Start delay (units of 8128 cycles) of the second workgroup of each compute unit in the fused
-// call, whose epilogue is long and HBM-bound: measured best at 6 for 1024 tokens (196 us against
-// 200 us at 8, 208 us at 0), flat between 6 and 10 for 4096 and 8192; the plain gradient gains
-// nothing.
-constexpr int kStaggerAdamW = 6;
-// The large tile has one workgroup per compute unit: there every second compute unit of an XCD starts
-// late, so that the epilogues of half the part fall into the loops of the other half (measured at
-// T = 8192: 1 - 3 % at 10, nothing from 24 on).
-constexpr int kStaggerAdamWLarge = 10;
+// Start delay (units of 8128 cycles) of the second workgroup of each compute unit in the fused call, whose epilogue is
+// long and HBM-bound; the plain gradient gains nothing.  With the state requested ahead 2 is best (32 Mi elements, 1024
+// tokens, delays of 0 / 2 / 4 / 6: 183.7 / 179.5 / 180.8 / 182.5 us; 12 Mi, less than a round: 82.3 / 84.6 / 87.4 / 88.6),
+// otherwise 6 (2048 tokens: 225.6 / 221.4 / 219.0 / 218.5; 40 Mi of 14336-wide rows 325 / 320 / 313 / 309).  The 256-row
+// tile, one workgroup per compute unit, starts together: every second unit late by 10 was no faster (64 Mi, 8192 tokens
+// 1018 us against 1016; 32 Mi, 6400 tokens 447 against 439).
+template <class C> constexpr int kStaggerAdamW = C::WM == 2 ? 0 : C::AHEAD ? 2 : 6;
+// A group of segments keeps 6 either way (a 4096-wide block in two chunks, 1024 tokens, state requested ahead: 1130 us against
+// 1141 with 2; without it 1144).
+constexpr int kStaggerGroup = 6;
 // 256 x 256 tiles, four slabs of 33 KB in LDS, one workgroup per compute unit: both waves of a SIMD are in
 // the loop together, which the 16x16x32 MFMA needs (a wave then issues one MFMA per 32 cycles; alone
 // on its SIMD it would have to issue one per 16 cycles beside its reads and loads, and cannot)
@@ -1660,8 +1750,8 @@ using MainCfg = RingCfg<2, 4, 16>;
 // epilogue a workgroup's waves are alone on their SIMDs, so this one keeps the 32x32x16 MFMA (with the
 // other shape its loops were 10 % slower).  The two shapes give the same bits: the hardware adds the
 // tokens of either in the same order.
-using FusedCfg = RingCfg<1, 3, 32>;
-                                  // (the fused call, and plain gradients with few tiles)
+using FusedCfg = RingCfg<1, 3, 32>;         // (the fused call, and plain gradients with few tiles)
+using FusedLongCfg = RingCfg<1, 3, 32, false>;   // the fused call over more tokens (update_requests_ahead)
 
 template <class C, int MODE>
 int launch_mfma_mode(const MfmaParams& q, int grid, hipStream_t st) {
@@ -1722,21 +1812,27 @@ bool fill_mfma_params(const WgradProblem& p, int mode, const Sinks& s, const Row
   // for the fused call on 4096 x 14336 at T = 4096: 571 us in groups of 4 against 736 us row-major;
   // on 14336 x 4096 at T = 1024: 313 against 335 us.
   q.group_m = mode == EMIT_ADAMW ? 4 : 8;
-  q.stagger = mode == EMIT_ADAMW ? (C::WM == 1 ? kStaggerAdamW : kStaggerAdamWLarge) : 0;
+  q.stagger = mode == EMIT_ADAMW ? kStaggerAdamW<C> : 0;
   return true;
 }
 
 template <class C>
-int launch_mfma_cfg(const WgradProblem& p, int mode, const Sinks& s, hipStream_t st) {
-  const RowSplit rs = split_rows(p);
+int launch_update_cfg(const WgradProblem& p, const Sinks& s, hipStream_t st) {
   MfmaParams q;
-  if (!fill_mfma_params<C>(p, mode, s, rs, q)) return (int)hipErrorInvalidValue;   // work items are counted in 32 bits
+  if (!fill_mfma_params<C>(p, EMIT_ADAMW, s, split_rows(p), q)) return (int)hipErrorInvalidValue;   // work items are counted in 32 bits
+  return launch_mfma_mode<C, EMIT_ADAMW>(q, (q.n_tile_items + 7) / 8 * 8, st);
+}
+
+template <class C>
+int launch_mfma_cfg(const WgradProblem& p, int mode, const Sinks& s, hipStream_t st) {
+  if (mode == EMIT_ADAMW) return launch_update_cfg<C>(p, s, st);
+  MfmaParams q;
+  if (!fill_mfma_params<C>(p, mode, s, split_rows(p), q)) return (int)hipErrorInvalidValue;
   const int grid = (q.n_tile_items + 7) / 8 * 8;
   switch (mode) {
     case EMIT_STORE: return launch_mfma_mode<C, EMIT_STORE>(q, grid, st);
     case EMIT_ACCUM: return launch_mfma_mode<C, EMIT_ACCUM>(q, grid, st);
-    case EMIT_PARTIAL: return launch_mfma_mode<C, EMIT_PARTIAL>(q, grid, st);
-    default: return launch_mfma_mode<C, EMIT_ADAMW>(q, grid, st);
+    default: return launch_mfma_mode<C, EMIT_PARTIAL>(q, grid, st);
   }
 }
 
@@ -1748,7 +1844,8 @@ int launch_wgrad_bf16_mfma(const WgradProblem& p, int mode, const Sinks& s, void
   // whose epilogue moves 26 bytes per element, gains from two workgroups per compute unit.
   if (mode == EMIT_ADAMW) {
     if (fused_takes_large_tile(p, device_compute_units())) return launch_mfma_cfg<MainCfg>(p, mode, s, (hipStream_t)stream);
-    return launch_mfma_cfg<FusedCfg>(p, mode, s, (hipStream_t)stream);
+    if (update_requests_ahead(p.in, p.S > 1 ? p.kslab : p.T)) return launch_mfma_cfg<FusedCfg>(p, mode, s, (hipStream_t)stream);
+    return launch_update_cfg<FusedLongCfg>(p, s, (hipStream_t)stream);
   }
   // The plain gradient takes whichever tile is faster for its number of tiles and tokens
   // (plain_takes_large_tile, csrc/shape.cpp); every element is summed over the tokens in the same
@@ -1782,12 +1879,11 @@ static int launch_group_cfg(const GroupSegment* segs, int n, hipStream_t st) {
         items += ceil_div(g.p.end - g.p.begin, kColsumCols);
       } else {
         if (!fill_mfma_params<C>(g.p, EMIT_ADAMW, g.s, split_rows(g.p), q)) return (int)hipErrorInvalidValue;
-        gp.stagger = q.stagger;
         items += q.n_tile_items;
       }
       if (items > 0x3fffffff) return (int)hipErrorInvalidValue;
     }
-    if (gp.stagger == 0) gp.stagger = C::WM == 1 ? kStaggerAdamW : kStaggerAdamWLarge;
+    gp.stagger = C::WM == 2 ? 0 : kStaggerGroup;
     gp.item_start[count] = (int32_t)items;
     gp.n_segs = count;
     gp.n_items = (int32_t)items;
@@ -1801,8 +1897,14 @@ static int launch_group_cfg(const GroupSegment* segs, int n, hipStream_t st) {
 
 int launch_fused_group(const GroupSegment* segs, int n, bool large_tile, void* stream) {
   if (n <= 0) return 0;
-  return large_tile ? launch_group_cfg<MainCfg>(segs, n, (hipStream_t)stream)
-                    : launch_group_cfg<FusedCfg>(segs, n, (hipStream_t)stream);
+  if (large_tile) return launch_group_cfg<MainCfg>(segs, n, (hipStream_t)stream);
+  // A group reads its state ahead up to 1024 tokens whatever the widths of its segments.  Blocks under 256 MiB and less in
+  // us, without / with: 4096 wide 300 tokens 1089 / 1053, 1024 tokens 1126 / 1118 (its 14336-wide segment without, the others
+  // with: 1120 where all without are 1106); 3072 wide 800 tokens 571 / 556; 2048 wide 1024 tokens 360 / 348.
+  bool ahead = true;
+  for (int i = 0; i < n; ++i) ahead = ahead && (segs[i].vector || update_requests_ahead(1, segs[i].p.T));
+  return ahead ? launch_group_cfg<FusedCfg>(segs, n, (hipStream_t)stream)
+               : launch_group_cfg<FusedLongCfg>(segs, n, (hipStream_t)stream);
 }
 
 template <typename T, int NORM, int CB>

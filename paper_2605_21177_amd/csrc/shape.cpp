@@ -144,6 +144,15 @@ bool fused_takes_large_tile(const WgradProblem& p, int compute_units) {
   return round_ratio * round_cost(w) / (round_cost(2.0 * w) / 2.0) < 0.99;
 }
 
+// Whether the update on 128-row tiles requests its state ahead (tile_epilogue in kernels.hip).  It does where the update's streams
+// decide, up to 1024 tokens (768 on rows of more than 8192 elements, which come in more and shorter pieces per tile
+// row).  Fused call in us, without / with, each at its start delay: 32 Mi elements of 4096-wide rows 256 tokens 163.4 / 159.4,
+// 512 tokens 176.8 / 167.3, 1024 tokens 182.5 / 179.5, 1300 tokens 192.7 / 187.8, 1500 tokens 195.8 / 196.1, 2048 tokens 218.5 / 222.8;
+// 64 Mi 1024 tokens 341 / 329; 48 Mi of 8192-wide rows 1024 tokens (64 Mi) 342.5 / 336.1, 1150 tokens 280.8 / 281.7, 1500 tokens
+// 292 / 297; 14336-wide rows 24 Mi 64 tokens 154.3 / 149.8, 24 Mi 1024 tokens 181.1 / 178.8, 50 Mi 310 / 314, 30 Mi 1300 tokens
+// 201 / 203, 40 Mi 2048 tokens 309 / 327.
+bool update_requests_ahead(int64_t in, int64_t slab_tokens) { return slab_tokens <= (in <= 8192 ? 1024 : 768); }
+
 int64_t countable_run(int64_t in, int32_t S, int64_t bm, int64_t bn, int threads) {
   const int64_t tiles = kMaxLaunchThreads / threads / 8 * 8 / S;             // the grid is a multiple of the 8 XCDs
   const int64_t rows = tiles / ceil_div(in, bn) * bm - 8;      // a run of whole rows touches one more; the first tile may begin 7 earlier

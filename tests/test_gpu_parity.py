@@ -240,6 +240,20 @@ def test_bf16_long_token_count_takes_the_large_tile_in_the_fused_call(begin, end
     _full_check(case, begin, end, check_accum=False)
 
 
+# The update on 128-row tiles requests its state ahead up to 1024 tokens (768 on rows of more than 8192 elements), not
+# beyond; begin % 4 is the column at which a tile's 16-byte groups start.  Last tile rows of 8 and 9 - 40 rows, a last
+# column tile of 8 columns (2312 = 9 x 256 + 8, 8200 = 32 x 256 + 8).
+@pytest.mark.parametrize("out,n_in,T,begin,end", [
+    (2072, 2312, 1024, 2312 * 3 + 1, 2312 * 2064), (2072, 2312, 1025, 2312 * 3 + 1, 2312 * 2064),
+    (2072, 2312, 1024, 2312 * 16 + 6, 2312 * 2071 + 9), (2072, 2312, 33, 2312 * 8, 2312 * 2064),
+    (560, 8200, 768, 8200 * 2 + 3, 8200 * 550 + 5), (560, 8200, 769, 8200 * 2 + 3, 8200 * 550 + 5)])
+def test_update_with_its_state_requested_ahead_and_not(out, n_in, T, begin, end):
+    case = WL.linear_case(np.random.default_rng([97, T]), "ahead", out, n_in, T, WL.BF16, 1e-3)
+    _full_check(case, begin, end, warm=True, step=3)
+    with H.phase_aligned(begin):
+        _full_check(case, begin, end, check_accum=False)
+
+
 @pytest.mark.parametrize("split_k", [2, 3, 4])
 def test_bf16_forced_token_split(split_k):
     case = _small_bf16(T=200)
