@@ -17,8 +17,9 @@ namespace {
 typedef unsigned int u32x4_a2 __attribute__((ext_vector_type(4), aligned(2)));   // 16 bytes at any bf16
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 
-template <int WM_, int WN_, int WK_>
+template <int WM_, int WN_, int WK_, bool UNDER_ = true>
 struct RaggedCfg {
+  static constexpr bool UNDER = UNDER_;                           // the next slab is stored between the two steps of a slab, else behind them
   static constexpr int WM = WM_, WN = WN_, WK = WK_, BM = 64 * WM, BN = 64 * WN;
   static constexpr int GT = 64 * WM * WN, NT = GT * WK;           // threads of a group, of the workgroup
   static constexpr int BK = 32;
@@ -199,7 +200,7 @@ __global__ __launch_bounds__(C::NT, C::WK == 1 && MODE != EMIT_ADAMW ? 3 : 2) vo
   // A slab is in LDS for those who read it.  A group of one wave has its slabs to itself, and LDS serves a wave's accesses in the order
   // they are issued: there only the compiler has to keep that order.  With the workgroup's barrier each of the four waves of a 64 x 64
   // tile waited for the slowest one's loads in every slab (1 Mi elements of 32003 x 4096, 2047 tokens, gradient / fused call 22.5 / 28.0 us, without
-  // 19.8 / 24.8; 1001 x 1003, 5000 tokens, gradient 8 % less).
+  // 19.8 / 24.8; 1001 x 1003, 5000 tokens, 32.9 / 42.8 and 31.0 / 39.9).
   auto slab_ready = [&] {
     if constexpr (C::GT == 64) {
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -215,10 +216,12 @@ __global__ __launch_bounds__(C::NT, C::WK == 1 && MODE != EMIT_ADAMW ? 3 : 2) vo
   int kt = 0;
   for (; kt + 2 < nk; kt += 2) {
     load(a0, b0, kt + 2);
-    multiply(kt, [&] { store(a1, b1, kt + 1); });
+    multiply(kt, [&] { if constexpr (C::UNDER) store(a1, b1, kt + 1); });
+    if constexpr (!C::UNDER) store(a1, b1, kt + 1);
     slab_ready();
     load(a1, b1, kt + 3);                     // may be past the end: clamped, never multiplied
-    multiply(kt + 1, [&] { store(a0, b0, kt + 2); });
+    multiply(kt + 1, [&] { if constexpr (C::UNDER) store(a0, b0, kt + 2); });
+    if constexpr (!C::UNDER) store(a0, b0, kt + 2);
     slab_ready();
   }
   multiply(kt, [] {});
@@ -264,6 +267,19 @@ int launch_cfg(const WgradProblem& p, int mode, const Sinks& s, hipStream_t st) 
   }
 }
 
+// The update on the 64 x 128 tile, the slab stored behind both steps: the loop is slower, but the kernel's epilogue streams the state a little
+// faster where rows of the state are whole 16-byte pieces, and up to 512 tokens that decides.  Fused call in us, stored between / behind: 4 Mi elements
+// of 32003 x 4096 1 token 25.9 / 25.0, 256 tokens 29.6 / 28.5, 512 tokens 35.2 / 34.4; of 50257 x 768 256 tokens 30.3 / 29.3, 512 tokens 36.2 /
+// 35.1, 768 tokens 38.1 / 39.0; 16 Mi 256 tokens 96.5 / 94.5, 32 Mi 512 tokens 192.0 / 189.1.  On other rows neither is ahead up to 256 tokens
+// (4 Mi of 2705 x 2907 128 tokens 35.1 / 34.8, 16 Mi of 31999 x 4100 40 tokens 125.5 / 128.4) and the first beyond (4 Mi of 4097 x 4095
+// 420 tokens 43.4 / 44.4).
+int launch_update_behind(const WgradProblem& p, const Sinks& s, hipStream_t st) {
+  typedef RaggedCfg<1, 2, 2, false> C;
+  TileGrid q;
+  if (!fill_grid<C::BM, C::BN>(q, p, s, 1)) return (int)hipErrorInvalidValue;
+  return launch_kernel<C, false, EMIT_ADAMW>(q, st);
+}
+
 }  // namespace
 
 // Which tile (times: gradient / fused call; a scalar-FMA tile was here before, 807 us on the first):
@@ -284,7 +300,10 @@ int launch_wgrad_ragged(const WgradProblem& p, int mode, const Sinks& s, void* s
   if (p.out < 64 || p.in < 64 || !near) return launch_cfg<RaggedCfg<1, 1, 4>, true>(p, mode, s, st);
   const bool few = ceil_div(rows, 128) * ceil_div(p.in, 128) * p.S <= device_compute_units();
   if (few || p.in < 128) return launch_cfg<RaggedCfg<1, 1, 4>, false>(p, mode, s, st);
-  if (p.kslab <= 1024 || p.out < 128) return launch_cfg<RaggedCfg<1, 2, 2>, false>(p, mode, s, st);
+  if (p.kslab <= 1024 || p.out < 128) {
+    if (mode == EMIT_ADAMW && p.in % 8 == 0 && p.kslab <= 512) return launch_update_behind(p, s, st);
+    return launch_cfg<RaggedCfg<1, 2, 2>, false>(p, mode, s, st);
+  }
   return launch_cfg<RaggedCfg<2, 2, 1>, false>(p, mode, s, st);
 }
 

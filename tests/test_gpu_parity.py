@@ -254,6 +254,15 @@ def test_update_with_its_state_requested_ahead_and_not(out, n_in, T, begin, end)
         _full_check(case, begin, end, check_accum=False)
 
 
+# Layers without 16-byte rows on the 64 x 128 tile (17 x 17 tiles of 128 x 128: more than one per compute unit): the update stores
+# the next slab behind the two steps of a slab up to 512 tokens on rows that are whole 16-byte pieces, between them
+# otherwise; the gradient always between them.  _full_check holds the two orders to the same bits.
+@pytest.mark.parametrize("n_in,T", [(2056, 70), (2056, 512), (2056, 513), (2053, 512)])
+def test_bf16_ragged_update_with_the_next_slab_stored_between_the_steps_and_behind(n_in, T):
+    case = WL.linear_case(np.random.default_rng([103, n_in, T]), "ragged order", 2051, n_in, T, WL.BF16, 1e-3)
+    _full_check(case, n_in + 5, n_in * 2050 + 77, warm=True, step=2)
+
+
 @pytest.mark.parametrize("split_k", [2, 3, 4])
 def test_bf16_forced_token_split(split_k):
     case = _small_bf16(T=200)
