@@ -1732,16 +1732,15 @@ __global__ __launch_bounds__(256) void elementwise_kernel(const ElemParams q) {
 // ---------------------------------------------------------------------------
 namespace {
 
-// Start delay (units of 8128 cycles) of the second workgroup of each compute unit in the fused call, whose epilogue is
-// long and HBM-bound; the plain gradient gains nothing.  With the state requested ahead 2 is best (32 Mi elements, 1024
-// tokens, delays of 0 / 2 / 4 / 6: 183.7 / 179.5 / 180.8 / 182.5 us; 12 Mi, less than a round: 82.3 / 84.6 / 87.4 / 88.6),
-// otherwise 6 (2048 tokens: 225.6 / 221.4 / 219.0 / 218.5; 40 Mi of 14336-wide rows 325 / 320 / 313 / 309).  The 256-row
-// tile, one workgroup per compute unit, starts together: every second unit late by 10 was no faster (64 Mi, 8192 tokens
-// 1018 us against 1016; 32 Mi, 6400 tokens 447 against 439).
+// Start delay (units of 8128 cycles) of the second workgroup of each compute unit in the fused call, single or grouped, whose
+// epilogue is long and HBM-bound; the plain gradient gains nothing.  In us at delays of 0 / 2 / 4 / 6.  With the state requested
+// ahead, 2: 32 Mi elements, 1024 tokens 183.7 / 179.5 / 180.8 / 182.5; groups at 1024 tokens, two 1024 x 14336 183.3 / 179.7 /
+// 182.5 / 183.8, a 1024-wide block 84.1 / 86.3 / 89.7 / 90.1, a 2048-wide one 327 / 325 / 329 / 330 (without the state ahead, at 6:
+// 180.5, 91.9, 343).  A launch of less than a round would rather have none (12 Mi, 82.3 / 84.6 / 87.4 / 88.6, and the
+// 1024-wide block).  Without, 6: 2048 tokens 225.6 / 221.4 / 219.0 / 218.5; 40 Mi of 14336-wide rows 325 / 320 / 313 / 309.  The
+// 256-row tile, one workgroup per compute unit, starts together: every second unit late by 10 was no faster (64 Mi, 8192
+// tokens 1018 us against 1016; 32 Mi, 6400 tokens 447 against 439).
 template <class C> constexpr int kStaggerAdamW = C::WM == 2 ? 0 : C::AHEAD ? 2 : 6;
-// A group of segments keeps 6 either way (a 4096-wide block in two chunks, 1024 tokens, state requested ahead: 1130 us against
-// 1141 with 2; without it 1144).
-constexpr int kStaggerGroup = 6;
 // 256 x 256 tiles, four slabs of 33 KB in LDS, one workgroup per compute unit: both waves of a SIMD are in
 // the loop together, which the 16x16x32 MFMA needs (a wave then issues one MFMA per 32 cycles; alone
 // on its SIMD it would have to issue one per 16 cycles beside its reads and loads, and cannot)
@@ -1883,7 +1882,7 @@ static int launch_group_cfg(const GroupSegment* segs, int n, hipStream_t st) {
       }
       if (items > 0x3fffffff) return (int)hipErrorInvalidValue;
     }
-    gp.stagger = C::WM == 2 ? 0 : kStaggerGroup;
+    gp.stagger = kStaggerAdamW<C>;
     gp.item_start[count] = (int32_t)items;
     gp.n_segs = count;
     gp.n_items = (int32_t)items;
