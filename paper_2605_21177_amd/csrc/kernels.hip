@@ -66,6 +66,7 @@ struct MfmaParams {
   int32_t n_tile_items;        // tiles_m * tiles_n * S
   int32_t group_m;
   int32_t stagger;             // start delay of every second resident workgroup, in units of 8128 cycles
+  int32_t turned;              // XCD x begins x eighths into its run of tiles (runs_in_step)
   int64_t lead_base;           // edge rows folded into the first tile row (the 8-row group before rb0; -1: none)
   int64_t trail_row;
   Sinks s;
@@ -1185,8 +1186,15 @@ __global__ __launch_bounds__(C::NT, 2) void wgrad_mfma_kernel(const MfmaArgs arg
   const MfmaParams& q = args.q[blockIdx.y];
   const int n_items = q.n_tile_items;
   const int per_xcd = (n_items + 7) >> 3;
-  const int item = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
-  if (item >= n_items) return;
+  const int xcd = (int)(blockIdx.x & 7), first = xcd * per_xcd;
+  int j = (int)(blockIdx.x >> 3);
+  if (first + j >= n_items) return;
+  if (MODE == EMIT_ACCUM && q.turned) {
+    const int run = n_items - first < per_xcd ? n_items - first : per_xcd;
+    j += xcd * (run >> 3);
+    if (j >= run) j -= run;
+  }
+  const int item = first + j;
   start_offset<C>(q.stagger);
   if constexpr (C::MI == 16) mfma_tile16<C, MODE>(q, item, ldsb);
   else mfma_tile<C, MODE>(q, item, ldsb);
@@ -1790,6 +1798,22 @@ int device_compute_units() {
   return cus;
 }
 
+// Whether the tiles that the XCDs start with, one run of tiles each, lie a power of two of at least 8 MiB (16 on the 256-row
+// tile) apart in g, or nearly, on rows of a power of two of at least 16 KB: the XCDs then walk over the same address bits in step, and the
+// sum into g, which requests its rows ahead, holds up a part of the channels.  Each XCD then begins an eighth of its run
+// further on than the one before.  g of 4096-wide rows in us, in step / turned (one batch at a time, in step): 16 Mi elements 16 tokens
+// 32.9 / 25.1 (28.7), 128 tokens 34.7 / 26.5 (32.6), 512 tokens 38.0 / 32.7 (41.7); 32 Mi 16 tokens 59.6 / 44.3 (52.4),
+// 1024 tokens, 256-row tile, 101.7 / 85.1 (109.2); 8192-wide 32 Mi 128 tokens 61.7 / 50.2 (70.7).  Elsewhere turning only breaks up the groups of
+// tile rows: 4096-wide 20 Mi 1024 tokens 58.8 / 61.0, 40 Mi 102.5 / 107.3, 14336-wide 8 Mi 512 tokens 25.4 / 28.6; and so it does over more than
+// 2048 tokens, where the loop decides (32 Mi 4096 tokens, 4096-wide 225 / 213, 16384-wide 212 / 219; 128 Mi of 8192-wide rows 6000
+// tokens 1240 / 1273).
+bool runs_in_step(int64_t in, int64_t tokens, int64_t items) {
+  const int64_t per_xcd = (items + 7) / 8;
+  int64_t top = 1;
+  while (top * 2 <= per_xcd) top *= 2;
+  return tokens <= 2048 && in >= 4096 && (in & (in - 1)) == 0 && per_xcd >= 64 && per_xcd - top <= per_xcd / 32;
+}
+
 // Parameters of the MFMA kernel for a call.  False if the work items cannot be counted in 32 bits.
 template <class C>
 bool fill_mfma_params(const WgradProblem& p, int mode, const Sinks& s, const RowSplit& rs, MfmaParams& q) {
@@ -1812,6 +1836,7 @@ bool fill_mfma_params(const WgradProblem& p, int mode, const Sinks& s, const Row
   // on 14336 x 4096 at T = 1024: 313 against 335 us.
   q.group_m = mode == EMIT_ADAMW ? 4 : 8;
   q.stagger = mode == EMIT_ADAMW ? kStaggerAdamW<C> : 0;
+  q.turned = mode == EMIT_ACCUM && runs_in_step(p.in, p.T, q.n_tile_items);
   return true;
 }
 

@@ -254,6 +254,33 @@ def test_update_with_its_state_requested_ahead_and_not(out, n_in, T, begin, end)
         _full_check(case, begin, end, check_accum=False)
 
 
+# The sum into g begins each XCD's run of tiles an eighth further on where the runs lie a power of two apart on rows of a power of two:
+# 64 and 66 small tiles an XCD (without and with edge rows), 64 large ones (32 Mi elements, more than 1000 tokens), 32 of 8192-wide
+# rows two to a tile row; 62 small tiles an XCD and 12288-wide rows stay in order.  Every element gets its gradient, as a call that stores it
+# gives it, exactly once.
+@pytest.mark.parametrize("out,n_in,T,begin,end", [
+    (4096, 4096, 33, 0, 4096 * 4096), (4128, 4096, 40, 4096 * 16 + 5, 4096 * 4112 + 5), (8192, 4096, 1025, 0, 8192 * 4096),
+    (2080, 8192, 17, 8192 * 8, 8192 * 2056), (4000, 4096, 33, 0, 4096 * 3968), (1400, 12288, 33, 12288 * 8 + 7, 12288 * 1373)])
+def test_sum_into_g_with_the_runs_of_the_xcds_turned_and_not(out, n_in, T, begin, end):
+    gen = torch.Generator(device=H.DEV).manual_seed(out + T)
+    X = torch.randn(T, n_in, generator=gen, device=H.DEV, dtype=torch.bfloat16)
+    dY = torch.randn(T, out, generator=gen, device=H.DEV, dtype=torch.bfloat16)
+    layer = B.make_layer(B.LINEAR, X, dY, out, n_in, split_k=1)
+    base = torch.randn(end - begin, generator=gen, device=H.DEV)
+    with H.phase_aligned(begin):
+        full_g, g = H.guarded(end - begin)
+        full_a, acc = H.guarded(end - begin, base)
+    B.chunkft_chunk_wgrad(layer, begin, end, g)
+    B.chunkft_chunk_wgrad(layer, begin, end, acc, accumulate=True)
+    torch.cuda.synchronize()
+    assert H.guards_intact(full_g) and H.guards_intact(full_a)
+    assert torch.equal(acc, base + g)
+    rows = torch.tensor([begin // n_in + 1, (begin + end) // 2 // n_in, (end - 1) // n_in - 1], device=H.DEV)
+    want = dY[:, rows].double().T @ X.double()
+    got = torch.stack([g[r * n_in - begin:(r + 1) * n_in - begin] for r in rows.tolist()]).double()
+    assert ((got - want).norm() / want.norm()).item() <= TOL_G[WL.BF16]
+
+
 # Layers without 16-byte rows on the 64 x 128 tile (17 x 17 tiles of 128 x 128: more than one per compute unit): the update stores
 # the next slab behind the two steps of a slab up to 512 tokens on rows that are whole 16-byte pieces, between them
 # otherwise; the gradient always between them.  _full_check holds the two orders to the same bits.
