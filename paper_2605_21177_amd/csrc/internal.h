@@ -96,7 +96,10 @@ Split pick_split(int32_t kind, int32_t dtype, int64_t out, int64_t in, int64_t T
 // one (two per compute unit) when it is compute-bound and its operands are too large to stay in
 // the last-level cache (shape.cpp).
 bool fused_takes_large_tile(const WgradProblem& p, int compute_units);
-bool update_requests_ahead(int64_t in, int64_t slab_tokens);   // of the update on the 128 x 256 tile
+// Whether the update on the 128 x 256 tile requests its state ahead: of a single call, and of a group (no for one segment is no
+// for all).
+bool update_requests_ahead(int64_t in, int64_t tokens);
+bool group_requests_ahead(int64_t tokens);
 
 // One segment of a grouped fused call: a bf16 matrix segment for the MFMA kernel (S = 1) or a
 // bf16 scale-vector segment whose normalised input the caller supplies.

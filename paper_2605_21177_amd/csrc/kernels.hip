@@ -161,8 +161,7 @@ __device__ __forceinline__ void tile_epilogue(const MfmaParams& q, unsigned char
     d.master = q.s.master + i;
     d.m = q.s.m + i;
     d.v = q.s.v + i;
-    d.W = q.s.w_kind == W_BF16 ? (void*)((unsigned short*)q.s.W + i + p.begin)
-                               : (void*)((float*)q.s.W + i + p.begin);
+    d.W = (unsigned short*)q.s.W + i + p.begin;                    // a bf16 copy or none (the launchers refuse others)
     return d;
   };
   // Rows that are read before they are written.  AHEAD (the sum into g; the update on 256-row tiles, and on 128-row tiles over few tokens): batches
@@ -284,8 +283,7 @@ __device__ __forceinline__ void tile_epilogue(const MfmaParams& q, unsigned char
         q.s.master[lo_i] = lo_th;
         q.s.m[lo_i] = lo_m;
         q.s.v[lo_i] = lo_v;
-        if (q.s.w_kind == W_BF16) ((unsigned short*)q.s.W)[lo_i + p.begin] = f32_to_bf16_rne(lo_th);
-        else if (q.s.w_kind == W_F32) ((float*)q.s.W)[lo_i + p.begin] = lo_th;
+        if (low) ((unsigned short*)q.s.W)[lo_i + p.begin] = f32_to_bf16_rne(lo_th);
       } else {
         emit<MODE>(q.s, E, slab, lo_i, lo_i + p.begin, lo_val);
       }
@@ -325,7 +323,7 @@ __device__ __forceinline__ void tile_epilogue(const MfmaParams& q, unsigned char
             if (ok[u]) {
               const float4 q4 = *reinterpret_cast<const float4*>(stage + ((j0 + u) * C::NW + wave) * C::EPI_PITCH + sft + c4);
               const f32x4_u val = {q4.x, q4.y, q4.z, q4.w};
-              finish4<MODE>(d[u], q.s.w_kind, q.s.c, val, st[u]);
+              finish4<MODE>(d[u], low ? W_BF16 : W_NONE, q.s.c, val, st[u]);
             }
           }
         }
@@ -1866,6 +1864,7 @@ bool sum_takes_short_batches(const WgradProblem& p, const RowSplit& rs) {
 }
 
 int launch_wgrad_bf16_mfma(const WgradProblem& p, int mode, const Sinks& s, void* stream) {
+  if (mode == EMIT_ADAMW && (s.w_kind == W_F32 || p.S > 1)) return (int)hipErrorInvalidValue;   // bf16 weights; slabs are summed first
   if (takes_small_tiles(p.in, p.T, p.begin, p.end, device_compute_units()) &&
       (mode == EMIT_ADAMW || !plain_leaves_small_tiles(p, device_compute_units())))
     return launch_wgrad_small(p, mode, s, stream);
@@ -1873,7 +1872,7 @@ int launch_wgrad_bf16_mfma(const WgradProblem& p, int mode, const Sinks& s, void
   // whose epilogue moves 26 bytes per element, gains from two workgroups per compute unit.
   if (mode == EMIT_ADAMW) {
     if (fused_takes_large_tile(p, device_compute_units())) return launch_mfma_cfg<MainCfg>(p, mode, s, (hipStream_t)stream);
-    if (update_requests_ahead(p.in, p.S > 1 ? p.kslab : p.T)) return launch_mfma_cfg<FusedCfg>(p, mode, s, (hipStream_t)stream);
+    if (update_requests_ahead(p.in, p.T)) return launch_mfma_cfg<FusedCfg>(p, mode, s, (hipStream_t)stream);
     return launch_mfma_one<FusedLongCfg, EMIT_ADAMW>(p, s, (hipStream_t)stream);
   }
   // The plain gradient takes whichever tile is faster for its number of tiles and tokens
@@ -1928,12 +1927,11 @@ static int launch_group_cfg(const GroupSegment* segs, int n, hipStream_t st) {
 
 int launch_fused_group(const GroupSegment* segs, int n, bool large_tile, void* stream) {
   if (n <= 0) return 0;
+  for (int i = 0; i < n; ++i)
+    if (!segs[i].vector && (segs[i].s.w_kind == W_F32 || segs[i].p.S > 1)) return (int)hipErrorInvalidValue;
   if (large_tile) return launch_group_cfg<MainCfg>(segs, n, (hipStream_t)stream);
-  // A group reads its state ahead up to 1024 tokens whatever the widths of its segments.  Blocks under 256 MiB and less in
-  // us, without / with: 4096 wide 300 tokens 1089 / 1053, 1024 tokens 1126 / 1118 (its 14336-wide segment without, the others
-  // with: 1120 where all without are 1106); 3072 wide 800 tokens 571 / 556; 2048 wide 1024 tokens 360 / 348.
   bool ahead = true;
-  for (int i = 0; i < n; ++i) ahead = ahead && (segs[i].vector || update_requests_ahead(1, segs[i].p.T));
+  for (int i = 0; i < n; ++i) ahead = ahead && (segs[i].vector || group_requests_ahead(segs[i].p.T));
   return ahead ? launch_group_cfg<FusedCfg>(segs, n, (hipStream_t)stream)
                : launch_group_cfg<FusedLongCfg>(segs, n, (hipStream_t)stream);
 }

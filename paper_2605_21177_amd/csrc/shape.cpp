@@ -144,14 +144,20 @@ bool fused_takes_large_tile(const WgradProblem& p, int compute_units) {
   return round_ratio * round_cost(w) / (round_cost(2.0 * w) / 2.0) < 0.99;
 }
 
-// Whether the update on 128-row tiles requests its state ahead (tile_epilogue in kernels.hip).  It does where the update's streams
-// decide, up to 1024 tokens (768 on rows of more than 8192 elements, which come in more and shorter pieces per tile
-// row).  Fused call in us, without / with, each at its start delay: 32 Mi elements of 4096-wide rows 256 tokens 163.4 / 159.4,
-// 512 tokens 176.8 / 167.3, 1024 tokens 182.5 / 179.5, 1300 tokens 192.7 / 187.8, 1500 tokens 195.8 / 196.1, 2048 tokens 218.5 / 222.8;
-// 64 Mi 1024 tokens 341 / 329; 48 Mi of 8192-wide rows 1024 tokens (64 Mi) 342.5 / 336.1, 1150 tokens 280.8 / 281.7, 1500 tokens
-// 292 / 297; 14336-wide rows 24 Mi 64 tokens 154.3 / 149.8, 24 Mi 1024 tokens 181.1 / 178.8, 50 Mi 310 / 314, 30 Mi 1300 tokens
-// 201 / 203, 40 Mi 2048 tokens 309 / 327.
-bool update_requests_ahead(int64_t in, int64_t slab_tokens) { return slab_tokens <= (in <= 8192 ? 1024 : 768); }
+// Whether the update on 128-row tiles requests its state ahead (tile_epilogue in kernels.hip): where the update's streams
+// decide and not the loops.  The lines are where measurements cross, per width and not per size: up to 1024 tokens, 768 on rows of more
+// than 8192 elements.  Fused call in us, without / with, each at its start delay:
+//   4096-wide rows, 32 Mi elements 256 tokens 163.4 / 159.4, 512 176.8 / 167.3, 1024 182.5 / 179.5, 1300 192.7 / 187.8, 1500 195.8 / 196.1,
+//   2048 218.5 / 222.8; 64 Mi 1024 341 / 329, 24 Mi 1024 137.8 / 140.3 (the most that it costs below the line);
+//   8192-wide, 64 Mi 1024 tokens 342.5 / 336.1, 40 Mi 1024 227.0 / 227.2, 48 Mi 1150 280.8 / 281.7, 1500 292 / 297;
+//   14336-wide, 24 Mi 64 tokens 154.3 / 149.8, 1024 181.1 / 178.8, 30 Mi 1300 201 / 203, 40 Mi 2048 309 / 327, 50 Mi 1024 310 / 314.
+// (At 1300 tokens 4096-wide rows would still gain, at 1150 8192-wide ones no longer: the line keeps to what both gain from.)
+bool update_requests_ahead(int64_t in, int64_t tokens) { return tokens <= (in <= 8192 ? 1024 : 768); }
+
+// A group up to 1024 tokens whatever the widths of its segments.  Planner chunks of a block in us, without / with: 4096-wide under
+// 256 MiB 300 tokens 1062 / 1032, 1024 tokens 1110 / 1105; under 128 MiB 1184 / 1165; 2048-wide 1024 tokens 352 / 340; 3072-wide 622 / 612; 4096-wide
+// with 11008 1009 / 997; groups of 14336-wide segments at 1024 tokens 179.8 / 180.4, 333.8 / 328.8, 637 / 629.
+bool group_requests_ahead(int64_t tokens) { return tokens <= 1024; }
 
 int64_t countable_run(int64_t in, int32_t S, int64_t bm, int64_t bn, int threads) {
   const int64_t tiles = kMaxLaunchThreads / threads / 8 * 8 / S;             // the grid is a multiple of the 8 XCDs
