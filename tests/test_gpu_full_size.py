@@ -544,3 +544,50 @@ def test_scale_vector_of_more_blocks_than_one_launch_takes(dtype, n):
     assert H.guards_intact(full) and bool(((g.double() - want).abs() <= 3 * 2.0 ** -23 * size).all())
     del want, size, prod
     _fused_equals_gradient_then_adamw(layer, n, g, dtype)
+
+
+# The rows of a tile are addressed by 32-bit offsets from its corner, which reach 2^31 bytes at the widest rows the
+# matrix-core tiles take (2^21 - 8 elements; two tile rows of 128, one of 256).  33 tokens: 128-row tiles, the update and the sum
+# with their rows requested ahead; 1024: the sum on the 256-row tile; 5952: the update on it.
+@pytest.mark.parametrize("T", [33, 1024, 5952])
+def test_widest_rows_of_the_matrix_core_tiles(T):
+    out, n_in = 256, (1 << 21) - 8
+    end = out * n_in
+    gen = torch.Generator(device=H.DEV).manual_seed(T)
+    X = torch.randn(T, n_in, generator=gen, device=H.DEV, dtype=torch.bfloat16)
+    dY = torch.randn(T, out, generator=gen, device=H.DEV, dtype=torch.bfloat16) * 1e-3
+    layer = B.make_layer(B.LINEAR, X, dY, out, n_in)
+    _say(f"{out}x{n_in} T={T}")
+    full_g, g = H.guarded(end)
+    B.chunkft_chunk_wgrad(layer, 0, end, g)
+    torch.cuda.synchronize()
+    assert H.guards_intact(full_g)
+    rows = torch.tensor([0, 127, 128, 255], device=H.DEV)
+    cols = torch.cat([torch.arange(lo, lo + 300, device=H.DEV) for lo in (0, n_in // 2, n_in - 300)])
+    want = dY[:, rows].double().T @ X[:, cols].double()
+    assert ((g.view(out, n_in)[rows][:, cols] - want).norm() / want.norm()).item() <= 3e-3
+    if T != 5952:
+        full_a, acc = H.guarded(end, torch.full((end,), 0.25, device=H.DEV))
+        B.chunkft_chunk_wgrad(layer, 0, end, acc, accumulate=True)
+        torch.cuda.synchronize()
+        assert H.guards_intact(full_a) and torch.equal(acc, g + 0.25)
+        del full_a, acc
+    if T != 1024:
+        W0 = torch.randn(end, generator=gen, device=H.DEV, dtype=torch.bfloat16) * 0.02
+        state0 = (W0.float(), torch.randn(end, generator=gen, device=H.DEV) * 1e-3, torch.rand(end, generator=gen, device=H.DEV) * 1e-6)
+        hp = B.hparams(step=3, **HP)
+        results = []
+        for fused in (True, False):
+            fulls, state = zip(*(H.guarded(end, s) for s in state0))
+            W = W0.clone()
+            if fused:
+                B.chunkft_wgrad_adamw_fused(layer, 0, end, W, *state, hp)
+            else:
+                B.chunkft_adamw_chunk(g, *state, W, end, hp)
+            torch.cuda.synchronize()
+            assert all(H.guards_intact(f) for f in fulls)
+            results.append((*state, W))
+            del fulls
+        for name, a, b in zip(("master", "m", "v", "W"), *results):
+            assert torch.equal(a, b), f"{name} of the fused call differs from the un-fused pair"
+        assert not torch.equal(results[0][3], W0)

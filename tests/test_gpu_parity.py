@@ -241,7 +241,7 @@ def test_bf16_long_token_count_takes_the_large_tile_in_the_fused_call(begin, end
 
 
 # The update on 128-row tiles requests its state ahead up to 1024 tokens (768 on rows of more than 8192 elements), not
-# beyond; begin % 4 is the column at which a tile's 16-byte groups start.  Last tile rows of 8 and 9 - 40 rows, a last
+# beyond; begin % 4 is the column at which a tile's 16-byte groups start.  Last tile rows of 8, 127 and 30 rows, a last
 # column tile of 8 columns (2312 = 9 x 256 + 8, 8200 = 32 x 256 + 8).
 @pytest.mark.parametrize("out,n_in,T,begin,end", [
     (2072, 2312, 1024, 2312 * 3 + 1, 2312 * 2064), (2072, 2312, 1025, 2312 * 3 + 1, 2312 * 2064),
@@ -842,6 +842,42 @@ def test_grouped_call_on_random_groups_of_every_kind(seed):
         for si, (a, g) in enumerate(zip(single, group)):
             for name, x, y in zip(("W", "master", "m", "v"), a, g):
                 assert torch.equal(x, y), f"case {it} segment {si} ({desc[si]}): {name} differs"
+
+
+# A group requests its state ahead if none of its matrix segments has more than 1024 tokens: all at the line, all beyond it, and one beyond
+# it among others.  Edge rows, left-over columns (begin % 4), a scale vector of more tokens than the matrices.
+@pytest.mark.parametrize("tokens", [(1024, 1024, 1024), (1025, 1025, 1025), (1024, 1100, 40)])
+def test_grouped_call_with_its_state_requested_ahead_and_not(tokens):
+    rng = np.random.default_rng([107, *tokens])
+    shapes = [(520, 776, 776 * 3 + 1, 776 * 517 + 9), (776, 264, 264 * 8 + 6, 264 * 776), (264, 1032, 0, 1032 * 264)]
+    segs = [(WL.linear_case(rng, f"m{i}", out, n_in, T, WL.BF16, 1e-3), b, e, 1)
+            for i, ((out, n_in, b, e), T) in enumerate(zip(shapes, tokens))]
+    segs.append((WL.vector_case(rng, "v", 776, 1300, WL.BF16, 1e-3), 3, 770, 0))
+    dls = [H.DeviceLayer(case, sk) for case, _, _, sk in segs]
+    hp = B.hparams(step=3, **HP)
+
+    def run(grouped):
+        calls, fulls = [], []
+        for i, ((case, b, e, _), dl) in enumerate(zip(segs, dls)):
+            gen = torch.Generator().manual_seed(i)
+            parts = [H.guarded(e - b, x) for x in (case.W0.reshape(-1)[b:e].float(), torch.randn(e - b, generator=gen) * 1e-3,
+                                                   (0.25 + torch.randn(e - b, generator=gen) ** 2) * 1e-6)]
+            fulls += [f for f, _ in parts]
+            calls.append((dl.layer(), b, e, case.W0.reshape(-1).clone().to(H.DEV), *(x for _, x in parts)))
+        if grouped:
+            B.GroupCall(calls, device=H.DEV)(hp)
+        else:
+            for layer, b, e, W, master, m, v in calls:
+                B.chunkft_wgrad_adamw_fused(layer, b, e, W, master, m, v, hp)
+        torch.cuda.synchronize()
+        assert all(H.guards_intact(f) for f in fulls)
+        return [c[3:] for c in calls]
+
+    for i, (single, group) in enumerate(zip(run(False), run(True))):
+        for name, x, y in zip(("W", "master", "m", "v"), single, group):
+            assert torch.equal(x, y), f"segment {i}: {name} differs"
+        case, b, e, _ = segs[i]
+        assert not torch.equal(group[1].cpu(), case.W0.reshape(-1)[b:e].float())      # updated
 
 
 def test_grouped_call_runs_what_its_kernel_cannot_take_by_itself():
