@@ -174,7 +174,7 @@ __device__ __forceinline__ void tile_epilogue(const MfmaParams& q, unsigned char
   // finished: the loops decide there, and with twice the requests in flight the update takes more of the memory from
   // the loop beside it than it gains (2048 tokens 218 us, with the pipeline 223; 40 Mi of 14336-wide rows 309 against 326).
   constexpr bool AHEAD = MODE == EMIT_ACCUM || (MODE == EMIT_ADAMW && C::AHEAD);
-  constexpr int RPT = MODE == EMIT_ACCUM && C::AHEAD ? 8 : 4, NB = HALF_ROWS / C::NW / RPT;
+  constexpr int RPT = MODE == EMIT_ACCUM ? 8 : 4, NB = HALF_ROWS / C::NW / RPT;
   static_assert(NB * RPT * C::NW == HALF_ROWS, "whole batches");
   constexpr int kNowhere = (int)0x80000000;                        // past every descriptor's end
   // (read once into scalar registers: a value that the compiler fetches again behind a lane-dependent branch makes
@@ -1756,7 +1756,7 @@ using MainCfg = RingCfg<2, 4, 16>;
 // other shape its loops were 10 % slower).  The two shapes give the same bits: the hardware adds the
 // tokens of either in the same order.
 using FusedCfg = RingCfg<1, 3, 32>;         // (the fused call, and plain gradients with few tiles)
-using FusedLongCfg = RingCfg<1, 3, 32, false>;   // the fused call and the sum into g over more tokens (update_requests_ahead, sum_takes_short_batches)
+using FusedLongCfg = RingCfg<1, 3, 32, false>;   // the fused call over more tokens (update_requests_ahead)
 
 template <class C, int MODE>
 int launch_mfma_mode(const MfmaParams& q, int grid, hipStream_t st) {
@@ -1838,29 +1838,24 @@ bool fill_mfma_params(const WgradProblem& p, int mode, const Sinks& s, const Row
   return true;
 }
 
-template <class C, int MODE>
-int launch_mfma_one(const WgradProblem& p, const Sinks& s, hipStream_t st) {
+template <class C>
+int launch_update_cfg(const WgradProblem& p, const Sinks& s, hipStream_t st) {
   MfmaParams q;
-  if (!fill_mfma_params<C>(p, MODE, s, split_rows(p), q)) return (int)hipErrorInvalidValue;   // work items are counted in 32 bits
-  return launch_mfma_mode<C, MODE>(q, (q.n_tile_items + 7) / 8 * 8, st);
+  if (!fill_mfma_params<C>(p, EMIT_ADAMW, s, split_rows(p), q)) return (int)hipErrorInvalidValue;   // work items are counted in 32 bits
+  return launch_mfma_mode<C, EMIT_ADAMW>(q, (q.n_tile_items + 7) / 8 * 8, st);
 }
 
 template <class C>
 int launch_mfma_cfg(const WgradProblem& p, int mode, const Sinks& s, hipStream_t st) {
+  if (mode == EMIT_ADAMW) return launch_update_cfg<C>(p, s, st);
+  MfmaParams q;
+  if (!fill_mfma_params<C>(p, mode, s, split_rows(p), q)) return (int)hipErrorInvalidValue;
+  const int grid = (q.n_tile_items + 7) / 8 * 8;
   switch (mode) {
-    case EMIT_STORE: return launch_mfma_one<C, EMIT_STORE>(p, s, st);
-    case EMIT_ACCUM: return launch_mfma_one<C, EMIT_ACCUM>(p, s, st);
-    case EMIT_PARTIAL: return launch_mfma_one<C, EMIT_PARTIAL>(p, s, st);
-    default: return launch_mfma_one<C, EMIT_ADAMW>(p, s, st);
+    case EMIT_STORE: return launch_mfma_mode<C, EMIT_STORE>(q, grid, st);
+    case EMIT_ACCUM: return launch_mfma_mode<C, EMIT_ACCUM>(q, grid, st);
+    default: return launch_mfma_mode<C, EMIT_PARTIAL>(q, grid, st);
   }
-}
-
-// The sum into g on 128-row tiles leaves in batches of four rows, not eight, over more than 1792 tokens where there is more than a round of tiles: with
-// eight it takes more of the memory from the loop beside it than it gains.  In us, eight / four (four, each batch requested, awaited and finished):
-// 4096-wide rows 40 Mi elements 1700 tokens 147.2 / 145.2 (152.1), 2048 tokens 169.1 / 163.8 (168.1), 2800 tokens 218.7 / 215.6 (218.9);
-// 24 Mi 1700 tokens 94.3 / 95.1, 2800 tokens 137.2 / 135.9; less than a round, 6 Mi of 2312-wide rows 2048 tokens 41.3 / 42.1.
-bool sum_takes_short_batches(const WgradProblem& p, const RowSplit& rs) {
-  return p.T > 1792 && ceil_div(rs.rb1 - rs.rb0, FusedCfg::BM) * ceil_div(p.in, FusedCfg::BN) > 2 * device_compute_units();
 }
 
 int launch_wgrad_bf16_mfma(const WgradProblem& p, int mode, const Sinks& s, void* stream) {
@@ -1873,7 +1868,7 @@ int launch_wgrad_bf16_mfma(const WgradProblem& p, int mode, const Sinks& s, void
   if (mode == EMIT_ADAMW) {
     if (fused_takes_large_tile(p, device_compute_units())) return launch_mfma_cfg<MainCfg>(p, mode, s, (hipStream_t)stream);
     if (update_requests_ahead(p.in, p.T)) return launch_mfma_cfg<FusedCfg>(p, mode, s, (hipStream_t)stream);
-    return launch_mfma_one<FusedLongCfg, EMIT_ADAMW>(p, s, (hipStream_t)stream);
+    return launch_update_cfg<FusedLongCfg>(p, s, (hipStream_t)stream);
   }
   // The plain gradient takes whichever tile is faster for its number of tiles and tokens
   // (plain_takes_large_tile, csrc/shape.cpp); every element is summed over the tokens in the same
@@ -1881,10 +1876,8 @@ int launch_wgrad_bf16_mfma(const WgradProblem& p, int mode, const Sinks& s, void
   const RowSplit rs = split_rows(p);
   const int64_t big_tiles = ceil_div(rs.rb1 - rs.rb0, MainCfg::BM) * ceil_div(p.in, MainCfg::BN) * p.S;
   const int64_t slab_tokens = p.S > 1 ? p.kslab : p.T;
-  if (!plain_takes_large_tile(big_tiles, slab_tokens, device_compute_units())) {
-    if (mode == EMIT_ACCUM && sum_takes_short_batches(p, rs)) return launch_mfma_one<FusedLongCfg, EMIT_ACCUM>(p, s, (hipStream_t)stream);
+  if (!plain_takes_large_tile(big_tiles, slab_tokens, device_compute_units()))
     return launch_mfma_cfg<FusedCfg>(p, mode, s, (hipStream_t)stream);
-  }
   return launch_mfma_cfg<MainCfg>(p, mode, s, (hipStream_t)stream);
 }
 
