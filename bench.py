@@ -33,7 +33,7 @@ PEAK_HBM_GBPS = 8000.0        # HBM3E
 # HBM bytes per launch at this workload from rocprofv3 --pmc runs (FETCH_SIZE, then WRITE_SIZE,
 # each scaled by what the counter reads for the plain copy of --copy-probe: x2.000 and x1.000);
 # the summary of those runs is profiles/bench_llama8b_upproj_hbm_traffic.txt.
-MEASURED_TRAFFIC = {"wgrad": 237.8e6, "adamw": 1006.7e6, "fused": 1048.8e6}
+MEASURED_TRAFFIC = {"wgrad": 237.9e6, "adamw": 1006.7e6, "fused": 1048.0e6}
 
 
 def main():

@@ -166,11 +166,14 @@ __device__ __forceinline__ void tile_epilogue(const MfmaParams& q, unsigned char
   };
   // Rows that are read before they are written.  AHEAD (the sum into g; the update on 256-row tiles, and on 128-row tiles over few tokens): batches
   // of RPT rows in a pipeline, the state of the next batch requested before the present one is finished, across the two
-  // halves, the first before the tile is staged; a batch's stores are then younger than the next batch's loads, whose
-  // wait does not include them.  The accesses are buffer forms whose range check drops what is not there (a row past the
-  // body, a group of four past the row), so that no branch lies between a load and its use and the compiler can count what
-  // is in flight.  32 Mi elements of 4096-wide rows, fused call: 512 tokens 176.8 -> 167.3 us, 1024 tokens 182.5 ->
-  // 179.5; two gradients and the optimizer pass 335 -> 330.  Else (the update of 128-row tiles over more tokens) a batch is requested, awaited and
+  // halves, the first before the tile is staged; a batch's stores are then younger than the next batch's loads.  The fp32
+  // accesses are buffer forms whose range check drops what is not there (a row past the body, a group of four past the
+  // row), so that no branch lies around them and the compiler counts what is in flight: the wait for a batch's loads leaves the stores of the batch
+  // before it in flight.  (In the update the up to four bf16 stores of a batch do lie behind branches and are not counted; where they
+  // were issued the last wait of the next batch takes in as many of the older fp32 stores.  Edge rows, one element at a time behind the
+  // first request, wait for everything in flight.)  32 Mi elements of 4096-wide rows, fused call: 512 tokens
+  // 176.8 -> 167.3 us, 1024 tokens 182.5 -> 179.5; sum into g, 24 Mi, 256 tokens 49.9 -> 42.5, 1024 tokens 79.4 -> 67.8.  Else (the
+  // update of 128-row tiles over more tokens) a batch is requested, awaited and
   // finished: the loops decide there, and with twice the requests in flight the update takes more of the memory from
   // the loop beside it than it gains (2048 tokens 218 us, with the pipeline 223; 40 Mi of 14336-wide rows 309 against 326).
   constexpr bool AHEAD = MODE == EMIT_ACCUM || (MODE == EMIT_ADAMW && C::AHEAD);

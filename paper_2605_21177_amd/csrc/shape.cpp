@@ -127,11 +127,14 @@ bool plain_takes_large_tile(int64_t large_tiles, int64_t slab_tokens, int comput
 }
 
 // Which tile the fused call takes.  Its AdamW epilogue is HBM-bound and overlaps the partner's loop
-// only on the small tile, so the large tile pays only when the loops dominate: measured ratio of the
-// large tile's time to the small one's on fully filled rounds 1.05 - 1.10 at 3072 - 4096 tokens, 0.98 -
-// 0.99 (in = 4096) and 0.89 (in = 8192) at 6144, 0.84 - 0.93 at 8192, fitted by 0.55 + 2600 / T; partly
-// filled rounds are priced as for the plain gradient.  The rule agrees with the faster tile in all 16
-// measured cases (four shapes x 3072 - 8192 tokens; X from 24 to 224 MiB).
+// only on the small tile, so the large tile pays only when the loops dominate: the ratio of the large tile's time
+// to the small one's on fully filled rounds was fitted by 0.55 + 2600 / T, and partly filled rounds are priced as for the plain
+// gradient, before either tile's update took its present form (the small one's requests its state ahead up to 1024 tokens, the
+// large one's always, and no unit of it starts late).  With the present kernels the rule is within 3 % of the faster tile in 49 of 54
+// measured cases (nine shapes of 1 - 16 rounds, 2048 - 8192 tokens).  In the other five, of many rounds at 4096 - 6144 tokens, it takes the small tile
+// where the large one is ahead: 256 Mi of 4096-wide rows 4096 tokens 2642 / 2563 us, 5120 tokens 3100 / 2909, 200 Mi of 8192-wide 5120 tokens 2340 / 2265 and 6144 tokens
+// 2796 / 2605, 100 Mi of 14336-wide 6144 tokens 1534 / 1380.  (32 Mi of 4096-wide rows, small / large: 3072 tokens 261 / 312, 5120 365 / 398, 6144
+// 419 / 426, 8192 542 / 510.)
 bool fused_takes_large_tile(const WgradProblem& p, int compute_units) {
   const double cus = compute_units > 0 ? compute_units : kDefaultComputeUnits;
   const RowSplit rs = split_rows(p);
