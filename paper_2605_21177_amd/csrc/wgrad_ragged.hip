@@ -289,8 +289,9 @@ int launch_update_behind(const WgradProblem& p, const Sinks& s, hipStream_t st) 
 //   2705 x 2907, 1.5 Mi elements, 1024 tokens (115 tiles of 128 x 128): 16.6 / 32.8, 19.7 / 42.5, 16.3 / 27.7 us;
 //   32003 x 4096, 12 Mi elements, 1536 tokens: 80 / 121, 67 / 118 us;
 //   1001 x 1003, 1024 tokens (64 tiles): 15.4 / 26.4, 20.3 / 45.6, 12.2 / 18.7 us.
-// (Before the slab was stored between the steps; since then 122, 214, 27, 113 and 18 us for the tiles chosen.)
-// The update's streams (82 us of the 122) run under the loops of the other workgroups of a compute unit, of
+// (Before the slab was stored between the steps and the waves of a 64 x 64 tile went without the barrier; since then 70 / 123, 98 / 204, 14.8 /
+// 26.5, 66 / 111 and 10.0 / 17.1 us for the tiles chosen.)
+// The update's streams (82 us of the 123) run under the loops of the other workgroups of a compute unit, of
 // which the 64 x 128 tile leaves more room for; with more tokens the loop decides, and the larger tile reads
 // its operands fewer times.  Every mode of a call takes the same tile: the order of the sum is the same.
 int launch_wgrad_ragged(const WgradProblem& p, int mode, const Sinks& s, void* stream) {
